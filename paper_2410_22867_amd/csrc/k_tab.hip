@@ -155,11 +155,49 @@ struct TabArgs {
 };
 
 // Work layout: one wavefront per centre atom and neighbour section (columns
-// of the net taken from a per-work-group counter as in the MLP kernels);
-// lanes 16 r + f work on row r of a group of four rows and on features
-// f, f + 16, ... (NF = m1 / 16 rounded up per lane), so a coefficient load
-// of 16 lanes is 128 contiguous bytes and every row's sums over features
-// reduce over 16 lanes.
+// of the net taken from a per-work-group counter as in the MLP kernels).
+//
+// Window.  48 bytes of coefficients per row and feature (5 GB at water12k)
+// made the table's trip from L2 the bound of both kernels.  Most rows lie at
+// small x (s(r) falls to 0 at the cut-off: 9 of 10 water rows at x < 3, 30 of
+// the 1,475 intervals), so a work-group of WPB = 16 waves, one per CU, keeps
+// the first A.nk intervals of its net in LDS, [interval][feature][power] with
+// the interval stride an odd number of 16-byte units: lanes that read
+// neighbouring intervals, or neighbouring features, fall in different banks.
+// Rows past the window read L2.  Frames of few columns take 4-wave
+// work-groups and no window (launch_embed_tab).  water12k: forward 395 ->
+// 103 us, backward 418 -> 187 us; copper of 23,328 atoms 2,175 -> 346 and
+// 1,746 -> 596 us.  The backward is now bound by LDS reads (4.8 KB per window
+// row of 64 lanes at 128 bytes per cycle: ~100 us), the forward by issue.
+template <int M1>
+struct TabWin {
+  static constexpr int stride = 6 * M1 + 2;                   // doubles per interval
+  static constexpr int most = (148 * 1024) / (8 * stride);    // intervals that fit: 31 (m1 = 100), 24 (128)
+};
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+// Copies the window's nk intervals of a net's table [k][p][a] to LDS
+// [k][a][p]: two features per thread and read, every read requested before
+// the first is used.
+template <int M1, int NT>
+__device__ __forceinline__ void tab_stage(const double* __restrict__ tabnet, int nk, double* __restrict__ tw) {
+  constexpr int NL = (TabWin<M1>::most * 3 * M1 + NT - 1) / NT;
+  const int total = nk * 3 * M1;
+  d2 x[NL];
+#pragma unroll
+  for (int l = 0; l < NL; ++l) x[l] = *reinterpret_cast<const d2*>(tabnet + 2 * min((int)threadIdx.x + l * NT, total - 1));
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    const int e = threadIdx.x + l * NT;
+    if (e >= total) break;
+    const int k = e / (3 * M1), pa = e - k * 3 * M1, p = pa / (M1 / 2), a = 2 * (pa - p * (M1 / 2));
+    double* w = tw + k * TabWin<M1>::stride + a * 6 + p;
+    w[0] = x[l][0];
+    w[6] = x[l][1];
+  }
+}
+
 #define DPSE_TAB_PROLOGUE                                                  \
   int grp = 0, ngrp = 1;                                                  \
   const int net = net_of_group(A.meta, A.sec, A.ntypes, gridDim.x, blockIdx.x, &grp, &ngrp); \
@@ -170,136 +208,280 @@ struct TabArgs {
   const int c_hi = (int)((int64_t)n_t * (grp + 1) / ngrp);                \
   if (c_lo >= c_hi) return;                                               \
   const int lane = threadIdx.x & 63;                                      \
-  const int fl = lane & 15, rg = lane >> 4;                               \
   int* const next_col = A.ctr + blockIdx.x * 32;                          \
   if (threadIdx.x == 0) atomicExch(next_col, c_lo);                       \
+  const double* tabnet = A.table + (int64_t)net * A.g.nint * 6 * M1;      \
+  constexpr bool WIN = WPB == 16;                                         \
+  constexpr int TS = TabWin<M1>::stride;                                  \
+  __shared__ __attribute__((aligned(16))) double tw[WIN ? TabWin<M1>::most * TS : 2]; \
+  const int nk = WIN ? min(TabWin<M1>::most, A.g.nint) : 0;               \
+  if constexpr (WIN) tab_stage<M1, 64 * WPB>(tabnet, nk, tw);             \
   __syncthreads();                                                        \
   auto take = [&]() {                                                     \
     int k = 0;                                                            \
     if (lane == 0) k = atomicAdd(next_col, 1);                            \
     return k;                                                             \
-  };                                                                      \
-  const double* tabnet = A.table + (int64_t)net * A.g.nint * 6 * M1;
+  };
 
-template <int M1>
-__global__ __launch_bounds__(256) void k_embed_fwd_tab(TabArgs A) {
-  constexpr int NF = (M1 + 15) / 16;
+// Reads through the constant address space: a wave-uniform address then
+// becomes one scalar load for the wave (the buffers read so are written by
+// earlier kernels only).
+typedef const __attribute__((address_space(4))) double* cdouble_p;
+__device__ __forceinline__ cdouble_p uniform_ptr(const double* p) {
+  const unsigned long long a = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  return (cdouble_p)(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double readlane_d(double x, int l) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, l);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Forward: lanes are features (two per lane: l and l + M1/2), rows are taken
+// one after another with their input wave-uniform.  A section is sorted by
+// distance, so rows of one interval follow each other and its coefficients
+// stay in registers from row to row; no sum crosses lanes.  Correct for any
+// order of the rows.
+template <int M1, int WPB>
+__global__ __launch_bounds__(64 * WPB) void k_embed_fwd_tab(TabArgs A) {
+  constexpr int MH = M1 / 2;  // features l and l + MH of lane l < MH
+  static_assert(MH <= 64 && M1 % 2 == 0, "two features per lane");
   DPSE_TAB_PROLOGUE
+  const int fl = lane < MH ? lane : MH - 1;  // the lanes past MH repeat the last and store nothing
   bool clipped = false;
   for (int c_next = take();;) {
-    const int c = __builtin_amdgcn_readfirstlane(__shfl(c_next, 0, 64));
+    const int c = __builtin_amdgcn_readfirstlane(c_next);
     if (c >= c_hi) break;
     c_next = take();
     const int col = cb + c;
-    const int i = A.atom_at[col];
-    const int nn = A.nnei[i * kMaxT + tj];
+    const int i = __builtin_amdgcn_readfirstlane(A.atom_at[col]);
+    const int nn = __builtin_amdgcn_readfirstlane(A.nnei[i * kMaxT + tj]);
     const double* Rs = A.R + ((int64_t)i * A.nm + A.sec[tj]) * 4;
-    double acc[NF][4];
+    const cdouble_p Ru = uniform_ptr(Rs);
+    double acc[2][4];
 #pragma unroll
-    for (int u = 0; u < NF; ++u)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc[u][k] = 0.0;
-    const env_rsrc_t Rb = env_rsrc(Rs, nn);
-    d4 Rn = env_row(Rb, rg);
-    for (int r0 = 0; r0 < nn; r0 += 4) {
-      const int row = r0 + rg;
-      const d4 Rv = Rn;  // zero past the section's real rows
-      Rn = env_row(Rb, row + 4);
+      for (int q = 0; q < 4; ++q) acc[u][q] = 0.0;
+    double cf[2][6];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int p = 0; p < 6; ++p) cf[u][p] = 0.0;
+    int kcur = -1;
+    for (int r0 = 0; r0 < nn; r0 += 64) {
+      // interval and offset of 64 rows, one per lane
+      const int row = r0 + lane;
       double t;
       bool cl;
-      const int k = tab_interval(A.g, Rv[0], t, cl);
+      const int kl = tab_interval(A.g, row < nn ? Rs[(int64_t)row * 4] : 0.0, t, cl);
       clipped |= cl && row < nn;
-      const double* cf = tabnet + (int64_t)k * 6 * M1 + fl;
+      const int nr = min(64, nn - r0);
+      for (int r = 0; r < nr; ++r) {
+        const int k = __builtin_amdgcn_readlane(kl, r);
+        const double tr = readlane_d(t, r);
+        const double R0 = Ru[(r0 + r) * 4], R1 = Ru[(r0 + r) * 4 + 1], R2 = Ru[(r0 + r) * 4 + 2],
+                     R3 = Ru[(r0 + r) * 4 + 3];
+        if (k != kcur) {
+          kcur = k;
+          if (k < nk) {
+            const double* cw = tw + k * TS + fl * 6;
 #pragma unroll
-      for (int u = 0; u < NF; ++u) {
-        if (M1 % 16 != 0 && fl + 16 * u >= M1) break;
-        const double* cu = cf + 16 * u;
-        double G = cu[5 * M1];
-        G = fma(G, t, cu[4 * M1]);
-        G = fma(G, t, cu[3 * M1]);
-        G = fma(G, t, cu[2 * M1]);
-        G = fma(G, t, cu[M1]);
-        G = fma(G, t, cu[0]);
+            for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[u][q] = fma(G, Rv[q], acc[u][q]);
+              for (int p = 0; p < 6; p += 2) {
+                const d2 x = *reinterpret_cast<const d2*>(cw + u * MH * 6 + p);
+                cf[u][p] = x[0];
+                cf[u][p + 1] = x[1];
+              }
+          } else {
+            const double* cg = tabnet + (int64_t)k * 6 * M1 + fl;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+              for (int p = 0; p < 6; ++p) cf[u][p] = cg[p * M1 + u * MH];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          double G = cf[u][5];
+#pragma unroll
+          for (int p = 4; p >= 0; --p) G = fma(G, tr, cf[u][p]);
+          acc[u][0] = fma(G, R0, acc[u][0]);
+          acc[u][1] = fma(G, R1, acc[u][1]);
+          acc[u][2] = fma(G, R2, acc[u][2]);
+          acc[u][3] = fma(G, R3, acc[u][3]);
+        }
       }
     }
-    // sum the four row groups; lanes of row group 0 write T (scaled 1/nm)
     double* T = A.Tpart + tj * A.tpart_stride + (int64_t)col * M1 * 4;
+    if (lane < MH) {
 #pragma unroll
-    for (int u = 0; u < NF; ++u) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double v = acc[u][q];
-        v += shfl_xor_d(v, 16);
-        v += shfl_xor_d(v, 32);
-        acc[u][q] = v * A.inv_nm;
-      }
-      const int a = fl + 16 * u;
-      if (rg == 0 && a < M1) *reinterpret_cast<d4*>(T + a * 4) = d4{acc[u][0], acc[u][1], acc[u][2], acc[u][3]};
+      for (int u = 0; u < 2; ++u)
+        *reinterpret_cast<d4*>(T + (lane + u * MH) * 4) =
+            d4{acc[u][0] * A.inv_nm, acc[u][1] * A.inv_nm, acc[u][2] * A.inv_nm, acc[u][3] * A.inv_nm};
     }
   }
   if (__ballot(clipped) && lane == 0) set_flag(A.flags, DP_FLAG_TABLE_RANGE);
 }
 
+// Sum over the 64 lanes of four values at once: two half-wave swaps fold the
+// four into one register, value q in lane row q (lanes 16 q ..), which a
+// 16-lane tree then sums; every lane of row q returns the sum of x[q].
+__device__ __forceinline__ double swap_add32(double a, double b) {  // lanes < 32: a of both halves, else b
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+         __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ double swap_add16(double a, double b) {  // even 16-lane rows: a of the row pair, odd: b
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+         __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum4(const double x[4]) {
+  // rows 0, 1, 2, 3 of the result hold x[0], x[1], x[2], x[3]: the 32-lane
+  // swap splits {0, 2} and {1, 3}, the 16-lane swap the members
+  double v = swap_add16(swap_add32(x[0], x[2]), swap_add32(x[1], x[3]));
+  v = dpp_add<0xb1>(v);   // quad_perm [1, 0, 3, 2]
+  v = dpp_add<0x4e>(v);   // quad_perm [2, 3, 0, 1]
+  v = dpp_add<0x141>(v);  // row_half_mirror
+  return dpp_add<0x140>(v);  // row_mirror
+}
+
 // Backward: per row, dE/dG_a = g_T[a] . R~ / nm, the direct term
 // dE/dR~ = sum_a g_T[a] G_a / nm and dE/dx = sum_a dE/dG_a dG_a/dx.
-template <int M1>
-__global__ __launch_bounds__(256) void k_embed_bwd_tab(TabArgs A) {
-  constexpr int NF = (M1 + 15) / 16;
+// Rows of the window: lanes are rows, the features are taken one after
+// another with g_T wave-uniform, so no sum crosses lanes (three 16-byte LDS
+// reads and 18 multiply-adds per row and feature).  The others (and every row
+// without a window), one at a time: lanes are features as in the forward,
+// coefficients from L2 kept while the interval stays, four sums over the wave.
+template <int M1, int WPB>
+__global__ __launch_bounds__(64 * WPB) void k_embed_bwd_tab(TabArgs A) {
+  constexpr int MH = M1 / 2;
   DPSE_TAB_PROLOGUE
+  const int fl = lane < MH ? lane : MH - 1;
   for (int c_next = take();;) {
-    const int c = __builtin_amdgcn_readfirstlane(__shfl(c_next, 0, 64));
+    const int c = __builtin_amdgcn_readfirstlane(c_next);
     if (c >= c_hi) break;
     c_next = take();
     const int col = cb + c;
-    const int i = A.atom_at[col];
-    const int nn = A.nnei[i * kMaxT + tj];
+    const int i = __builtin_amdgcn_readfirstlane(A.atom_at[col]);
+    const int nn = __builtin_amdgcn_readfirstlane(A.nnei[i * kMaxT + tj]);
     const int64_t rbase = (int64_t)i * A.nm + A.sec[tj];
-    const double* Rs = A.R + rbase * 4;
-    double gt[NF][4];
+    const env_rsrc_t Rb = env_rsrc(A.R + rbase * 4, nn);
     const double* gcol = A.gT + (int64_t)col * M1 * 4;
+    const cdouble_p gu = uniform_ptr(gcol);
+    const cdouble_p Ru = uniform_ptr(A.R + rbase * 4);
+    // g_T of the lane's two features, zero in the lanes past MH
+    d4 gt[2];
 #pragma unroll
-    for (int u = 0; u < NF; ++u) {
-      const int a = fl + 16 * u;
-      d4 v = {0.0, 0.0, 0.0, 0.0};
-      if (a < M1) v = *reinterpret_cast<const d4*>(gcol + a * 4);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) gt[u][q] = v[q] * A.inv_nm;
+    for (int u = 0; u < 2; ++u) {
+      gt[u] = *reinterpret_cast<const d4*>(gcol + (fl + u * MH) * 4);
+      if (lane >= MH) gt[u] = d4{0.0, 0.0, 0.0, 0.0};
     }
-    const env_rsrc_t Rb = env_rsrc(Rs, nn);
-    d4 Rn = env_row(Rb, rg);
-    for (int r0 = 0; r0 < nn; r0 += 4) {
-      const int row = r0 + rg;
-      const d4 Rv = Rn;
-      Rn = env_row(Rb, row + 4);
+    for (int r0 = 0; r0 < nn; r0 += 64) {
+      const int row = r0 + lane;
+      const d4 Rv = env_row(Rb, row);  // zero past the section's real rows
       double t;
       bool cl;
       const int k = tab_interval(A.g, Rv[0], t, cl);
-      const double* cf = tabnet + (int64_t)k * 6 * M1 + fl;
-      double ds = 0.0, dr[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int u = 0; u < NF; ++u) {
-        if (M1 % 16 != 0 && fl + 16 * u >= M1) break;
-        const double* cu = cf + 16 * u;
-        const double c5 = cu[5 * M1], c4 = cu[4 * M1], c3 = cu[3 * M1], c2 = cu[2 * M1], c1 = cu[M1], c0 = cu[0];
-        double G = fma(fma(fma(fma(fma(c5, t, c4), t, c3), t, c2), t, c1), t, c0);
-        double Gp = fma(fma(fma(fma(5.0 * c5, t, 4.0 * c4), t, 3.0 * c3), t, 2.0 * c2), t, c1);
-        if (cl) Gp = 0.0;
-        const double dG = fma(gt[u][0], Rv[0], fma(gt[u][1], Rv[1], fma(gt[u][2], Rv[2], gt[u][3] * Rv[3])));
-        ds = fma(dG, Gp, ds);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) dr[q] = fma(gt[u][q], G, dr[q]);
+      const bool win = k < nk;
+      if constexpr (WIN) {
+        const double* cw = tw + (win ? k : 0) * TS;
+        double ds = 0.0, dr[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int a = 0; a < M1; ++a) {
+          const double g0 = gu[4 * a], g1 = gu[4 * a + 1], g2 = gu[4 * a + 2], g3 = gu[4 * a + 3];
+          const d2 c01 = *reinterpret_cast<const d2*>(cw + a * 6);
+          const d2 c23 = *reinterpret_cast<const d2*>(cw + a * 6 + 2);
+          const d2 c45 = *reinterpret_cast<const d2*>(cw + a * 6 + 4);
+          // value and slope by Horner's rule in one sweep
+          double G = fma(c45[1], t, c45[0]);
+          double Gp = fma(c45[1], t, G);
+          G = fma(G, t, c23[1]);
+          Gp = fma(Gp, t, G);
+          G = fma(G, t, c23[0]);
+          Gp = fma(Gp, t, G);
+          G = fma(G, t, c01[1]);
+          Gp = fma(Gp, t, G);
+          G = fma(G, t, c01[0]);
+          const double dG = fma(g0, Rv[0], fma(g1, Rv[1], fma(g2, Rv[2], g3 * Rv[3])));
+          ds = fma(dG, Gp, ds);
+          dr[0] = fma(g0, G, dr[0]);
+          dr[1] = fma(g1, G, dr[1]);
+          dr[2] = fma(g2, G, dr[2]);
+          dr[3] = fma(g3, G, dr[3]);
+        }
+        if (cl) ds = 0.0;
+        if (win && row < nn)
+          *reinterpret_cast<d4*>(A.netd + (rbase + row) * 4) =
+              d4{(dr[0] + ds) * A.inv_nm, dr[1] * A.inv_nm, dr[2] * A.inv_nm, dr[3] * A.inv_nm};
       }
+      int kcur = -1;
+      double cf[2][6];
+      const unsigned long long clips = __ballot(cl);
+      for (unsigned long long todo = __ballot(!win && row < nn); todo; todo &= todo - 1) {
+        const int r = __builtin_ctzll(todo);
+        const int kr = __builtin_amdgcn_readlane(k, r);
+        const double tr = readlane_d(t, r);
+        const double R0 = Ru[(r0 + r) * 4], R1 = Ru[(r0 + r) * 4 + 1], R2 = Ru[(r0 + r) * 4 + 2],
+                     R3 = Ru[(r0 + r) * 4 + 3];
+        if (kr != kcur) {
+          kcur = kr;
+          const double* cg = tabnet + (int64_t)kr * 6 * M1 + fl;
 #pragma unroll
-      for (int m = 1; m < 16; m <<= 1) {
-        ds += shfl_xor_d(ds, m);
+          for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) dr[q] += shfl_xor_d(dr[q], m);
+            for (int p = 0; p < 6; ++p) cf[u][p] = cg[p * M1 + u * MH];
+        }
+        double dr[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          double G = fma(cf[u][5], tr, cf[u][4]);
+          double Gp = fma(cf[u][5], tr, G);
+          G = fma(G, tr, cf[u][3]);
+          Gp = fma(Gp, tr, G);
+          G = fma(G, tr, cf[u][2]);
+          Gp = fma(Gp, tr, G);
+          G = fma(G, tr, cf[u][1]);
+          Gp = fma(Gp, tr, G);
+          G = fma(G, tr, cf[u][0]);
+          if ((clips >> r) & 1) Gp = 0.0;
+          const double dG = fma(gt[u][0], R0, fma(gt[u][1], R1, fma(gt[u][2], R2, gt[u][3] * R3)));
+          dr[0] = fma(gt[u][0], G, fma(dG, Gp, dr[0]));
+          dr[1] = fma(gt[u][1], G, dr[1]);
+          dr[2] = fma(gt[u][2], G, dr[2]);
+          dr[3] = fma(gt[u][3], G, dr[3]);
+        }
+        const double v = wave_sum4(dr);
+        if ((lane & 15) == 0) A.netd[(rbase + r0 + r) * 4 + (lane >> 4)] = v * A.inv_nm;
       }
-      if (fl == 0 && row < nn)
-        *reinterpret_cast<d4*>(A.netd + (rbase + row) * 4) = d4{dr[0] + ds, dr[1], dr[2], dr[3]};
     }
+  }
+}
+
+template <int M1>
+static void launch_tab(bool bwd, int wpb, dim3 grid, const TabArgs& A, hipStream_t s) {
+  if (wpb == 16) {
+    if (bwd) hipLaunchKernelGGL((k_embed_bwd_tab<M1, 16>), grid, dim3(1024), 0, s, A);
+    else hipLaunchKernelGGL((k_embed_fwd_tab<M1, 16>), grid, dim3(1024), 0, s, A);
+  } else {
+    if (bwd) hipLaunchKernelGGL((k_embed_bwd_tab<M1, 4>), grid, dim3(256), 0, s, A);
+    else hipLaunchKernelGGL((k_embed_fwd_tab<M1, 4>), grid, dim3(256), 0, s, A);
   }
 }
 
@@ -323,19 +505,20 @@ void launch_embed_tab(dp_ctx* c, bool bwd, hipStream_t s) {
   A.inv_nm = 1.0 / (double)m->nm;
   A.ctr = c->emb_ctr;
   A.flags = c->flags_dev;
-  // 4-wave work-groups, three per CU, on one grid row shared out among the
-  // nets by their work (net_of_group), all resident at once
+  // one grid row shared out among the nets by their work (net_of_group), all
+  // work-groups resident at once.  The window pays from about ten columns
+  // per CU (below, its staging and the one work-group per CU cost more than
+  // the L2 reads): forward / backward with and without it at water's 2,400
+  // columns 36 / 47 against 37 / 49 us, copper's 1,372 72 / 104 against
+  // 55 / 88 us, copper's 4,000 80 / 122 against 116 / 214 us
   const int nnets = A.ntypes * A.ntypes;
-  const int64_t need = (c->natoms_last * A.ntypes + 3) / 4, res = (int64_t)c->ncu * 3;
+  const int64_t columns = c->natoms_last * A.ntypes;
+  const int wpb = columns >= (int64_t)c->ncu * 10 ? 16 : 4;
+  const int64_t need = (columns + wpb - 1) / wpb, res = (int64_t)c->ncu * (wpb == 16 ? 1 : 3);
   const int64_t groups = need < res ? need : res;
   dim3 grid((unsigned)(groups > nnets ? groups : nnets), 1);
-  if (m->m1 == 100) {
-    if (bwd) hipLaunchKernelGGL(k_embed_bwd_tab<100>, grid, dim3(256), 0, s, A);
-    else hipLaunchKernelGGL(k_embed_fwd_tab<100>, grid, dim3(256), 0, s, A);
-  } else {
-    if (bwd) hipLaunchKernelGGL(k_embed_bwd_tab<128>, grid, dim3(256), 0, s, A);
-    else hipLaunchKernelGGL(k_embed_fwd_tab<128>, grid, dim3(256), 0, s, A);
-  }
+  if (m->m1 == 100) launch_tab<100>(bwd, wpb, grid, A, s);
+  else launch_tab<128>(bwd, wpb, grid, A, s);
 }
 
 }  // namespace dpse
