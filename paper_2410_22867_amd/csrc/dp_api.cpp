@@ -204,6 +204,24 @@ void frag_block32(std::vector<T>& out, int64_t base, int mtiles, int ktiles32, F
           out[base + (((int64_t)mt * ktiles32 + t) * 64 + l) * 8 + j] = wfun(16 * mt + (l & 15), kfeat32(t, l, j));
 }
 
+// Compact blocks of the FP64 force kernels (embedding nets): a product's
+// operand, four slots to an element and no padding elements.  The m elements
+// of full 16-row tiles come first, as [tile][k element][64] in the lane order
+// of a 16x16x4 product; the others follow as [m element][k element][16], the
+// value of row i and sub-k kk at i + 4 kk.  kslot / mslot
+// give the slots' base of an element.
+template <class SK, class SM, class F>
+void frag_compact64(std::vector<int32_t>& out, int64_t base, int nk, int nm, int nfull, SK kslot, SM mslot, F wfun) {
+  for (int k = 0; k < nk; ++k)
+    for (int m = 0; m < nm; ++m)
+      for (int kk = 0; kk < 4; ++kk)
+        for (int i = 0; i < 4; ++i) {
+          const int64_t at = m < 4 * nfull ? ((int64_t)(m / 4) * nk + k) * 64 + 4 * (m % 4) + i + 16 * kk
+                                           : ((int64_t)m * nk + k) * 16 + i + 4 * kk;
+          out[base + at] = wfun(mslot(m) + i, kslot(k) + kk);
+        }
+}
+
 template <class T>
 int upload_vec(T** dst, const std::vector<T>& v, const char* what) {
   int rc;
@@ -216,6 +234,7 @@ int upload_vec(T** dst, const std::vector<T>& v, const char* what) {
 void free_model(dp_model* m) {
   if (!m) return;
   void* ptrs[] = {m->params, m->emb_vec64, m->emb_vec32, m->emb_frag64, m->emb_vec64d, m->emb_frag64d,
+                  m->tanh_lut,
                   m->emb_frag_bf16, m->emb_frag_f16, m->emb_frag_f32,
                   m->fit_frag64, m->fit_frag_bf16, m->fit_frag_f16, m->fit_frag_f32, m->fit_vec64, m->fit_vec32,
                   m->table, m->tab_nodes};
@@ -296,7 +315,35 @@ int build_maps(dp_model* m) {
   fo.B3 = fo.F3t + 8192;
   fo.B2 = fo.B3 + 8192;
   fo.per_net = fo.B2 + 2048;
-  Map e64((size_t)nnets * fo.per_net, -1), e64d((size_t)nnets * fo.per_net, -1), e32((size_t)nnets * fo.per_net, -1);
+  // the FP64 force kernels' blocks, without the padding elements: n1 / n2 /
+  // n3e elements in the three layers (8 / 16 / 32 for w = 32, 7 / 13 / 25 for
+  // w = 25), those of full tiles first
+  std::vector<int> s1, s2, s3;  // first slot of each element
+  auto number = [](std::vector<int>& sl, int nslots, auto used) {
+    for (int full = 1; full >= 0; --full)
+      for (int t = 0; t < nslots / 16; ++t) {
+        int nv = 0;
+        while (nv < 4 && used(16 * t + 4 * nv)) ++nv;
+        if ((nv == 4) == (full == 1))
+          for (int v = 0; v < nv; ++v) sl.push_back(16 * t + 4 * v);
+      }
+  };
+  number(s1, 32, [&](int p) { return val1(w, p) >= 0; });
+  number(s2, 64, [&](int p) { return val2(w, p) >= 0; });
+  number(s3, 128, [&](int p) { return val3(w, p) >= 0; });
+  const int n1 = (int)s1.size(), n2 = (int)s2.size(), n3e = (int)s3.size();
+  const int f1 = w <= 28 ? 1 : 2, f2 = w <= 28 ? 2 : 4;  // full tiles of layers 1 and 2 (twice f2 in layer 3)
+  auto at1 = [&](int e) { return s1[e]; };
+  auto at2 = [&](int e) { return s2[e]; };
+  auto at3 = [&](int e) { return s3[e]; };
+  EmbFragOffsets& fd = m->efd;
+  fd.F2 = 0;
+  fd.F3n = fd.F2 + 16 * n1 * n2;
+  fd.F3t = fd.F3n + 16 * n2 * w;
+  fd.B3 = fd.F3t + 16 * n2 * n3e;
+  fd.B2 = fd.B3 + 16 * n3e * n2;
+  fd.per_net = fd.B2 + 16 * n2 * n1;
+  Map e64((size_t)nnets * fo.per_net, -1), e64d((size_t)nnets * fd.per_net, -1), e32((size_t)nnets * fo.per_net, -1);
   const int m1 = 4 * w;
   for (int a = 0; a < nt; ++a)
     for (int b = 0; b < nt; ++b) {
@@ -344,11 +391,13 @@ int build_maps(dp_model* m) {
         const int fi = wt2(w, in_slot);
         return (fi < 0 || out_feat >= m1) ? -1 : I(W3 + (int64_t)fi * 4 * w + out_feat);
       };
-      frag_block64(e64d, base + fo.F2, 4, 2, [&](int mo, int ki) { return w2d(ki, mo); }, true);
-      frag_block64(e64d, base + fo.F3n, m->n3, 4, [&](int mo, int ki) { return w3fd(ki, mo); }, true);
-      frag_block64(e64d, base + fo.F3t, 8, 4, [&](int mo, int ki) { return w3sd(ki, mo); }, true);
-      frag_block64(e64d, base + fo.B3, 4, 8, [&](int mi, int ko) { return w3sd(mi, ko); }, true);
-      frag_block64(e64d, base + fo.B2, 2, 4, [&](int mi, int ko) { return w2d(mi, ko); }, true);
+      const int64_t bd = (int64_t)(a * nt + b) * fd.per_net;
+      frag_compact64(e64d, bd + fd.F2, n1, n2, f2, at1, at2, [&](int mo, int ki) { return w2d(ki, mo); });
+      frag_compact64(e64d, bd + fd.F3n, n2, w, w / 4, at2, [](int e) { return 4 * e; },
+                     [&](int mo, int ki) { return w3fd(ki, mo); });
+      frag_compact64(e64d, bd + fd.F3t, n2, n3e, 2 * f2, at2, at3, [&](int mo, int ki) { return w3sd(ki, mo); });
+      frag_compact64(e64d, bd + fd.B3, n3e, n2, f2, at3, at2, [&](int mi, int ko) { return w3sd(mi, ko); });
+      frag_compact64(e64d, bd + fd.B2, n2, n1, f1, at2, at1, [&](int mi, int ko) { return w2d(mi, ko); });
       // forward (A operand W^T: m = out, k = in)
       frag_block64(e64, base + fo.F2, 4, 2, [&](int mo, int ki) { return w2(ki, mo); }, true);
       frag_block32(e32, base + fo.F2, 4, 1, [&](int mo, int ki) { return w2h(ki, mo); });
@@ -438,6 +487,10 @@ int build_maps(dp_model* m) {
     pm.kind = t.kind;
     pm.dst = *t.dst;
   }
+  // tanh(k / 128), rounded to double from the 64-bit mantissa of long double
+  std::vector<double> lut(kTanhLutEntries);
+  for (int k = 0; k < kTanhLutEntries; ++k) lut[k] = (double)tanhl((long double)k / 128.0L);
+  if ((rc = upload_vec(&m->tanh_lut, lut, "hipMalloc(tanh table)"))) return rc;
   return dev_alloc(&m->params, (size_t)m->n_params, "hipMalloc(params)");
 }
 

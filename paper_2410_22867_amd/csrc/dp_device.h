@@ -36,6 +36,15 @@ __device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// Four independent 4x4x4 products in the cycles of a quarter of a 16x16x4 one
+// (16 against 64, measured 18 and 70): A[m][k] of block b at lane m + 4b + 16k,
+// B[k][n] of block b at lane n + 4b + 16k, D[m][n] of block b at lane
+// n + 4b + 16m (measured).  With the same A in every block it is one element
+// of the 16x16x4 layout: rows 4v..4v+3 of A against all 16 columns of B.
+__device__ __forceinline__ double mfma4_f64(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
 typedef _Float16 h16x4 __attribute__((ext_vector_type(4)));
 
 // 16x16x16 FP16 product with FP32 accumulation (4 elements per lane).
@@ -267,6 +276,40 @@ __device__ __forceinline__ double tanh_d_tab(double x, const double* tab) {
   const double r = fma(-d, q0, 1.0);
   const double q = fma(q0, fma(r, r, r), q0);
   return __builtin_copysign(fma(2.0, q, -1.0), x);
+}
+
+// FP64 tanh from a table of tanh at the multiples of 2^-LOG (correctly rounded;
+// tab in LDS).  |x|, clamped to 19.49 (tanh rounds to 1 from 19.07), plus
+// 1.5 2^(52 - LOG) rounds to the nearest multiple xk, whose number k is the
+// sum's low word; f = |x| - xk is exact and |f| <= 2^-(LOG + 1).  With T =
+// tab[k] and u = tanh f (odd Taylor polynomial: degree 5 for LOG = 7, 7 for
+// LOG = 6, truncation below 1e-19), the addition theorem gives tanh|x| =
+// T + (1 - T^2) u / (1 + y), y = T u; 1/(1 + y) is (1 - y)(1 + y^2 + y^4) for
+// |y| <= 2^-8 and (1 - y)(1 + y^2)(1 + y^4) for 2^-7 (remainders y^6, y^8,
+// times (1 - T^2) u below 1e-17).  No division, no exponential: 16 (18) FP64
+// instructions where tanh_d_tab needs 19 and a reciprocal that costs four.
+// Absolute error below 1.3e-16, relative accuracy kept for small |x|.
+template <int LOG>
+__device__ __forceinline__ double tanh_lut(double x, const double* tab) {
+  constexpr double magic = 1.5 * (double)(1ull << (52 - LOG));
+  const double a = __builtin_fmin(__builtin_fabs(x), 19.49);
+  const double s = a + magic;
+  const double T = tab[(unsigned)__builtin_bit_cast(unsigned long long, s)];
+  const double f = a - (s - magic);
+  const double f2 = f * f;
+  double g = LOG == 7 ? 0.13333333333333333 : fma(f2, -0.05396825396825397, 0.13333333333333333);
+  g = f2 * fma(f2, g, -0.3333333333333333);
+  const double u = fma(f, g, f);
+  const double y = T * u;
+  const double y2 = y * y;
+  double r = 1.0 - y;
+  if constexpr (LOG == 7) {
+    r = fma(r, fma(y2, y2, y2), r);
+  } else {
+    r = fma(r, y2, r);
+    r = fma(r, y2 * y2, r);
+  }
+  return __builtin_copysign(fma(fma(-T, T, 1.0) * u, r, T), x);
 }
 
 constexpr float kTanhScale = 2.8853900817779268f;  // 2/ln 2

@@ -16,6 +16,7 @@ constexpr int kColPad = 128;     // fitting-GEMM column tile; type segments are 
 constexpr int kSplitMax = 16, kSplitCols = 2048;
 constexpr int kCandCap = 512;    // neighbour candidates inside r_c per atom (LDS capacity)
 constexpr int kMaxNm = 1024;     // sum(sel)
+constexpr int kTanhLutEntries = 2496;  // tanh(k / 128) for |x| up to 19.5
 constexpr int kRedChunk = 256;  // atoms per partial sum of the per-frame reductions
 
 // Slot layout of the embedding activations (see k_embed.hip): widths
@@ -116,10 +117,12 @@ struct dp_model {
   // mixed kernels use the plain layout
   double* emb_vec64d;
   double* emb_frag64d;
+  double* tanh_lut;          // tanh(k / 128), k < kTanhLut (the FP64 force kernels' table)
   uint16_t* emb_frag_bf16;
   uint16_t* emb_frag_f16;
   float* emb_frag_f32;
   dpse::EmbFragOffsets efo;
+  dpse::EmbFragOffsets efd;  // emb_frag64d: compact blocks (see EmbLay in k_embed.hip)
   // fitting
   double* fit_frag64;
   uint16_t* fit_frag_bf16;

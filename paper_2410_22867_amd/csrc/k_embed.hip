@@ -49,6 +49,7 @@ struct EmbArgs {
   const void* fraglp;     // mixed forms: fragments in the form's element type
   const double* vec64;
   const float* vec32;
+  const double* tanh_lut;  // tanh(k / 128)
   int64_t vec_per_net;
   EmbFragOffsets fo;
   void* Tpart;           // forward: [ntypes][cols][m1][4] partial T per neighbour section
@@ -201,6 +202,85 @@ template <int W>
 __device__ __forceinline__ constexpr bool kpad3(int zo, int t, int v) {  // layer-3 slots 64 zo + 16 t + 4 v + g
   return kpad2<W>(t, v) || (kDense2<W> && zo == 1 && t == 1 && v == 2);
 }
+// elements of a 16-slot tile before its padding (padding is always last)
+template <int W>
+__device__ __forceinline__ constexpr int nv1(int t) {
+  return 4 - kpad<W>(t, 3);
+}
+template <int W>
+__device__ __forceinline__ constexpr int nv2(int t) {
+  return 4 - kpad2<W>(t, 3) - kpad2<W>(t, 2);
+}
+template <int W>
+__device__ __forceinline__ constexpr int nv3(int zo, int t) {
+  return 4 - kpad3<W>(zo, t, 3) - kpad3<W>(zo, t, 2);
+}
+// Compact numbering of the FP64 kernels' elements (four slots each, padding
+// ones left out; the elements of full tiles first), shared with the blocks the
+// host lays out: of a product's operand, the m elements of a full tile as
+// [k element][64] in lane order, a single m element as [k element][16], row i
+// and sub-k kk at i + 4 kk (lane offset lo4); k values one after another, so
+// that one LDS instruction reads two of them.
+template <int W>
+struct EmbLay {
+  static constexpr int n1 = nv1<W>(0) + nv1<W>(1);
+  static constexpr int n2 = nv2<W>(0) + nv2<W>(1) + nv2<W>(2) + nv2<W>(3);
+  static constexpr int n3 = n2 + nv3<W>(1, 0) + nv3<W>(1, 1) + nv3<W>(1, 2) + nv3<W>(1, 3);
+  static constexpr int F2 = 16 * n1 * n2, F3n = 16 * n2 * W, F3t = 16 * n2 * n3, B3 = F3t, B2 = F2;
+  // first element of tile t in layers 2 and 3 (layer 3: t = 4 zo + tile)
+  static __device__ __forceinline__ constexpr int e2(int t) {
+    int before = 0, full = 0;
+    for (int u = 0; u < 4; ++u) {
+      full += nv2<W>(u) == 4;
+      if (u < t && (nv2<W>(u) == 4) == (nv2<W>(t) == 4)) before += nv2<W>(u);
+    }
+    return before + (nv2<W>(t) == 4 ? 0 : 4 * full);
+  }
+  static __device__ __forceinline__ constexpr int e3(int t) {
+    int before = 0, full = 0;
+    for (int u = 0; u < 8; ++u) {
+      full += nv3<W>(u >> 2, u & 3) == 4;
+      if (u < t && (nv3<W>(u >> 2, u & 3) == 4) == (nv3<W>(t >> 2, t & 3) == 4)) before += nv3<W>(u >> 2, u & 3);
+    }
+    return before + (nv3<W>(t >> 2, t & 3) == 4 ? 0 : 4 * full);
+  }
+  // compact column of slot p
+  static __device__ __forceinline__ int col2(int p) {
+    const int t = p >> 4;
+    return 4 * (t == 0 ? e2(0) : t == 1 ? e2(1) : t == 2 ? e2(2) : e2(3)) + (p & 15);
+  }
+  static __device__ __forceinline__ int col3(int p) {  // -1 for padding slots
+    const int t = p >> 4;
+    int e = 0, n = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (t == u) {
+        e = e3(u);
+        n = nv3<W>(u >> 2, u & 3);
+      }
+    return (p & 15) < 4 * n ? 4 * e + (p & 15) : -1;
+  }
+};
+
+// What bounds the FP64 kernels is the FP64 pipe: matrix and vector FP64
+// instructions do not overlap on a SIMD (16x16x4 64 cycles, 4x4x4 16, a vector
+// operation 4), and a third wave per SIMD (12-wave work-groups) changed
+// nothing (forward 460 -> 461 us).  So the work itself was cut: products whose
+// tile holds three or fewer elements as 4x4x4 ones, and a tanh of 16 FP64
+// operations (tanh_lut).  water12k: forward 518 -> 460 us (577 -> 513 with the
+// activation store), backward 887 -> 782 us (583 -> 522 with the store).
+
+// z += A B for the nv elements of a tile that hold slots and k element k of
+// nk, blk at the tile's first element (e0 16 nk from the operand's start); nv
+// is a constant once the loops are unrolled.  A 16x16x4 product takes 64
+// cycles whatever its rows hold, a 4x4x4 one 16 per element.
+__device__ __forceinline__ d4 mfma_f64_el(int nv, const double* blk, int nk, int k, int lane, int lo4, double b, d4 z) {
+  if (nv == 4) return mfma_f64(blk[64 * k + lane], b, z);
+#pragma unroll
+  for (int e = 0; e < nv; ++e) z[e] = mfma4_f64(blk[16 * (e * nk + k) + lo4], b, z[e]);
+  return z;
+}
+
 template <int W>
 __device__ __forceinline__ int slot2d_of_feat(int f) {  // f in [0, 2W), FP64 layout
   if (kDense2<W> && f == 2 * W - 1) return W;
@@ -223,10 +303,11 @@ __device__ __forceinline__ int feat3d_of_slot(int p) {  // FP64 layout; -1 for p
 // a column and walks its tiles alone, which leaves most of the chip idle
 // when there are fewer columns than wave slots.
 template <int W, int WPB, bool ST, bool GM>
-__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_embed_fwd_f64(EmbArgs A) {
+__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 4, WPB / 4))) void k_embed_fwd_f64(EmbArgs A) {
   constexpr int M1 = 4 * W;
   constexpr int N3 = (M1 + 15) / 16;
-  constexpr int NF2 = 2048, NF3 = N3 * 1024;
+  typedef EmbLay<W> LY;
+  constexpr int NF2 = LY::F2, NF3 = LY::F3n, HS = 4 * LY::n2 + 1;
   // A last feature tile with at most 4 real features (w = 25: features
   // 96..99) is evaluated transposed, features along M: its real outputs are
   // then element 0 of every lane (one tanh per lane instead of four), and
@@ -234,18 +315,22 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
   constexpr int REM = M1 % 16;
   constexpr bool TLAST = REM > 0 && REM <= 4;
   __shared__ double fr[NF2 + NF3];
-  __shared__ double h2s[WPB][16][kP2 + 1];
+  __shared__ double h2s[WPB][16][HS];
   __shared__ double vs[kVecPerNet];
-  __shared__ double etab[32];  // tanh_d_tab's table
+  // tanh table: steps of 1/128 where LDS has room (w = 25), 1/64 otherwise
+  constexpr int LOG = W <= 28 ? 7 : 6;
+  __shared__ double etab[LOG == 7 ? kTanhLutEntries : kTanhLutEntries / 2];
   __shared__ int col_sh;  // group mode: the work-group's column
   DPSE_NET_PROLOGUE(WPB)
+  const int lo4 = (lane & 3) + 4 * (lane >> 4);
   {
     const double* src = A.frag64 + net * A.fo.per_net;
     for (int k = threadIdx.x; k < NF2; k += 64 * WPB) fr[k] = src[A.fo.F2 + k];
     for (int k = threadIdx.x; k < NF3; k += 64 * WPB) fr[NF2 + k] = src[A.fo.F3n + k];
     const double* vsrc = A.vec64 + net * A.vec_per_net;
     for (int k = threadIdx.x; k < kVecPerNet; k += 64 * WPB) vs[k] = vsrc[k];
-    if (threadIdx.x < 32) etab[threadIdx.x] = kExp2Frac32[threadIdx.x];
+    constexpr int NE = LOG == 7 ? kTanhLutEntries : kTanhLutEntries / 2;
+    for (int k = threadIdx.x; k < NE; k += 64 * WPB) etab[k] = A.tanh_lut[LOG == 7 ? k : 2 * k];
   }
   __syncthreads();
   constexpr int RSTEP = GM ? 16 * WPB : 16;  // rows between a wave's tiles
@@ -300,7 +385,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          h1[mt][v] = kpad<W>(mt, v) ? 0.0 : tanh_d_tab(fma(s, vec[kV_W1 + 16 * mt + 4 * v + g], vec[kV_B1 + 16 * mt + 4 * v + g]), etab);
+          h1[mt][v] = kpad<W>(mt, v) ? 0.0 : tanh_lut<LOG>(fma(s, vec[kV_W1 + 16 * mt + 4 * v + g], vec[kV_B1 + 16 * mt + 4 * v + g]), etab);
       double h2[4][4];
 #pragma unroll
       for (int ot = 0; ot < 4; ++ot) {
@@ -310,15 +395,15 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            if (!kpad<W>(mt, v)) z = mfma_f64(fr[z0 + ((ot * 2 + mt) * 4 + v) * 64 + lane], h1[mt][v], z);
+            if (!kpad<W>(mt, v)) z = mfma_f64_el(nv2<W>(ot), fr + z0 + LY::e2(ot) * LY::n1 * 16, LY::n1, 4 * mt + v, lane, lo4, h1[mt][v], z);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) h2[ot][v] = kpad2<W>(ot, v) ? 0.0 : h1[ot & 1][v] + tanh_d_tab(z[v], etab);
+        for (int v = 0; v < 4; ++v) h2[ot][v] = kpad2<W>(ot, v) ? 0.0 : h1[ot & 1][v] + tanh_lut<LOG>(z[v], etab);
       }
       wave_lds_sync();
 #pragma unroll
       for (int ot = 0; ot < 4; ++ot)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) h2s[wv][r16][16 * ot + 4 * v + g] = h2[ot][v];
+        for (int v = 0; v < nv2<W>(ot); ++v) h2s[wv][r16][4 * (LY::e2(ot) + v) + g] = h2[ot][v];
       wave_lds_sync();
 #pragma unroll
       for (int o = 0; o < N3; ++o) {
@@ -331,11 +416,11 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
           for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-              if (!kpad2<W>(mt, v)) z = mfma_f64(fr[z0 + NF2 + ((o * 4 + mt) * 4 + v) * 64 + lane], h2[mt][v], z);
+              if (!kpad2<W>(mt, v)) z[0] = mfma4_f64(fr[z0 + NF2 + (4 * o * LY::n2 + LY::e2(mt) + v) * 16 + lo4], h2[mt][v], z[0]);
           if (g < REM) {
-            const double t3 = tanh_d_tab(z[0], etab);
+            const double t3 = tanh_lut<LOG>(z[0], etab);
             if constexpr (ST) recb[f * 16 + r16] = t3;
-            const double G = h2s[wv][r16][slot2d_of_feat<W>(f % (2 * W))] + t3;
+            const double G = h2s[wv][r16][LY::col2(slot2d_of_feat<W>(f % (2 * W)))] + t3;
 #pragma unroll
             for (int k = 0; k < 4; ++k) accL[k] = fma(G, Rown[k], accL[k]);
           }
@@ -349,12 +434,12 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
           for (int v = 0; v < 4; ++v)
             if (!kpad2<W>(mt, v))
-              z = mfma_f64(h2[mt][v], fr[z0 + NF2 + ((o * 4 + mt) * 4 + v) * 64 + lane], z);
+              z = mfma_f64(h2[mt][v], fr[z0 + NF2 + (o * LY::n2 + LY::e2(mt) + v) * 64 + lane], z);
         if (feat < M1) {
-          const int src = slot2d_of_feat<W>(feat % (2 * W));
+          const int src = LY::col2(slot2d_of_feat<W>(feat % (2 * W)));
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            const double t3 = tanh_d_tab(z[v], etab);
+            const double t3 = tanh_lut<LOG>(z[v], etab);
             if constexpr (ST) rec[o * 256 + 4 * v] = t3;
             const double G = h2s[wv][4 * v + g][src] + t3;
 #pragma unroll
@@ -399,7 +484,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
         *reinterpret_cast<d4*>(dst + (16 * (N3 - 1) + g) * 4) = d4{accL[0], accL[1], accL[2], accL[3]};
     }
     if constexpr (GM) {
-      static_assert(WPB * M1 * 4 <= WPB * 16 * (kP2 + 1), "partials fit the h2s tiles");
+      static_assert(WPB * M1 * 4 <= WPB * 16 * HS, "partials fit the h2s tiles");
       __syncthreads();
       const double* red = &h2s[0][0][0];
       for (int e = threadIdx.x; e < M1 * 4; e += 64 * WPB) {
@@ -415,32 +500,41 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
 // ============================================================== FP64 backward
 // GM: group mode as in the forward (the waves share the column's g_T tile).
 template <int W, int WPB, bool ST, bool GM>
-__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_embed_bwd_f64(EmbArgs A) {
+__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 4, WPB / 4))) void k_embed_bwd_f64(EmbArgs A) {
   constexpr int M1 = 4 * W;
-  // F3t | B3; with the activation store F3t is not needed and its space
-  // holds F2 | B2 | the vector block instead (no global operand loads)
-  __shared__ double fr[8192 + 8192];
-  __shared__ d4 gts[GM ? 1 : WPB][kP3];
+  typedef EmbLay<W> LY;
+  // F2 | B2 | vector block | tanh table | B3, and F3t without the activation
+  // store; w = 32 without the store has no room beyond B3 and F3t and reads
+  // the small blocks from global memory
+  constexpr bool SM = ST || W <= 28;  // small blocks and the tanh table in LDS
+  constexpr int U3 = SM ? 2 : 1;      // layer-3 halves unrolled
+  constexpr int oB2 = LY::F2, oV = oB2 + LY::B2, oT = oV + kVecPerNet, oB3 = SM ? oT + kTanhLutEntries : 0,
+                oF3 = oB3 + LY::B3;
+  constexpr bool E32 = !SM && GM;     // room for the small table of tanh_d_tab only
+  constexpr int oE = oF3 + (ST ? 0 : LY::F3t);
+  __shared__ double fr[oE + (E32 ? 32 : 0)];
+  __shared__ d4 gts[GM ? 1 : WPB][4 * LY::n3];
   __shared__ int col_sh;  // group mode: the work-group's column
   DPSE_NET_PROLOGUE(WPB)
+  const int lo4 = (lane & 3) + 4 * (lane >> 4);
   const double* gsrc = A.frag64 + net * A.fo.per_net;
   const double* vecg = A.vec64 + net * A.vec_per_net;
-  for (int k = threadIdx.x; k < 8192; k += 64 * WPB) {
-    if constexpr (!ST) {
-      fr[k] = gsrc[A.fo.F3t + k];
-    } else {
-      if (k < 2048) fr[k] = gsrc[A.fo.F2 + k];
-      else if (k < 4096) fr[k] = gsrc[A.fo.B2 + k - 2048];
-      else if (k < 4096 + kVecPerNet) fr[k] = vecg[k - 4096];
-      else if (k < 4096 + kVecPerNet + 32) fr[k] = kExp2Frac32[k - 4096 - kVecPerNet];  // tanh_d_tab's table
-    }
-    fr[8192 + k] = gsrc[A.fo.B3 + k];
+  auto stage = [&](int dst, const double* src, int n) {
+    for (int k = threadIdx.x; k < n; k += 64 * WPB) fr[dst + k] = src[k];
+  };
+  if constexpr (SM) {
+    stage(0, gsrc + A.fo.F2, LY::F2);
+    stage(oB2, gsrc + A.fo.B2, LY::B2);
+    stage(oV, vecg, kVecPerNet);
+    stage(oT, A.tanh_lut, kTanhLutEntries);
   }
+  stage(oB3, gsrc + A.fo.B3, LY::B3);
+  if constexpr (!ST) stage(oF3, gsrc + A.fo.F3t, LY::F3t);
+  if constexpr (E32) stage(oE, kExp2Frac32, 32);
   __syncthreads();
-  // layers 1-2: the table form of the FP64 tanh where the store leaves LDS
-  // room for its table
-  const double* etab = fr + 4096 + kVecPerNet;
-  auto tanh_l = [&](double x) { return ST ? tanh_d_tab(x, etab) : tanh_d(x); };
+  auto tanh_l = [&](double x) {
+    return SM ? tanh_lut<7>(x, fr + oT) : E32 ? tanh_d_tab(x, fr + oE) : tanh_d(x);
+  };
   const int gw = GM ? 0 : wv;  // this wave's g_T tile
   constexpr int RSTEP = GM ? 16 * WPB : 16;
   const int rfirst = GM ? 16 * wv : 0;
@@ -461,10 +555,10 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
       const double* gT = reinterpret_cast<const double*>(A.gT) + (int64_t)col * M1 * 4;
       if constexpr (!GM) wave_lds_sync();
       for (int p = GM ? (int)threadIdx.x : lane; p < kP3; p += GM ? 64 * WPB : 64) {
-        const int a = feat3d_of_slot<W>(p);
+        const int a = feat3d_of_slot<W>(p), cp = LY::col3(p);
         d4 x = {0.0, 0.0, 0.0, 0.0};
         if (a >= 0) x = *reinterpret_cast<const d4*>(gT + a * 4) * A.inv_nm;
-        gts[gw][p] = x;
+        if (cp >= 0) gts[gw][cp] = x;
       }
       if constexpr (GM) __syncthreads();
       else wave_lds_sync();
@@ -476,9 +570,9 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (rfirst + r16 < nn) R_next = *reinterpret_cast<const d4*>(Rs + (rfirst + r16) * 4);
     for (int r0 = rfirst; r0 < nn; r0 += RSTEP) {
       const int z0 = opaque_zero();
-      const double* F2 = ST ? fr + z0 : opaque(gsrc + A.fo.F2);
-      const double* B2 = ST ? fr + 2048 + z0 : opaque(gsrc + A.fo.B2);
-      const double* vec = ST ? fr + 4096 + z0 : opaque(vecg);
+      const double* F2 = SM ? fr + z0 : opaque(gsrc + A.fo.F2);
+      const double* B2 = SM ? fr + oB2 + z0 : opaque(gsrc + A.fo.B2);
+      const double* vec = SM ? fr + oV + z0 : opaque(vecg);
       const int row = r0 + r16;
       const bool valid = row < nn;
       const d4 Rrow = R_next;
@@ -528,7 +622,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            if (!kpad<W>(mt, v)) z = mfma_f64(F2[((ot * 2 + mt) * 4 + v) * 64 + lane], t1[mt][v], z);
+            if (!kpad<W>(mt, v)) z = mfma_f64_el(nv2<W>(ot), F2 + LY::e2(ot) * LY::n1 * 16, LY::n1, 4 * mt + v, lane, lo4, t1[mt][v], z);
 #pragma unroll
         for (int v = 0; v < 4; ++v) h2[ot][v] = kpad2<W>(ot, v) ? 0.0 : t1[ot & 1][v] + tanh_l(z[v]);
       }
@@ -542,37 +636,37 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int v = 0; v < 4; ++v) skip2[ot][v] = 0.0;
       }
-#pragma unroll 1
+#pragma unroll(U3)
       for (int oo = 0; oo < 2; ++oo) {
-        const int zo = opaque_zero() + oo;
+        const int zo = opaque_zero() + (U3 == 1 ? oo : 0);
+        const int hf = U3 == 1 ? zo : oo;  // the half
 #pragma unroll
         for (int o4 = 0; o4 < 4; ++o4) {
+          const int e0 = U3 == 2 ? LY::e3(4 * oo + o4) : 16 * hf + 4 * o4;  // the tile's first element
+          const int n3 = U3 == 2 ? nv3<W>(oo, o4) : 4;
           d4 z = {0.0, 0.0, 0.0, 0.0};
           if constexpr (!ST) {
-            const double* b3 = vec + kV_B3S + 16 * (4 * zo + o4) + g;
+            const double* b3 = vec + kV_B3S + 16 * (4 * hf + o4) + g;
             z = d4{b3[0], b3[4], b3[8], b3[12]};
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-              for (int v = 0; v < 4; ++v)
-                if (!kpad2<W>(mt, v)) z = mfma_f64(fr[z0 + zo * 4096 + ((o4 * 4 + mt) * 4 + v) * 64 + lane], h2[mt][v], z);
+              for (int v = 0; v < nv2<W>(mt); ++v)
+                z = mfma_f64_el(n3, fr + oF3 + (U3 == 2 ? zo : 0) + e0 * LY::n2 * 16, LY::n2, LY::e2(mt) + v, lane, lo4,
+                                h2[mt][v], z);
           }
           double dz3[4];
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            dz3[v] = 0.0;
-            if (kpad2<W>(o4, v)) continue;  // padding slots: G = 0 and no weights
-            if (kDense2<W> && o4 == 1 && v == 2 && oo != 0) continue;
-            const int p = 16 * (4 * zo + o4) + 4 * v + g;
+          for (int v = 0; v < n3; ++v) {
             double t3;
             if constexpr (ST) {
-              const double x = oo == 0 ? t3v[0][o4 * 4 + v] : t3v[1][o4 * 4 + v];
+              const double x = t3v[oo][o4 * 4 + v];
               t3 = (kDense2<W> && o4 == 1 && v == 2) || 16 * (o4 & 1) + 4 * v + g < W ? x : 0.0;
             } else {
-              t3 = tanh_d(z[v]);
+              t3 = tanh_l(z[v]);
             }
             const double G = h2[o4][v] + t3;
-            const d4 gt = gts[gw][p];
+            const d4 gt = gts[gw][4 * (e0 + v) + g];
             const double dG = gt[0] * Rrow[0] + gt[1] * Rrow[1] + gt[2] * Rrow[2] + gt[3] * Rrow[3];
 #pragma unroll
             for (int k = 0; k < 4; ++k) dRd[k] = fma(gt[k], G, dRd[k]);
@@ -582,9 +676,9 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
           for (int i2 = 0; i2 < 4; ++i2)
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-              if (!kpad2<W>(o4, v) && !(kDense2<W> && o4 == 1 && v == 2 && oo != 0))
-                dh2a[i2] = mfma_f64(fr[z0 + 8192 + zo * 1024 + ((i2 * 8 + o4) * 4 + v) * 64 + lane], dz3[v], dh2a[i2]);
+            for (int v = 0; v < n3; ++v)
+              dh2a[i2] = mfma_f64_el(nv2<W>(i2), fr + oB3 + (U3 == 2 ? zo : 0) + LY::e2(i2) * LY::n3 * 16, LY::n3, e0 + v, lane, lo4, dz3[v],
+                                     dh2a[i2]);
         }
       }
       double dz2[4][4];
@@ -612,7 +706,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int o = 0; o < 4; ++o)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            if (!kpad2<W>(o, v)) z = mfma_f64(B2[((i2 * 4 + o) * 4 + v) * 64 + lane], dz2[o][v], z);
+            if (!kpad2<W>(o, v)) z = mfma_f64_el(nv1<W>(i2), B2 + 4 * i2 * LY::n2 * 16, LY::n2, LY::e2(o) + v, lane, lo4, dz2[o][v], z);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const double dh1 = z[v];
@@ -1146,8 +1240,9 @@ static EmbArgs emb_args(dp_ctx* c, int32_t mode) {
   A.fraglp = mode == DP_FP64 ? nullptr : frag_of(m->emb_frag_bf16, m->emb_frag_f16, m->emb_frag_f32, mix_kinds(mode).emb);
   A.vec64 = m->emb_vec64d;
   A.vec32 = m->emb_vec32;
+  A.tanh_lut = m->tanh_lut;
   A.vec_per_net = m->emb_vec_per_net;
-  A.fo = m->efo;
+  A.fo = mode == DP_FP64 ? m->efd : m->efo;
   A.Tpart = c->Tpart;
   A.tpart_stride = c->max_cols * m->m1 * 4;
   A.gT = c->gT;
@@ -1212,7 +1307,7 @@ static void launch_embed_lp_gm(bool bwd, bool gm, dim3 grid, const EmbArgs& A, h
 template <int W>
 static void launch_embed(dp_ctx* c, int32_t mode, bool bwd, hipStream_t s) {
   const int kind = mode == DP_FP64 ? 0 : mix_kinds(mode).emb;
-  const int wpb = mode == DP_FP64 ? 8 : (bwd ? (kind == 3 ? 16 : 8) : (kind == 3 ? 8 : kWPBlp));
+  const int wpb = mode == DP_FP64 ? kWPB64 : (bwd ? (kind == 3 ? 16 : 8) : (kind == 3 ? 8 : kWPBlp));
   EmbArgs A = emb_args(c, mode);
   const int per_cu = mode == DP_FP64 ? 1 : (kind == 3 ? (bwd ? 1 : 2) : (bwd ? 2 : 4));
   const int nnets = A.ntypes * A.ntypes;
