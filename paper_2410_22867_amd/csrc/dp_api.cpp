@@ -1180,14 +1180,22 @@ int dp_ctx_create(const dp_model* m, int64_t max_atoms, int32_t max_frames, int6
   {
     // parameter-gradient workspace: per-chunk partials of the fitting
     // reductions, per-work-group records of the embedding reductions
-    int64_t fch = N / 1024, slots = N / 64;
-    c->grad_chunks = (int32_t)(fch < 1 ? 1 : (fch > 16 ? 16 : fch));
-    c->grad_slots = (int32_t)(slots < 1 ? 1 : (slots > 1024 ? 1024 : slots));
     const int64_t nt = m->desc.ntypes;
-    const int64_t fit_w = nt * c->grad_chunks * (int64_t)nd * m->fw;
-    const int64_t fit_b = nt * ((N + 255) / 256) * (int64_t)m->fw;  // bias sums: 256-column chunks
+    int64_t fch = N / 64, slots = N / 64;
+    c->grad_chunks = (int32_t)(fch > 16 ? 16 : (fch < nt ? nt : fch));
+    c->grad_slots = (int32_t)(slots < 1 ? 1 : (slots > 1024 ? 1024 : slots));
+    // chunk records of the three layers' weights and biases; the output
+    // layer's 64-column chunks
+    const int64_t fit_w = c->grad_chunks * (int64_t)(nd + 2 * m->fw + 3) * m->fw;
+    const int64_t fit_b = nt * ((N + 63) / 64) * (int64_t)(m->fw + 1);
     const int64_t fit = fit_w > fit_b ? fit_w : fit_b;
-    const int64_t emb = nt * nt * c->grad_slots * 10496LL;
+    int64_t emb = nt * nt * c->grad_slots * 10496LL;
+    if (m->w1 == 25) {  // one record of 6,712 sums per work-group, one work-group per CU at most
+      const int64_t need = (N * nt + 3) / 4;
+      c->grad_slots = (int32_t)(need < c->ncu ? need : c->ncu);
+      if (c->grad_slots < nt * nt) c->grad_slots = (int32_t)(nt * nt);
+      emb = c->grad_slots * 6712LL;
+    }
     ALLOC(c->gpart, fit > emb ? fit : emb);
   }
   double* tmp = nullptr;
@@ -1326,61 +1334,45 @@ int dp_backward_params(dp_ctx* c, const double* dL_dE, double* grad_params, hipS
     launch_fit_backward(c, c->mode_last, true, stream);
     c->h_stored = true;
   }
-  ParamGradInputs in;
-  in.ldz = fw;
+  bool fill_act = false;
+  ParamGradInputs in = {};
   if (c->mode_last == DP_FP64) {
     launch_descriptor_ex(c, DP_FP64, true, stream);  // D is only formed inside the GEMM on the force path
-    in.X[0] = (const double*)c->D;
-    in.X[1] = (const double*)c->fa[0];
-    in.X[2] = (const double*)c->fa[2];
-    in.dz[0] = (const double*)c->fa[8];
-    in.dz[1] = (const double*)c->fa[7];
-    in.dz[2] = (const double*)c->fa[5];
-    in.h3 = (const double*)c->fa[4];
-    in.gT = (const double*)c->gT;
+    in.ldz = in.ldx[1] = in.ldx[2] = fw;
   } else {
     // mixed: the layer inputs, deltas and g_T of the mixed-precision passes,
-    // widened to FP64 into buffers the force path no longer needs; the
-    // weight-gradient reductions then run in FP64
-    // launch_widen kinds: 0 FP32, 1 BF16, 2 FP16
+    // widened to FP64 as they are read; the sums run in FP64
     const MixKinds mk = mix_kinds(c->mode_last);
-    const int k1 = mk.fit1 == 3 ? 0 : mk.fit1, k23 = mk.fit23 == 3 ? 0 : mk.fit23;
-    const int64_t cols = c->natoms_last + (int64_t)m->desc.ntypes * kColPad;
+    auto kind = [](int k) { return k == 3 ? 1 : k + 1; };  // MixKinds 1 bf16, 2 f16, 3 f32
+    in.kind[0] = kind(mk.fit1);
+    in.kind[1] = 1;
+    in.kind[2] = kind(mk.fit23);
+    in.ldz = in.ldx[1] = in.ldx[2] = fwp;
+    in.gt32 = 1;
     // the embedding gradient recomputes the FP64 activations of the frame;
-    // when the workspace holds them, the FP64 embedding forward with its
-    // store runs first (same inputs, same values) and the gradient reads the
-    // last layer back, which costs less than recomputing it there.  The
-    // forward also writes Tpart, which the widened g_T takes below.
+    // when the workspace holds them, the first pass stores the last layer
+    // for later passes over the same compute: w = 25 in the gradient kernel
+    // itself; w = 32 by the FP64 embedding forward, run first (same inputs,
+    // same values; it also writes Tpart, free by now), whose store the
+    // gradient reads back at once
     if (!c->grad_act && c->act &&
         (int64_t)c->natoms_last * m->tpa * (int64_t)m->m1 * 16 * 8 <= c->act_bytes) {
       c->grad_act = true;
-      launch_embed_fwd(c, nullptr, DP_FP64, stream);
+      if (m->w1 == 25) fill_act = true;
+      else launch_embed_fwd(c, nullptr, DP_FP64, stream);
     }
-    double* D64 = (double*)c->dD;
-    double* f64[6] = {(double*)c->fa[1], (double*)c->fa[3], (double*)c->fa[10],
-                      (double*)c->fa[11], (double*)c->fa[5], (double*)c->fa[6]};
-    launch_widen(c->D, k1, nd, D64, nd, nd, cols, stream);
-    launch_widen(c->fa[0], 0, fwp, f64[0], fw, fw, cols, stream);  // h1
-    launch_widen(c->fa[2], 0, fwp, f64[1], fw, fw, cols, stream);  // h2
-    launch_widen(c->fa[4], 0, fwp, f64[2], fw, fw, cols, stream);  // h3
-    launch_widen(c->fa[9], k1, fwp, f64[3], fw, fw, cols, stream);  // dz1
-    launch_widen(c->fa[8], k23, fwp, f64[4], fw, fw, cols, stream);  // dz2
-    launch_widen(c->fa[7], k23, fwp, f64[5], fw, fw, cols, stream);  // dz3
-    double* gT64 = (double*)c->Tpart;
-    launch_widen(c->gT, 0, m->m1 * 4, gT64, m->m1 * 4, m->m1 * 4, cols, stream);
-    in.X[0] = D64;
-    in.X[1] = f64[0];
-    in.X[2] = f64[1];
-    in.h3 = f64[2];
-    in.dz[0] = f64[3];
-    in.dz[1] = f64[4];
-    in.dz[2] = f64[5];
-    in.gT = gT64;
   }
+  const bool mixed = c->mode_last != DP_FP64;
+  in.X[0] = c->D;
+  in.X[1] = c->fa[0];
+  in.X[2] = c->fa[2];
+  in.h3 = c->fa[4];
+  in.dz[0] = c->fa[mixed ? 9 : 8];
+  in.dz[1] = c->fa[mixed ? 8 : 7];
+  in.dz[2] = c->fa[mixed ? 7 : 5];
+  in.gT = c->gT;
   in.ldx[0] = nd;
-  in.ldx[1] = fw;
-  in.ldx[2] = fw;
-  launch_param_grads(c, in, dL_dE, grad_params, stream);
+  launch_param_grads(c, in, dL_dE, grad_params, fill_act, stream);
   HIPCHECK(hipGetLastError());
   return DP_OK;
 }

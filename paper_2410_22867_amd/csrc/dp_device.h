@@ -172,32 +172,38 @@ __device__ __forceinline__ void store4(typename P::store_t* p, const float* v) {
 // heavy nets' slots and each work-group would get a few columns only, its
 // waves idling at its end for up to one column each.  Returns -1 for b past
 // the shares (none when G >= nnets and some net has work).
-__device__ __forceinline__ int net_of_group(const int32_t* meta, const int* sec, int ntypes, int G, int b, int* j,
-                                            int* gk) {
+// net_share: the share [lo, hi) of net k.
+__device__ __forceinline__ void net_share(const int32_t* meta, const int* sec, int ntypes, int G, int k, int* lo,
+                                          int* hi) {
   const int nnets = ntypes * ntypes;
-  auto wt = [&](int k) -> int64_t {
-    const int kti = k / ntypes, ktj = k - kti * ntypes;
+  auto wt = [&](int q) -> int64_t {
+    const int kti = q / ntypes, ktj = q - kti * ntypes;
     return (int64_t)meta[2 * kti] * ((sec[ktj + 1] - sec[ktj] + 15) / 16);
   };
   int64_t total = 0;
-  for (int k = 0; k < nnets; ++k) total += wt(k);
+  for (int q = 0; q < nnets; ++q) total += wt(q);
   const int64_t spare = G - nnets;
-  for (int k = 0; k < nnets; ++k) {
-    const int64_t wk = wt(k);
-    int rank = 0;
-    int64_t before = 0;  // work of the nets ranked before k
-    for (int q = 0; q < nnets; ++q) {
-      const int64_t wq = wt(q);
-      if (wq > wk || (wq == wk && q < k)) {
-        ++rank;
-        before += wq;
-      }
+  const int64_t wk = wt(k);
+  int rank = 0;
+  int64_t before = 0;  // work of the nets ranked before k
+  for (int q = 0; q < nnets; ++q) {
+    const int64_t wq = wt(q);
+    if (wq > wk || (wq == wk && q < k)) {
+      ++rank;
+      before += wq;
     }
-    const int64_t lo = rank + (total > 0 ? spare * before / total : 0);
-    const int64_t hi = rank + 1 + (total > 0 ? spare * (before + wk) / total : 0);
+  }
+  *lo = (int)(rank + (total > 0 ? spare * before / total : 0));
+  *hi = (int)(rank + 1 + (total > 0 ? spare * (before + wk) / total : 0));
+}
+__device__ __forceinline__ int net_of_group(const int32_t* meta, const int* sec, int ntypes, int G, int b, int* j,
+                                            int* gk) {
+  for (int k = 0; k < ntypes * ntypes; ++k) {
+    int lo, hi;
+    net_share(meta, sec, ntypes, G, k, &lo, &hi);
     if (b >= lo && b < hi) {
-      *j = (int)(b - lo);
-      *gk = (int)(hi - lo);
+      *j = b - lo;
+      *gk = hi - lo;
       return k;
     }
   }

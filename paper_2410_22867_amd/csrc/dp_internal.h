@@ -244,8 +244,8 @@ struct dp_ctx {
   double* gE_col;          // [cols]
   double* grad_tmp;        // [n_params]
   double* gpart;           // partial sums of the parameter-gradient reductions
-  int32_t grad_chunks;     // column chunks per type of the fitting reductions
-  int32_t grad_slots;      // work-group records per net of the embedding reductions
+  int32_t grad_chunks;     // column chunks of the fitting reductions that gpart holds
+  int32_t grad_slots;      // work-group records of the embedding reductions (w = 25: in all, else per net)
   // opt-in stage timing
   hipEvent_t* prof_ev;     // [2 * prof_cap]
   int32_t* prof_stage;     // [prof_cap]
@@ -316,21 +316,23 @@ void launch_kick_drift(dp_ctx* c, double* x, double* v, const double* f, const i
 void launch_wrap(dp_ctx* c, double* x, int32_t n, const double L[3], int32_t* images, hipStream_t s);
 void launch_kick(dp_ctx* c, double* v, const double* f, const int32_t* types, int32_t n, double dt, double* ke,
                  hipStream_t s);
-// parameter gradients from the state of the last compute, in FP64: the layer
-// inputs X_l and deltas dz_l of the fitting net (columns, leading dims ldx/ldz)
-// and g_T; FP64 computes pass their own buffers, mixed ones widened copies
+// parameter gradients from the state of the last compute, summed in FP64: the
+// layer inputs X_l and deltas dz_l of the fitting net (columns, leading
+// dimensions ldx / ldz) and g_T, in the types the compute left them in
 struct ParamGradInputs {
-  const double* X[3];
-  int ldx[3];
-  const double* dz[3];
-  const double* h3;
+  const void* X[3];
+  int ldx[3];       // ldx[2] also h3's
+  const void* dz[3];
+  const void* h3;
   int ldz;
-  const double* gT;
+  int kind[3];      // 0 f64, 1 f32, 2 bf16, 3 f16: of X1 and dz1; of X2, X3 and h3; of dz2 and dz3
+  const void* gT;
+  int gt32;         // g_T in FP32
 };
-void launch_param_grads(dp_ctx* c, const ParamGradInputs& in, const double* dLdE, double* grad, hipStream_t s);
-// widens a [rows][width] block of FP32 (kind 0), BF16 (1) or FP16 (2) values
-void launch_widen(const void* src, int kind, int ld_src, double* dst, int ld_dst, int width, int64_t rows,
-                  hipStream_t s);
+// fill_act (w = 25): the embedding gradient recomputes the last layer and
+// writes it to the activation store
+void launch_param_grads(dp_ctx* c, const ParamGradInputs& in, const double* dLdE, double* grad, bool fill_act,
+                        hipStream_t s);
 // inspection
 void launch_gather_cols(dp_ctx* c, int32_t which, int32_t mode, int32_t ntot, double* dst, hipStream_t s);
 
