@@ -75,6 +75,15 @@ template <int W>
 __device__ __forceinline__ constexpr bool kpadh(int t, int v) {
   return W <= 28 && (t & 1) && v == 3;
 }
+// One 32-slot k-step: its element 7 holds the padding slots of the odd tile,
+// so with w <= 28 the FP32 form, which issues one product per element, leaves
+// it out (water12k: forward 258 -> 241 us, backward 478 -> 450 us; FP32 products and vector
+// operations of a SIMD do not overlap, so the kernels are at their issue bound).
+template <class P, int W>
+__device__ __forceinline__ f4 mfma_h(typename P::vec8 a, typename P::vec8 b, f4 c) {
+  if constexpr (P::kind == 3 && kpadh<W>(1, 3)) return P::mfma7(a, b, c);
+  else return P::mfma(a, b, c);
+}
 template <int W>
 __device__ __forceinline__ int feat3h_of_slot(int p) {  // -1 for padding slots
   const int q = p & 31;
@@ -712,7 +721,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
       for (int ot = 0; ot < 4; ++ot) {
         f4 z = PS ? f4{0.f, 0.f, 0.f, 0.f} : f4{b2s[ot][0], b2s[ot][1], b2s[ot][2], b2s[ot][3]};
-        z = P::mfma(load8<P>(fr + z0 + (ot * 64 + lane) * 8), b1v, z);
+        z = mfma_h<P, W>(load8<P>(fr + z0 + (ot * 64 + lane) * 8), b1v, z);
 #pragma unroll
         for (int v = 0; v < 4; ++v) h2[ot][v] = kpadh<W>(ot, v) ? 0.f : h1[4 * (ot & 1) + v] + act(z[v], b2s[ot][v]);
       }
@@ -743,7 +752,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
         const float b3 = vec[kV_B3F + feat];  // the table spans kP3 features
         f4 z = PS ? f4{0.f, 0.f, 0.f, 0.f} : f4{b3, b3, b3, b3};
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) z = P::mfma(a3[kt], load8<P>(fr + z0 + NF2 + ((o * 2 + kt) * 64 + lane) * 8), z);
+        for (int kt = 0; kt < 2; ++kt) z = mfma_h<P, W>(a3[kt], load8<P>(fr + z0 + NF2 + ((o * 2 + kt) * 64 + lane) * 8), z);
         if constexpr (MC) {
           // A operand: G of rows 4g..4g+3 of this lane's feature (0 past m1)
           float gv[4] = {0.f, 0.f, 0.f, 0.f};
@@ -935,7 +944,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
       for (int ot = 0; ot < 4; ++ot) {
         const float* b2 = vec + kV_B2 + 16 * ot + 4 * g;
         f4 z = {b2[0], b2[1], b2[2], kpadh<W>(ot, 3) ? 0.f : b2[3]};
-        z = P::mfma(load8<P>(fr + z0 + oF2 + (ot * 64 + lane) * 8), b1v, z);
+        z = mfma_h<P, W>(load8<P>(fr + z0 + oF2 + (ot * 64 + lane) * 8), b1v, z);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           t2[ot][v] = kpadh<W>(ot, v) ? 0.f : tanh_f(z[v]);
@@ -978,7 +987,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
         const float* b3 = vec + kV_B3S + 16 * o + 4 * g;
         f4 z = {b3[0], b3[1], b3[2], kpadh<W>(o, 3) ? 0.f : b3[3]};
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) z = P::mfma(load8<P>(fr + z0 + oF3 + ((o * 2 + kt) * 64 + lane) * 8), b2v[kt], z);
+        for (int kt = 0; kt < 2; ++kt) z = mfma_h<P, W>(load8<P>(fr + z0 + oF3 + ((o * 2 + kt) * 64 + lane) * 8), b2v[kt], z);
         f4 dGv;
         if constexpr (MC) {
           dGv = mfma_f16k16(__builtin_bit_cast(h16x4, gth[gw][16 * o + r16]), bR, f4{0.f, 0.f, 0.f, 0.f});
@@ -1021,7 +1030,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
       for (int i2 = 0; i2 < 4; ++i2) {
         f4 z = {skip2[i2][0], skip2[i2][1], skip2[i2][2], skip2[i2][3]};
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) z = P::mfma(load8<P>(fr + z0 + oB3 + ((i2 * 4 + kt) * 64 + lane) * 8), bz3[kt], z);
+        for (int kt = 0; kt < 4; ++kt) z = mfma_h<P, W>(load8<P>(fr + z0 + oB3 + ((i2 * 4 + kt) * 64 + lane) * 8), bz3[kt], z);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           if (kpadh<W>(i2, v)) {
@@ -1046,7 +1055,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
       for (int i2 = 0; i2 < 2; ++i2) {
         f4 z = {skip1[i2][0], skip1[i2][1], skip1[i2][2], skip1[i2][3]};
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) z = P::mfma(load8<P>(fr + z0 + oB2 + ((i2 * 2 + kt) * 64 + lane) * 8), bz2[kt], z);
+        for (int kt = 0; kt < 2; ++kt) z = mfma_h<P, W>(load8<P>(fr + z0 + oB2 + ((i2 * 2 + kt) * 64 + lane) * 8), bz2[kt], z);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           if (kpadh<W>(i2, v)) continue;
