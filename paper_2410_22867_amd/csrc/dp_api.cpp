@@ -1138,7 +1138,7 @@ int dp_ctx_create(const dp_model* m, int64_t max_atoms, int32_t max_frames, int6
   ALLOC(c->cell_fill, c->max_cells + 1);
   ALLOC(c->cell_atoms, N);
   ALLOC(c->chunk_counts, (int64_t)nchunks * kMaxT + kMaxT);
-  ALLOC(c->type_meta, 2 * kMaxT);
+  ALLOC(c->type_meta, 2 * kMaxT + (int64_t)sizeof(NetShares) / 4);
   ALLOC(c->col_of, N);
   ALLOC(c->atom_at, C);
   ALLOC(c->frame_of, N);

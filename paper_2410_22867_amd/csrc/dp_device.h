@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dp_internal.h"
+
 namespace dpse {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
@@ -170,52 +172,39 @@ __device__ __forceinline__ void store4(typename P::store_t* p, const float* v) {
 
 // Per-net kernels on a one-row grid (the embedding nets, forward and
 // backward, and their tabulated form): every net gets one work-group and
-// the other G - nnets are split in proportion to the nets' work (a net's
-// columns times its section's row tiles), the nets' shares laid out in
-// decreasing order of work.  Work-group b serves the net
-// whose share holds b, as the j-th of gk work-groups.  A grid of the
-// work-groups the CUs hold at once then finishes every net in one round:
-// with one net per grid row, the light nets' work-groups would wait for the
-// heavy nets' slots and each work-group would get a few columns only, its
-// waves idling at its end for up to one column each.  Returns -1 for b past
-// the shares (none when G >= nnets and some net has work).
-// net_share: the share [lo, hi) of net k.
-__device__ __forceinline__ void net_share(const int32_t* meta, const int* sec, int ntypes, int G, int k, int* lo,
-                                          int* hi) {
-  const int nnets = ntypes * ntypes;
-  auto wt = [&](int q) -> int64_t {
-    const int kti = q / ntypes, ktj = q - kti * ntypes;
-    return (int64_t)meta[2 * kti] * ((sec[ktj + 1] - sec[ktj] + 15) / 16);
-  };
-  int64_t total = 0;
-  for (int q = 0; q < nnets; ++q) total += wt(q);
-  const int64_t spare = G - nnets;
-  const int64_t wk = wt(k);
-  int rank = 0;
-  int64_t before = 0;  // work of the nets ranked before k
-  for (int q = 0; q < nnets; ++q) {
-    const int64_t wq = wt(q);
-    if (wq > wk || (wq == wk && q < k)) {
-      ++rank;
-      before += wq;
-    }
-  }
-  *lo = (int)(rank + (total > 0 ? spare * before / total : 0));
-  *hi = (int)(rank + 1 + (total > 0 ? spare * (before + wk) / total : 0));
+// the other G - nnets are split in proportion to the nets' work (NetShares of
+// the given kind), the nets' shares laid out in decreasing order of work.
+// Work-group b serves the net whose share holds b, as the j-th of gk
+// work-groups.  A grid of the work-groups the CUs hold at once then finishes
+// every net in one round: with one net per grid row, the light nets'
+// work-groups would wait for the heavy nets' slots and each work-group would
+// get a few columns only, its waves idling at its end for up to one column
+// each.  Returns -1 for b past the shares (none when G >= nnets and some net
+// has work).  The end of a share and the start of the next are the same
+// expression, so the shares join; 1e-6 makes the last one end at G.
+__device__ __forceinline__ const NetShares* net_shares(const int32_t* meta) {
+  return reinterpret_cast<const NetShares*>(meta + 2 * kMaxT);
 }
-__device__ __forceinline__ int net_of_group(const int32_t* meta, const int* sec, int ntypes, int G, int b, int* j,
-                                            int* gk) {
-  for (int k = 0; k < ntypes * ntypes; ++k) {
-    int lo, hi;
-    net_share(meta, sec, ntypes, G, k, &lo, &hi);
-    if (b >= lo && b < hi) {
+__device__ __forceinline__ int share_start(const NetShares* S, int kind, int nnets, int G, int rank) {
+  return rank + (int)((double)(G - nnets) * S->before[kind][rank] + 1e-6);
+}
+__device__ __forceinline__ int net_of_group(const int32_t* meta, int ntypes, int G, int b, int* j, int* gk, int kind) {
+  const NetShares* S = net_shares(meta);
+  const int nnets = ntypes * ntypes;
+  int lo = 0;
+  for (int r = 0; r < nnets; ++r) {
+    const int hi = share_start(S, kind, nnets, G, r + 1);
+    if (b < hi) {
       *j = b - lo;
       *gk = hi - lo;
-      return k;
+      return S->net[kind][r];
     }
+    lo = hi;
   }
   return -1;
 }
+// Start of part g of n columns in G parts (part G starts at n).
+__device__ __forceinline__ int part_start(int n, int g, int G) { return (int)((double)n * (double)g / (double)G); }
 
 // ---------------------------------------------------------------------------
 // Activations.  FP32 (mixed forms): 1 - 2/(e^{2x}+1) with the hardware exp2
@@ -369,6 +358,25 @@ __device__ __forceinline__ double env_elt(env_rsrc_t r, int q, int c) {
   const u2v a = __builtin_amdgcn_raw_buffer_load_b64(r, q * 32 + c * 8, 0, 0);
   return __builtin_bit_cast(double, (unsigned long long)a[0] | ((unsigned long long)a[1] << 32));
 }
+
+// Copies N bytes (a multiple of 16, both sides 16-byte aligned) to LDS with NT
+// threads: load() requests every read, store() writes them, so that several
+// copies can be in flight together before the first wait.
+template <int N, int NT>
+struct LdsCopy {
+  typedef unsigned u4v __attribute__((ext_vector_type(4)));
+  static constexpr int L = (N / 16 + NT - 1) / NT;
+  u4v x[L];
+  __device__ __forceinline__ void load(const void* src) {
+#pragma unroll
+    for (int l = 0; l < L; ++l) x[l] = static_cast<const u4v*>(src)[min((int)threadIdx.x + l * NT, N / 16 - 1)];
+  }
+  __device__ __forceinline__ void store(void* dst) const {
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+      if ((int)threadIdx.x + l * NT < N / 16) static_cast<u4v*>(dst)[threadIdx.x + l * NT] = x[l];
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Wavefront helpers (wave64).

@@ -33,6 +33,19 @@ struct FrameInfo {
   double L[3];        // orthorhombic edges
 };
 
+// Work shares of the embedding nets, written by the type sort behind the
+// per-type counts and bases (type_meta): the nets in decreasing order of their
+// work (a net's columns times a unit of its section; ties in net order) and
+// the part of the total work that comes before each rank.  Kind 0 counts
+// 16-row tiles of the full section, kind 1 (kGroupWaves waves sharing a
+// column) rounds of kGroupWaves tiles of a section filled to 5/8, as real
+// ones are.
+constexpr int kGroupWaves = 4;
+struct NetShares {
+  double before[2][kMaxT * kMaxT + 1];
+  int32_t net[2][kMaxT * kMaxT];
+};
+
 // Fragment-arranged weights of one embedding net in one precision.
 // Element counts (per net) for every precision:
 //   F2   : fwd layer 2 (T layout)        4 ot x 32 in-slots  x 16 = 2048
@@ -190,7 +203,7 @@ struct dp_ctx {
   int32_t* cell_atoms;
   // type sort
   int32_t* chunk_counts;   // [nchunks * kMaxT]
-  int32_t* type_meta;      // [2*kMaxT]: n_t, cbase_t
+  int32_t* type_meta;      // [2*kMaxT]: n_t, cbase_t; NetShares
   int32_t* col_of;         // [max_atoms]
   int32_t* atom_at;        // [max_cols]
   int32_t* frame_of;       // [max_atoms]

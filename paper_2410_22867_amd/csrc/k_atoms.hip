@@ -99,8 +99,12 @@ __global__ __launch_bounds__(1024) void k_type_count(const int32_t* __restrict__
 }
 
 // One thread per type: turns per-chunk counts into per-chunk offsets and
-// writes n_t and the segment bases.
-__global__ void k_type_scan(int32_t* __restrict__ chunk_counts, int nchunks, int ntypes,
+// writes n_t and the segment bases; then one thread per net and kind writes
+// its place in the order of the nets' work (NetShares).
+struct Sections {
+  int sec[kMaxT + 1];
+};
+__global__ void k_type_scan(int32_t* __restrict__ chunk_counts, int nchunks, int ntypes, Sections q,
                             int32_t* __restrict__ meta) {
   __shared__ int32_t tot[kMaxT];
   int t = threadIdx.x;
@@ -123,6 +127,28 @@ __global__ void k_type_scan(int32_t* __restrict__ chunk_counts, int nchunks, int
       base += ((tot[u] + kColPad - 1) / kColPad) * kColPad;
     }
   }
+  const int kind = t >> 4, k = t & 15, nnets = ntypes * ntypes;
+  if (kind >= 2 || k >= nnets) return;
+  auto work = [&](int net) -> int64_t {
+    const int ti = net / ntypes, tj = net - ti * ntypes, n = q.sec[tj + 1] - q.sec[tj];
+    const int unit = kind == 0 ? (n + 15) / 16 : (n * 5 / 8 + 16 * kGroupWaves - 1) / (16 * kGroupWaves);
+    return (int64_t)tot[ti] * unit;
+  };
+  const int64_t own = work(k);
+  int64_t total = 0, before = 0;
+  int rank = 0;
+  for (int o = 0; o < nnets; ++o) {
+    const int64_t w = work(o);
+    total += w;
+    if (w > own || (w == own && o < k)) {
+      ++rank;
+      before += w;
+    }
+  }
+  NetShares* S = reinterpret_cast<NetShares*>(meta + 2 * kMaxT);
+  S->net[kind][rank] = k;
+  S->before[kind][rank] = total > 0 ? (double)before / (double)total : 0.0;
+  if (rank == nnets - 1) S->before[kind][nnets] = total > 0 ? 1.0 : 0.0;
 }
 
 __global__ __launch_bounds__(1024) void k_type_assign(const int32_t* __restrict__ types, int ntot, int ntypes,
@@ -160,7 +186,9 @@ void launch_type_sort(dp_ctx* c, const int32_t* types, int32_t ntot, int32_t nfr
   if (ntot > 0)
     hipLaunchKernelGGL(k_type_count, dim3(nchunks), dim3(kChunk), 0, s, types, ntot, ntypes, c->chunk_counts,
                        c->flags_dev);
-  hipLaunchKernelGGL(k_type_scan, dim3(1), dim3(64), 0, s, c->chunk_counts, nchunks, ntypes, c->type_meta);
+  Sections q;
+  for (int t = 0; t <= kMaxT; ++t) q.sec[t] = c->model->sec[t < ntypes ? t : ntypes];
+  hipLaunchKernelGGL(k_type_scan, dim3(1), dim3(64), 0, s, c->chunk_counts, nchunks, ntypes, q, c->type_meta);
   if (ntot > 0)
     hipLaunchKernelGGL(k_type_assign, dim3(nchunks), dim3(kChunk), 0, s, types, ntot, ntypes, c->chunk_counts,
                        c->type_meta, c->frames_dev, nframes, c->col_of, c->atom_at, c->frame_of);

@@ -64,6 +64,7 @@ struct EmbArgs {
   int sec[kMaxT + 1];
   double inv_nm;
   int32_t* ctr;          // [nets][gridDim.x][32] per-work-group column counters
+  int kind;              // kind of the nets' shares on a one-row grid (1: group mode)
 };
 
 // Slot order of the half-precision kernels (lane group g, element v hold
@@ -103,30 +104,11 @@ __constant__ double kExp2Frac32[32] = {
     1.7562521603732995, 1.7947090750031072, 1.8340080864093424, 1.8741676341103, 1.9152065613971474,
     1.9571441241754002};
 
-// The net that work-group row y serves: the nets in decreasing order of
-// their work, the centre type's columns times the neighbour section's row
-// tiles (ceil(sel / 16)), ties in net order.  Rows are dispatched in order,
-// so the heaviest net's work-groups start first and the lighter ones fill
-// the end of the launch.
-__device__ __forceinline__ int net_of_row(const int32_t* meta, const int* sec, int ntypes, int y) {
-  const int nnets = ntypes * ntypes;
-  int64_t wt[kMaxT * kMaxT];
-  for (int k = 0; k < nnets; ++k) {
-    const int kti = k / ntypes, ktj = k - kti * ntypes;
-    wt[k] = (int64_t)meta[2 * kti] * ((sec[ktj + 1] - sec[ktj] + 15) / 16);
-  }
-  for (int k = 0; k < nnets; ++k) {
-    int rank = 0;
-    for (int q = 0; q < nnets; ++q) rank += wt[q] > wt[k] || (wt[q] == wt[k] && q < k);
-    if (rank == y) return k;
-  }
-  return 0;
-}
-
 // Common prologue of the per-net kernels: net = t_i * ntypes + t_j (centre
-// type t_i, neighbour section t_j) from net_of_group (one-row grid) or
-// net_of_row (one grid row per net).  Work assignment: the
-// net's columns are split into contiguous ranges, one per
+// type t_i, neighbour section t_j) from net_of_group (one-row grid) or, with
+// one grid row per net, the y-th heaviest (rows are dispatched in order, so the
+// heaviest net's work-groups start first and the lighter ones fill the end of
+// the launch).  Work assignment: the net's columns are split into contiguous ranges, one per
 // work-group; inside its range a wavefront takes the next column from the
 // work-group's counter (a word in global memory that no other work-group
 // touches, set by the work-group itself before its first barrier; the next
@@ -139,13 +121,13 @@ __device__ __forceinline__ int net_of_row(const int32_t* meta, const int* sec, i
 #define DPSE_NET_PROLOGUE(WPB)                                            \
   int grp = blockIdx.x, ngrp = gridDim.x;                                 \
   const int net = gridDim.y == 1                                          \
-                      ? net_of_group(A.meta, A.sec, A.ntypes, gridDim.x, blockIdx.x, &grp, &ngrp) \
-                      : net_of_row(A.meta, A.sec, A.ntypes, blockIdx.y);  \
+                      ? net_of_group(A.meta, A.ntypes, gridDim.x, blockIdx.x, &grp, &ngrp, A.kind) \
+                      : net_shares(A.meta)->net[0][blockIdx.y];           \
   if (net < 0) return;                                                    \
   const int ti = net / A.ntypes, tj = net - ti * A.ntypes;                \
   const int n_t = A.meta[2 * ti], cb = A.meta[2 * ti + 1];                \
-  const int c_lo = (int)((int64_t)n_t * grp / ngrp);                      \
-  const int c_hi = (int)((int64_t)n_t * (grp + 1) / ngrp);                \
+  const int c_lo = part_start(n_t, grp, ngrp);                            \
+  const int c_hi = part_start(n_t, grp + 1, ngrp);                        \
   if (c_lo >= c_hi) return;                                               \
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;              \
   const int r16 = lane & 15, g = lane >> 4;                               \
@@ -159,11 +141,12 @@ __device__ __forceinline__ int net_of_row(const int32_t* meta, const int* sec, i
   };
 
 // ============================================================== FP64 forward
-// Group mode (GM, frames of few atoms): the work-group's waves share one
-// column at a time, wave w taking its tiles w, w + WPB, ...; the waves'
-// partial T are added in wave order through LDS.  Without it each wave owns
-// a column and walks its tiles alone, which leaves most of the chip idle
-// when there are fewer columns than wave slots.
+// Group mode (GM, frames of few atoms): four waves share a column, wave w of
+// them taking its tiles w, w + 4, ... (a water section has two to four), and a
+// work-group's groups the columns of its range in turn; the waves' partial T
+// are added in wave order through LDS.  Without it each wave owns a column and
+// walks its tiles alone, which leaves most of the chip idle when there are
+// fewer columns than wave slots.
 template <int W, int WPB, bool ST, bool GM>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 4, WPB / 4))) void k_embed_fwd_f64(EmbArgs A) {
   constexpr int M1 = 4 * W;
@@ -176,39 +159,47 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 
   // its contraction runs over the lane's own row
   constexpr int REM = M1 % 16;
   constexpr bool TLAST = REM > 0 && REM <= 4;
-  __shared__ double fr[NF2 + NF3];
+  __shared__ __attribute__((aligned(16))) double fr[NF2 + NF3];
   __shared__ double h2s[WPB][16][HS];
-  __shared__ double vs[kVecPerNet];
+  __shared__ __attribute__((aligned(16))) double vs[kVecPerNet];
   // tanh table: steps of 1/128 where LDS has room (w = 25), 1/64 otherwise
   constexpr int LOG = W <= 28 ? 7 : 6;
   __shared__ double etab[LOG == 7 ? kTanhLutEntries : kTanhLutEntries / 2];
-  __shared__ int col_sh;  // group mode: the work-group's column
   DPSE_NET_PROLOGUE(WPB)
   const int lo4 = (lane & 3) + 4 * (lane >> 4);
   {
     const double* src = A.frag64 + net * A.fo.per_net;
-    for (int k = threadIdx.x; k < NF2; k += 64 * WPB) fr[k] = src[A.fo.F2 + k];
-    for (int k = threadIdx.x; k < NF3; k += 64 * WPB) fr[NF2 + k] = src[A.fo.F3n + k];
-    const double* vsrc = A.vec64 + net * A.vec_per_net;
-    for (int k = threadIdx.x; k < kVecPerNet; k += 64 * WPB) vs[k] = vsrc[k];
-    constexpr int NE = LOG == 7 ? kTanhLutEntries : kTanhLutEntries / 2;
-    for (int k = threadIdx.x; k < NE; k += 64 * WPB) etab[k] = A.tanh_lut[LOG == 7 ? k : 2 * k];
+    constexpr int NT = 64 * WPB, NE = LOG == 7 ? kTanhLutEntries : kTanhLutEntries / 2;
+    LdsCopy<NF2 * 8, NT> f2;
+    LdsCopy<NF3 * 8, NT> f3;
+    LdsCopy<kVecPerNet * 8, NT> fv;
+    f2.load(src + A.fo.F2);
+    f3.load(src + A.fo.F3n);
+    fv.load(A.vec64 + net * A.vec_per_net);
+    double le[(NE + NT - 1) / NT];
+#pragma unroll
+    for (int l = 0; l < (NE + NT - 1) / NT; ++l)
+      le[l] = A.tanh_lut[min((int)threadIdx.x + l * NT, NE - 1) * (LOG == 7 ? 1 : 2)];
+    f2.store(fr);
+    f3.store(fr + NF2);
+    fv.store(vs);
+#pragma unroll
+    for (int l = 0; l < (NE + NT - 1) / NT; ++l)
+      if ((int)threadIdx.x + l * NT < NE) etab[threadIdx.x + l * NT] = le[l];
   }
   __syncthreads();
-  constexpr int RSTEP = GM ? 16 * WPB : 16;  // rows between a wave's tiles
-  const int rfirst = GM ? 16 * wv : 0;
+  constexpr int SG = GM ? kGroupWaves : 1, NS = WPB / SG;  // waves per column, columns at a time
+  constexpr int RSTEP = 16 * SG;                           // rows between a wave's tiles
+  const int sub = wv / SG, rfirst = 16 * (wv % SG);
 
-  for (int c_next = GM ? 0 : take();;) {
-    int c;
-    if constexpr (GM) {
-      if (threadIdx.x == 0) col_sh = atomicAdd(next_col, 1);
-      __syncthreads();
-      c = __builtin_amdgcn_readfirstlane(col_sh);
-    } else {
-      c = __builtin_amdgcn_readfirstlane(c_next);
-    }
+  for (int c_next = GM ? c_lo : take();;) {
+    int c = __builtin_amdgcn_readfirstlane(c_next);
     if (c >= c_hi) break;
-    if constexpr (!GM) c_next = take();
+    // group mode: the same number of rounds for every wave (they meet at
+    // barriers), an idle group walks no tile of the last column
+    c_next = GM ? c_next + NS : take();
+    const bool on = !GM || c + sub < c_hi;
+    if constexpr (GM) c = min(c + sub, c_hi - 1);
     const int col = cb + c;
     const int i = A.atom_at[col];
     double accT[N3][4];
@@ -217,7 +208,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 
 #pragma unroll
       for (int k = 0; k < 4; ++k) accT[o][k] = 0.0;
     double accL[4] = {0.0, 0.0, 0.0, 0.0};  // last tile when transposed: feature 16 (N3 - 1) + g, over rows r16
-    const int nn = A.nnei[i * kMaxT + tj];
+    const int nn = on ? A.nnei[i * kMaxT + tj] : 0;
     const double* Rs = A.R + ((int64_t)i * A.nm + A.sec[tj]) * 4;
     double s_next = rfirst + r16 < nn ? Rs[(rfirst + r16) * 4] : 0.0;  // s of the next tile is always in flight
     for (int r0 = rfirst; r0 < nn; r0 += RSTEP) {
@@ -348,19 +339,22 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 
     if constexpr (GM) {
       static_assert(WPB * M1 * 4 <= WPB * 16 * HS, "partials fit the h2s tiles");
       __syncthreads();
-      const double* red = &h2s[0][0][0];
-      for (int e = threadIdx.x; e < M1 * 4; e += 64 * WPB) {
-        double x = red[e];
-        for (int w = 1; w < WPB; ++w) x += red[w * M1 * 4 + e];
-        T[e] = x;
-      }
-      __syncthreads();  // h2s and col_sh are reused by the next column
+      const double* red = &h2s[0][0][0] + sub * SG * M1 * 4;
+      if (on)
+        for (int e = 64 * (wv % SG) + lane; e < M1 * 4; e += 64 * SG) {
+          double x = red[e];
+#pragma unroll
+          for (int w = 1; w < SG; ++w) x += red[w * M1 * 4 + e];
+          T[e] = x;
+        }
+      __syncthreads();  // h2s is reused by the next column
     }
   }
 }
 
 // ============================================================== FP64 backward
-// GM: group mode as in the forward (the waves share the column's g_T tile).
+// GM: group mode as in the forward (a group's waves share the column's g_T
+// tile).
 template <int W, int WPB, bool ST, bool GM>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 4, WPB / 4))) void k_embed_bwd_f64(EmbArgs A) {
   constexpr int M1 = 4 * W;
@@ -374,58 +368,71 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 
                 oF3 = oB3 + LY::B3;
   constexpr bool E32 = !SM && GM;     // room for the small table of tanh_d_tab only
   constexpr int oE = oF3 + (ST ? 0 : LY::F3t);
-  __shared__ double fr[oE + (E32 ? 32 : 0)];
-  __shared__ d4 gts[GM ? 1 : WPB][4 * LY::n3];
-  __shared__ int col_sh;  // group mode: the work-group's column
+  __shared__ __attribute__((aligned(16))) double fr[oE + (E32 ? 32 : 0)];
+  __shared__ d4 gts[GM ? WPB / kGroupWaves : WPB][4 * LY::n3];
   DPSE_NET_PROLOGUE(WPB)
   const int lo4 = (lane & 3) + 4 * (lane >> 4);
   const double* gsrc = A.frag64 + net * A.fo.per_net;
   const double* vecg = A.vec64 + net * A.vec_per_net;
-  auto stage = [&](int dst, const double* src, int n) {
-    for (int k = threadIdx.x; k < n; k += 64 * WPB) fr[dst + k] = src[k];
-  };
-  if constexpr (SM) {
-    stage(0, gsrc + A.fo.F2, LY::F2);
-    stage(oB2, gsrc + A.fo.B2, LY::B2);
-    stage(oV, vecg, kVecPerNet);
-    stage(oT, A.tanh_lut, kTanhLutEntries);
+  {
+    constexpr int NT = 64 * WPB;
+    LdsCopy<LY::F2 * 8, NT> f2, b2;
+    LdsCopy<kVecPerNet * 8, NT> fv;
+    LdsCopy<kTanhLutEntries * 8, NT> ft;
+    LdsCopy<LY::B3 * 8, NT> b3;
+    if constexpr (SM) {
+      f2.load(gsrc + A.fo.F2);
+      b2.load(gsrc + A.fo.B2);
+      fv.load(vecg);
+      ft.load(A.tanh_lut);
+    }
+    b3.load(gsrc + A.fo.B3);
+    if constexpr (SM) {
+      f2.store(fr);
+      b2.store(fr + oB2);
+      fv.store(fr + oV);
+      ft.store(fr + oT);
+    }
+    if constexpr (!ST) {
+      LdsCopy<LY::F3t * 8, NT> f3;
+      f3.load(gsrc + A.fo.F3t);
+      b3.store(fr + oB3);
+      f3.store(fr + oF3);
+    } else {
+      b3.store(fr + oB3);
+    }
+    if (E32 && threadIdx.x < 32) fr[oE + threadIdx.x] = kExp2Frac32[threadIdx.x];
   }
-  stage(oB3, gsrc + A.fo.B3, LY::B3);
-  if constexpr (!ST) stage(oF3, gsrc + A.fo.F3t, LY::F3t);
-  if constexpr (E32) stage(oE, kExp2Frac32, 32);
   __syncthreads();
   auto tanh_l = [&](double x) {
     return SM ? tanh_lut<7>(x, fr + oT) : E32 ? tanh_d_tab(x, fr + oE) : tanh_d(x);
   };
-  const int gw = GM ? 0 : wv;  // this wave's g_T tile
-  constexpr int RSTEP = GM ? 16 * WPB : 16;
-  const int rfirst = GM ? 16 * wv : 0;
-  for (int c_next = GM ? 0 : take();;) {
-    int c;
-    if constexpr (GM) {
-      if (threadIdx.x == 0) col_sh = atomicAdd(next_col, 1);
-      __syncthreads();
-      c = __builtin_amdgcn_readfirstlane(col_sh);
-    } else {
-      c = __builtin_amdgcn_readfirstlane(c_next);
-    }
+  constexpr int SG = GM ? kGroupWaves : 1, NS = WPB / SG;  // waves per column, columns at a time
+  constexpr int RSTEP = 16 * SG;                           // rows between a wave's tiles
+  const int sub = wv / SG, rfirst = 16 * (wv % SG);
+  for (int c_next = GM ? c_lo : take();;) {
+    int c = __builtin_amdgcn_readfirstlane(c_next);
     if (c >= c_hi) break;
-    if constexpr (!GM) c_next = take();
+    // group mode: the same number of rounds for every wave (they meet at
+    // barriers), an idle group walks no tile of the last column
+    c_next = GM ? c_next + NS : take();
+    const bool on = !GM || c + sub < c_hi;
+    if constexpr (GM) c = min(c + sub, c_hi - 1);
     const int col = cb + c;
     const int i = A.atom_at[col];
     {
       const double* gT = reinterpret_cast<const double*>(A.gT) + (int64_t)col * M1 * 4;
       if constexpr (!GM) wave_lds_sync();
-      for (int p = GM ? (int)threadIdx.x : lane; p < kP3; p += GM ? 64 * WPB : 64) {
+      for (int p = GM ? 64 * (wv % SG) + lane : lane; p < kP3; p += 64 * SG) {
         const int a = feat3d_of_slot<W>(p), cp = LY::col3(p);
         d4 x = {0.0, 0.0, 0.0, 0.0};
         if (a >= 0) x = *reinterpret_cast<const d4*>(gT + a * 4) * A.inv_nm;
-        if (cp >= 0) gts[gw][cp] = x;
+        if (cp >= 0) gts[sub][cp] = x;
       }
       if constexpr (GM) __syncthreads();
       else wave_lds_sync();
     }
-    const int nn = A.nnei[i * kMaxT + tj];
+    const int nn = on ? A.nnei[i * kMaxT + tj] : 0;
     const int64_t rbase = (int64_t)i * A.nm + A.sec[tj];
     const double* Rs = A.R + rbase * 4;
     d4 R_next = {0.0, 0.0, 0.0, 0.0};  // row of the next tile is always in flight
@@ -528,7 +535,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 
               t3 = tanh_l(z[v]);
             }
             const double G = h2[o4][v] + t3;
-            const d4 gt = gts[gw][4 * (e0 + v) + g];
+            const d4 gt = gts[sub][4 * (e0 + v) + g];
             const double dG = gt[0] * Rrow[0] + gt[1] * Rrow[1] + gt[2] * Rrow[2] + gt[3] * Rrow[3];
 #pragma unroll
             for (int k = 0; k < 4; ++k) dRd[k] = fma(gt[k], G, dRd[k]);
@@ -584,7 +591,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 
       }
       if (g == 0 && valid) *reinterpret_cast<d4*>(A.netd + (rbase + row) * 4) = d4{dRd[0] + dsp, dRd[1], dRd[2], dRd[3]};
     }
-    if constexpr (GM) __syncthreads();  // the g_T tile and col_sh are reused by the next column
+    if constexpr (GM) __syncthreads();  // the g_T tile is reused by the next column
   }
 }
 
@@ -601,14 +608,14 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(WPB / 
 // operand moves between lanes and the per-atom T needs no cross-lane
 // reduction.  The FP32 form keeps the vector contraction (its 16x16x4
 // products would cost more than the multiply-adds they replace).
-// GM: group mode as in the FP64 kernels (a work-group's waves share a column).
+// GM: group mode, all of a work-group's waves sharing a column (as the sums
+// over the tiles are FP32, their order is kept).
 template <class P, int W, int WPB, bool GM>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) void k_embed_fwd_lp(EmbArgs A) {
   constexpr int M1 = 4 * W;
   constexpr int N3 = (M1 + 15) / 16;
   constexpr int NF2 = 2048, NF3 = N3 * 1024;
   typedef typename P::store_t ST;
-  typedef typename P::raw8 R8;
   __shared__ __attribute__((aligned(16))) ST fr[NF2 + NF3];
   __shared__ float h2s[WPB][16][kP2 + 1];
   __shared__ float vs[kVecPerNet];
@@ -616,19 +623,25 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
   DPSE_NET_PROLOGUE(WPB)
   {
     const ST* src = reinterpret_cast<const ST*>(A.fraglp) + net * A.fo.per_net;
-    for (int k = threadIdx.x; k < NF2 / 8; k += 64 * WPB)
-      reinterpret_cast<R8*>(fr)[k] = reinterpret_cast<const R8*>(src + A.fo.F2)[k];
-    for (int k = threadIdx.x; k < NF3 / 8; k += 64 * WPB)
-      reinterpret_cast<R8*>(fr + NF2)[k] = reinterpret_cast<const R8*>(src + A.fo.F3n)[k];
-  }
-  __syncthreads();
-  {
+    constexpr int NT = 64 * WPB, NV = (kVecPerNet + NT - 1) / NT;
+    LdsCopy<NF2 * sizeof(ST), NT> f2;
+    LdsCopy<NF3 * sizeof(ST), NT> f3;
+    f2.load(src + A.fo.F2);
+    f3.load(src + A.fo.F3n);
     const float* vsrc = A.vec32 + net * A.vec_per_net;
+    float v[NV];
+#pragma unroll
+    for (int l = 0; l < NV; ++l) v[l] = vsrc[min((int)threadIdx.x + l * NT, kVecPerNet - 1)];
+    f2.store(fr);
+    f3.store(fr + NF2);
     // 16-bit forms: the biases pre-scaled by 2/ln 2 (they enter only tanh
     // arguments, as fma(z, 2/ln 2, b'), which saves the accumulator set-up
     // of every product); the layer-1 weights as they are
-    for (int k = threadIdx.x; k < kVecPerNet; k += 64 * WPB)
-      vs[k] = P::kind != 3 && k >= kV_B1 ? vsrc[k] * kTanhScale : vsrc[k];
+#pragma unroll
+    for (int l = 0; l < NV; ++l) {
+      const int k = threadIdx.x + l * NT;
+      if (k < kVecPerNet) vs[k] = P::kind != 3 && k >= kV_B1 ? v[l] * kTanhScale : v[l];
+    }
   }
   __syncthreads();
   constexpr bool MC = P::kind != 3;  // contraction on the matrix cores
@@ -848,53 +861,49 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
   constexpr int NFR = 2048 + 8192 + 8192 + 2048;  // F2 | F3t | B3 | B2
   constexpr bool MC = P::kind != 3;  // contractions on the matrix cores
   typedef typename P::store_t ST;
-  typedef typename P::raw8 R8;
   __shared__ __attribute__((aligned(16))) ST fr[NFR];
-  constexpr int NG = GM ? 1 : WPB;                // g_T tiles (group mode: one, shared)
+  constexpr int NG = GM ? WPB / kGroupWaves : WPB;  // g_T tiles (group mode: one per group)
   __shared__ f4 gts[MC ? 1 : NG][kP3];            // FP32 form: g_T per slot
   __shared__ u16x4 gth[MC ? NG : 1][kP3];         // 16-bit forms: g_T per slot, FP16
   __shared__ u16x4 gtt[MC ? NG : 1][4][kP3 / 4];   // 16-bit forms: column k of g_T, FP16
-  __shared__ float vs[kVecPerNet];
-  __shared__ int col_sh;  // group mode: the work-group's column
+  __shared__ __attribute__((aligned(16))) float vs[kVecPerNet];
   DPSE_NET_PROLOGUE(WPB)
-  {
-    const ST* src = reinterpret_cast<const ST*>(A.fraglp) + net * A.fo.per_net;
-    const int64_t offs[4] = {A.fo.F2, A.fo.F3t, A.fo.B3, A.fo.B2};
-    const int lens[4] = {2048, 8192, 8192, 2048};
-    int dst = 0;
-    for (int b = 0; b < 4; ++b) {
-      for (int k = threadIdx.x; k < lens[b] / 8; k += 64 * WPB)
-        reinterpret_cast<R8*>(fr + dst)[k] = reinterpret_cast<const R8*>(src + offs[b])[k];
-      dst += lens[b];
-    }
-  }
-  __syncthreads();
   constexpr int oF2 = 0, oF3 = 2048, oB3 = 2048 + 8192, oB2 = 2048 + 8192 + 8192;
   {
-    const float* vsrc = A.vec32 + net * A.vec_per_net;
-    for (int k = threadIdx.x; k < kVecPerNet; k += 64 * WPB) vs[k] = vsrc[k];
+    const ST* src = reinterpret_cast<const ST*>(A.fraglp) + net * A.fo.per_net;
+    constexpr int NT = 64 * WPB;
+    LdsCopy<2048 * sizeof(ST), NT> f2, b2;
+    LdsCopy<8192 * sizeof(ST), NT> f3, b3;
+    LdsCopy<kVecPerNet * 4, NT> fv;
+    f2.load(src + A.fo.F2);
+    f3.load(src + A.fo.F3t);
+    b3.load(src + A.fo.B3);
+    b2.load(src + A.fo.B2);
+    fv.load(A.vec32 + net * A.vec_per_net);
+    f2.store(fr + oF2);
+    f3.store(fr + oF3);
+    b3.store(fr + oB3);
+    b2.store(fr + oB2);
+    fv.store(vs);
   }
   __syncthreads();
-  const int gw = GM ? 0 : wv;  // this wave's g_T tile
-  constexpr int RSTEP = GM ? 16 * WPB : 16;
-  const int rfirst = GM ? 16 * wv : 0;
-  for (int c_next = GM ? 0 : take();;) {
-    int c;
-    if constexpr (GM) {
-      if (threadIdx.x == 0) col_sh = atomicAdd(next_col, 1);
-      __syncthreads();
-      c = __builtin_amdgcn_readfirstlane(col_sh);
-    } else {
-      c = __builtin_amdgcn_readfirstlane(c_next);
-    }
+  constexpr int SG = GM ? kGroupWaves : 1, NS = WPB / SG;  // waves per column, columns at a time
+  constexpr int RSTEP = 16 * SG;                           // rows between a wave's tiles
+  const int sub = wv / SG, rfirst = 16 * (wv % SG);
+  for (int c_next = GM ? c_lo : take();;) {
+    int c = __builtin_amdgcn_readfirstlane(c_next);
     if (c >= c_hi) break;
-    if constexpr (!GM) c_next = take();
+    // group mode: the same number of rounds for every wave (they meet at
+    // barriers), an idle group walks no tile of the last column
+    c_next = GM ? c_next + NS : take();
+    const bool on = !GM || c + sub < c_hi;
+    if constexpr (GM) c = min(c + sub, c_hi - 1);
     const int col = cb + c;
     const int i = A.atom_at[col];
     {
       const float* gT = reinterpret_cast<const float*>(A.gT) + (int64_t)col * M1 * 4;
       if constexpr (!GM) wave_lds_sync();
-      for (int p = GM ? (int)threadIdx.x : lane; p < kP3; p += GM ? 64 * WPB : 64) {
+      for (int p = GM ? 64 * (wv % SG) + lane : lane; p < kP3; p += 64 * SG) {
         const int a = feat3h_of_slot<W>(p);
         f4 x = {0.f, 0.f, 0.f, 0.f};
         if (a >= 0) x = *reinterpret_cast<const f4*>(gT + a * 4);
@@ -902,12 +911,12 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
           u16x4 h;
 #pragma unroll
           for (int k = 0; k < 4; ++k) h[k] = PrecF16::bits(x[k]);
-          gth[gw][p] = h;
-          uint16_t* tk = reinterpret_cast<uint16_t*>(&gtt[gw][0][0]);
+          gth[sub][p] = h;
+          uint16_t* tk = reinterpret_cast<uint16_t*>(&gtt[sub][0][0]);
 #pragma unroll
           for (int k = 0; k < 4; ++k) tk[k * kP3 + p] = h[k];
         } else {
-          gts[gw][p] = x;
+          gts[sub][p] = x;
         }
       }
       if constexpr (GM) __syncthreads();
@@ -915,7 +924,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
     }
     // A operands of the direct-term product, per centre atom: lane (m, g),
     // tile o, element v holds g_T[16o + 4g + v][m % 4]
-    const int nn = A.nnei[i * kMaxT + tj];
+    const int nn = on ? A.nnei[i * kMaxT + tj] : 0;
     const int64_t rbase = (int64_t)i * A.nm + A.sec[tj];
     const double* Rs = A.R + rbase * 4;
     const env_rsrc_t Rb = env_rsrc(Rs, nn);
@@ -990,7 +999,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
         for (int kt = 0; kt < 2; ++kt) z = mfma_h<P, W>(load8<P>(fr + z0 + oF3 + ((o * 2 + kt) * 64 + lane) * 8), b2v[kt], z);
         f4 dGv;
         if constexpr (MC) {
-          dGv = mfma_f16k16(__builtin_bit_cast(h16x4, gth[gw][16 * o + r16]), bR, f4{0.f, 0.f, 0.f, 0.f});
+          dGv = mfma_f16k16(__builtin_bit_cast(h16x4, gth[sub][16 * o + r16]), bR, f4{0.f, 0.f, 0.f, 0.f});
         }
         float G4[4];
 #pragma unroll
@@ -1007,7 +1016,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
             dG = dGv[v];
             G4[v] = G;
           } else {
-            const f4 gt = gts[gw][16 * o + 4 * g + v];
+            const f4 gt = gts[sub][16 * o + 4 * g + v];
             dG = gt[0] * Rrow[0] + gt[1] * Rrow[1] + gt[2] * Rrow[2] + gt[3] * Rrow[3];
 #pragma unroll
             for (int k = 0; k < 4; ++k) dRd[k] = fmaf(gt[k], G, dRd[k]);
@@ -1018,7 +1027,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
         // direct term: A operand lane (m, g), element v = g_T[16 o + 4 g + v][m % 4]
         // (read for every tile: kept in registers for the atom it would take
         // 16 of the 128 registers of four waves per SIMD)
-        if constexpr (MC) accD = mfma_f16k16(__builtin_bit_cast(h16x4, gtt[gw][r16 & 3][4 * o + g + z0]), pack4_f16(G4), accD);
+        if constexpr (MC) accD = mfma_f16k16(__builtin_bit_cast(h16x4, gtt[sub][r16 & 3][4 * o + g + z0]), pack4_f16(G4), accD);
         if (o & 1) bz3[o >> 1] = pack8<P>(dz3p);
       }
       float dz2[4][4], skip1[2][4];
@@ -1082,7 +1091,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
             d4{((double)dRd[0] + (double)dsp) * inv_nm, (double)dRd[1] * inv_nm, (double)dRd[2] * inv_nm,
                (double)dRd[3] * inv_nm};
     }
-    if constexpr (GM) __syncthreads();  // the g_T tile and col_sh are reused by the next column
+    if constexpr (GM) __syncthreads();  // the g_T tile is reused by the next column
   }
 }
 
@@ -1117,6 +1126,7 @@ static EmbArgs emb_args(dp_ctx* c, int32_t mode) {
   for (int t = 0; t <= kMaxT; ++t) A.sec[t] = t <= m->desc.ntypes ? m->sec[t] : m->nm;
   A.inv_nm = 1.0 / (double)m->nm;
   A.ctr = c->emb_ctr;
+  A.kind = 0;
   return A;
 }
 
@@ -1137,6 +1147,15 @@ static dim3 emb_grid(dp_ctx* c, int wpb, int per_cu, int ntypes, bool flat) {
   }
   const int64_t need = (c->natoms_last + wpb - 1) / wpb;
   return dim3((unsigned)(need < res ? need : res), (unsigned)nnets);
+}
+
+// Group mode: one grid row shared out among the nets by their rounds, the
+// work-groups resident at once, fewer when that leaves them less than `least`
+// columns each.
+static dim3 group_grid(dp_ctx* c, int per_cu, int least, int ntypes) {
+  const int64_t g = (c->natoms_last * ntypes + least - 1) / least, res = (int64_t)c->ncu * per_cu;
+  const int64_t n = g < res ? g : res, nnets = ntypes * ntypes;
+  return dim3((unsigned)(n > nnets ? n : nnets), 1);
 }
 
 template <int W, bool ST, bool GM>
@@ -1181,13 +1200,15 @@ static void launch_embed(dp_ctx* c, int32_t mode, bool bwd, hipStream_t s) {
   dim3 grid = emb_grid(c, wpb, per_cu, A.ntypes, flat);
   dim3 block(64 * wpb);
   if (mode == DP_FP64) {
-    // group mode when the columns (one per atom and neighbour section) are
-    // fewer than the chip's wave slots: about one work-group per CU in all,
-    // each taking whole columns with all its waves
-    const bool gm = c->natoms_last * A.ntypes < (int64_t)c->ncu * wpb;
-    if (gm) {  // row y: the y-th heaviest net
-      const int64_t per = c->ncu / nnets > 0 ? c->ncu / nnets : 1;
-      grid = dim3((unsigned)(c->natoms_last < per ? c->natoms_last : per), (unsigned)nnets);
+    // group mode for few columns (one per atom and neighbour section): below
+    // eight per CU, the chip's wave slots, where sections are long (copper,
+    // forward at 1,372 columns 187 us against 221 without, at 2,048 255
+    // against 244), below five where they have a few tiles (water, 900
+    // columns 42 against 59, 1,800 87 against 68)
+    const bool gm = c->natoms_last * A.ntypes < (int64_t)c->ncu * (c->model->tpa > 8 * A.ntypes ? 8 : 5);
+    if (gm) {
+      grid = group_grid(c, 1, 1, A.ntypes);
+      A.kind = 1;
       if (A.act) launch_embed_f64<W, true, true>(bwd, grid, block, A, s);
       else launch_embed_f64<W, false, true>(bwd, grid, block, A, s);
     } else {
@@ -1195,9 +1216,16 @@ static void launch_embed(dp_ctx* c, int32_t mode, bool bwd, hipStream_t s) {
       else launch_embed_f64<W, false, false>(bwd, grid, block, A, s);
     }
   } else {
-    // group mode on the same rule as FP64 (columns fewer than wave slots)
+    // group mode while the columns are fewer than the chip's wave slots
+    // (16-bit work-groups are small: an empty group costs less than another
+    // work-group's copy of the weights; 64 water molecules, backward: BF16
+    // 10.5 us with two columns in each against 12.2, FP32 29 with four
+    // against 20)
     const bool gm = c->natoms_last * A.ntypes < (int64_t)c->ncu * wpb * per_cu;
-    if (gm) {  // row y: the y-th heaviest net
+    if (gm && bwd) {
+      grid = group_grid(c, per_cu, kind == 3 ? 1 : 2, A.ntypes);
+      A.kind = 1;
+    } else if (gm) {  // row y: the y-th heaviest net
       const int64_t per = (int64_t)c->ncu * per_cu / nnets > 0 ? (int64_t)c->ncu * per_cu / nnets : 1;
       grid = dim3((unsigned)(c->natoms_last < per ? c->natoms_last : per), (unsigned)nnets);
     }

@@ -727,12 +727,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   __shared__ double tb[GW][16 * kTS];
   __shared__ d4 gts[GW][M1];
   int grp = 0, ngrp = 1;
-  const int net = net_of_group(A.meta, A.sec, A.ntypes, gridDim.x, blockIdx.x, &grp, &ngrp);
+  const int net = net_of_group(A.meta, A.ntypes, gridDim.x, blockIdx.x, &grp, &ngrp, 0);
   double* pr = A.part + (int64_t)blockIdx.x * kGrRec;
   if (net < 0) return;
   const int ti = net / A.ntypes, tj = net - ti * A.ntypes;
   const int n_t = A.meta[2 * ti], cb = A.meta[2 * ti + 1];
-  const int c_lo = (int)((int64_t)n_t * grp / ngrp), c_hi = (int)((int64_t)n_t * (grp + 1) / ngrp);
+  const int c_lo = part_start(n_t, grp, ngrp), c_hi = part_start(n_t, grp + 1, ngrp);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, g = lane >> 4;
   int* const next_col = A.ctr + blockIdx.x * 32;
@@ -1146,8 +1146,13 @@ __global__ __launch_bounds__(256) void k_egrad25_reduce(EGradArgs A, int G) {
   constexpr int W = 25;
   __shared__ double red[4][64];
   const int net = blockIdx.y, k = blockIdx.x * 64 + (threadIdx.x & 63), q4 = threadIdx.x >> 6;
-  int lo, hi;
-  net_share(A.meta, A.sec, A.ntypes, G, net, &lo, &hi);
+  const NetShares* S = net_shares(A.meta);
+  int lo = 0, hi = 0;
+  for (int r = 0; r < A.ntypes * A.ntypes; ++r)
+    if (S->net[0][r] == net) {
+      lo = share_start(S, 0, A.ntypes * A.ntypes, G, r);
+      hi = share_start(S, 0, A.ntypes * A.ntypes, G, r + 1);
+    }
   constexpr int nW3 = 50 * 100, nW2 = 25 * 50, total = nW3 + 100 + nW2 + 50 + 2 * W;
   auto c2 = [](int f) { return L25::col2(slot2d_of_feat<W>(f)); };
   int64_t dst = -1;

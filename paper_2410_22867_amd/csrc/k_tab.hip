@@ -200,12 +200,12 @@ __device__ __forceinline__ void tab_stage(const double* __restrict__ tabnet, int
 
 #define DPSE_TAB_PROLOGUE                                                  \
   int grp = 0, ngrp = 1;                                                  \
-  const int net = net_of_group(A.meta, A.sec, A.ntypes, gridDim.x, blockIdx.x, &grp, &ngrp); \
+  const int net = net_of_group(A.meta, A.ntypes, gridDim.x, blockIdx.x, &grp, &ngrp, 0); \
   if (net < 0) return;                                                    \
   const int ti = net / A.ntypes, tj = net - ti * A.ntypes;                \
   const int n_t = A.meta[2 * ti], cb = A.meta[2 * ti + 1];                \
-  const int c_lo = (int)((int64_t)n_t * grp / ngrp);                      \
-  const int c_hi = (int)((int64_t)n_t * (grp + 1) / ngrp);                \
+  const int c_lo = part_start(n_t, grp, ngrp);                            \
+  const int c_hi = part_start(n_t, grp + 1, ngrp);                        \
   if (c_lo >= c_hi) return;                                               \
   const int lane = threadIdx.x & 63;                                      \
   int* const next_col = A.ctr + blockIdx.x * 32;                          \
