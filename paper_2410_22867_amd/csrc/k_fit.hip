@@ -21,6 +21,20 @@ namespace dpse {
 
 enum { EPI_TANH = 0, EPI_PLAIN = 1 };
 
+// Whether the hidden layers 2 and 3 run one per launch (k_fit_layer_*)
+// instead of as pairs (k_fit_pair_*).  Both pair launches against all four
+// layer launches, water, fw = 240 (us):
+//   atoms            192          900          1,500        2,100
+//   FP64             49 -> 23     50 -> 44     51 -> 50     55 -> 65
+//   16-bit           26 -> 22     29 -> 29     29 -> 30     30 -> 49
+//   FP32             46 -> 28     46 -> 38     46 -> 39     47 -> 49
+// (the pairs' time hardly depends on the atoms until every CU has a
+// work-group, the layers' is their products and a launch each).
+static bool fit_by_layer(const dp_ctx* c, int32_t mode) {
+  const int kind = mode == DP_FP64 ? 0 : mix_kinds(mode).fit23;
+  return c->natoms_last <= (kind == 0 ? 1280 : kind == 3 ? 1792 : 640);
+}
+
 struct GemmArgs {
   const void* Afr;       // fragments of this layer for type 0
   int64_t a_type_stride; // elements between types
@@ -44,20 +58,58 @@ struct GemmArgs {
   void* part;
   int nsplit;
   int64_t part_cols;
+  // FP64, frames of few atoms: a one-dimensional grid over (weight slice,
+  // column tile) that keeps a slice's column tiles on one XCD (work-group b
+  // runs on XCD b % 8); xtiles: column tiles, yblocks: work-group rows per type
+  int xtiles, yblocks, ntypes;
 };
 
 // ---------------------------------------------------------------- FP64 GEMM
+// The 4 x 4 transpose across the four lane groups of a product's result: element
+// v of group g (row 4 v + g) becomes element g of group v, so that a lane
+// holds rows 4 g .. 4 g + 3 and its column's 16 rows are written as one
+// 128-byte line instead of four quarters of it.
+__device__ __forceinline__ void swap_rows32(double& a, double& b) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+  b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ void swap_rows16(double& a, double& b) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+  b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ d4 rows_of_lane(d4 a) {
+  double a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3];
+  swap_rows32(a0, a2);
+  swap_rows32(a1, a3);
+  swap_rows16(a0, a1);
+  swap_rows16(a2, a3);
+  return d4{a0, a1, a2, a3};
+}
+
 template <int MT, int NT, bool XT, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_fit_gemm_f64(GemmArgs g) {
-  const int t = blockIdx.z;
+  int bx = blockIdx.x, by = blockIdx.y, t = blockIdx.z;
+  if (g.xtiles) {
+    const int j = blockIdx.x >> 3, w = (j / g.xtiles) * 8 + (blockIdx.x & 7);
+    bx = j % g.xtiles;
+    t = w / g.yblocks;
+    by = w - t * g.yblocks;
+    if (t >= g.ntypes) return;
+  }
   const int n_t = g.meta[2 * t], cb = g.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
-  const int c0 = (blockIdx.x * 4 + wv) * NT * 16;
+  const int c0 = (bx * 4 + wv) * NT * 16;
   if (c0 >= n_t) return;
   const int mtiles = g.M / 16;
-  const int mb = SPLIT ? (int)blockIdx.y / g.nsplit : (int)blockIdx.y;
-  const int sp = SPLIT ? (int)blockIdx.y - mb * g.nsplit : 0;
+  const int mb = SPLIT ? by / g.nsplit : by;
+  const int sp = SPLIT ? by - mb * g.nsplit : 0;
   const int mt0 = mb * MT;
   const int KS = g.K / 16;
   // k-steps of this work-group: all of them, or one split's range
@@ -87,12 +139,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       for (int v = 0; v < 4; ++v) Tb[nt][v] = *reinterpret_cast<const d4*>(trow[nt] + (4 * gq + v) * 4);
     }
   }
-  // Operands of k-step S + 1 are requested before the products of step S
-  // issue: two register buffers used alternately (the loop is unrolled by
-  // two, so no copy between them forces an early wait); an odd last step
-  // runs after the loop on the buffer the loop filled last.
-  d4 xA[NT], xB[NT];
-  double aA[MT][4], aB[MT][4];
+  // Operands are requested R - 1 k-steps before the products that use them,
+  // through a ring of R register buffers (no copy between buffers, which would
+  // force an early wait).  Two buffers where two waves per SIMD cover a step's
+  // latency between them (three or four measured no faster at 12,288 columns);
+  // three in the split form, whose waves are often alone.
+  constexpr int R = SPLIT ? 3 : 2;
+  d4 xr[R][NT];
+  double ar[R][MT][4];
   auto load = [&](int S, d4* xv, double (*av)[4]) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
@@ -125,19 +179,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma_f64(av[mt][v], xb[nt][v], acc[mt][nt]);
   };
   // (scheduling barriers keep each phase's loads ahead of the products)
-  load(S0, xA, aA);
+#pragma unroll
+  for (int d = 0; d < R - 1; ++d) load(min(S0 + d, S1 - 1), xr[d], ar[d]);
   int S = S0;
-  for (; S + 1 < S1; S += 2) {
-    load(S + 1, xB, aB);
-    __builtin_amdgcn_sched_barrier(0);
-    step(xA, aA);
-    __builtin_amdgcn_sched_barrier(0);
-    load(S + 2 < S1 ? S + 2 : S1 - 1, xA, aA);
-    __builtin_amdgcn_sched_barrier(0);
-    step(xB, aB);
-    __builtin_amdgcn_sched_barrier(0);
+  for (; S + R <= S1; S += R) {
+#pragma unroll
+    for (int d = 0; d < R; ++d) {
+      load(min(S + d + R - 1, S1 - 1), xr[(d + R - 1) % R], ar[(d + R - 1) % R]);
+      __builtin_amdgcn_sched_barrier(0);
+      step(xr[d], ar[d]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
-  if (S < S1) step(xA, aA);
+#pragma unroll
+  for (int d = 0; d < R - 1; ++d)
+    if (S + d < S1) step(xr[d], ar[d]);
   if constexpr (SPLIT) {
     double* part = static_cast<double*>(g.part) + (int64_t)sp * g.part_cols * g.M;
 #pragma unroll
@@ -146,30 +202,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         const int64_t col = cb + c0 + nt * 16 + r16;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) part[col * g.M + (mt0 + mt) * 16 + gq + 4 * v] = acc[mt][nt][v];
+        *reinterpret_cast<d4*>(part + col * g.M + (mt0 + mt) * 16 + 4 * gq) = rows_of_lane(acc[mt][nt]);
       }
     }
     return;
   }
   const double* vec = reinterpret_cast<const double*>(g.vec) + t * g.vec_type_stride;
-  // D layout of the f64 MFMA: element v of lane n + 16g is row m = 16 mt + g + 4v.
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     if (mt0 + mt >= mtiles) break;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int64_t col = cb + c0 + nt * 16 + r16;
-      const d4 a = acc[mt][nt];
+      const int m0 = (mt0 + mt) * 16 + 4 * gq;
+      d4 a = rows_of_lane(acc[mt][nt]);
+      if (g.epi != EPI_PLAIN) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int m = (mt0 + mt) * 16 + gq + 4 * v;
-        if (g.epi == EPI_PLAIN) {
-          reinterpret_cast<double*>(g.out0)[col * g.ld0 + m] = a[v];
-        } else {
-          reinterpret_cast<double*>(g.out0)[col * g.ld0 + m] = tanh_d(a[v] + vec[g.bias_off + m]);
-        }
+        for (int v = 0; v < 4; ++v) a[v] = tanh_d(a[v] + vec[g.bias_off + m0 + v]);
       }
+      *reinterpret_cast<d4*>(reinterpret_cast<double*>(g.out0) + col * g.ld0 + m0) = a;
     }
   }
 }
@@ -196,6 +247,11 @@ struct PairArgs {
   double* out[4];          // forward: t2, h2, h3, dz3; backward: dz2, dz1
   double* Ei_col;
   double* Ei_atom;
+  // one layer per launch (frames of few atoms): dh2 between the backward's
+  // launches, E_i summed by m-tile ([m-tile][ecols]) between forward and backward
+  void* dh2;
+  double* epart;
+  int64_t ecols;
 };
 
 template <bool BWD, int NCT, int NW>
@@ -365,6 +421,92 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
   }
 }
 
+// The same layers one per launch, for frames of few atoms: a 16-column
+// work-group of the pair kernels walks 2 x 15 m-tiles (29,000 cycles of
+// products on one CU, and 0.9 MB of weights through it) however few columns
+// there are.  Here a work-group owns one m-tile of one column tile and its
+// four waves share the reduction, with every operand requested before the
+// first product.  E_i is left as one partial sum per m-tile, added by the
+// backward's first launch.
+template <bool BWD, bool SECOND>
+__global__ __launch_bounds__(256) void k_fit_layer_f64(PairArgs p) {
+  constexpr int KW = 4;  // k-steps of 16 per wave (fw <= 256)
+  __shared__ d4 red[4][64];
+  __shared__ double es[4][16];
+  const int t = blockIdx.z;
+  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int c0 = blockIdx.x * 16;
+  if (c0 >= n_t) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int r16 = lane & 15, gq = lane >> 4;
+  const int fw = p.fw, KS = fw / 16, mt = blockIdx.y;
+  const double* vec = p.vec + t * p.vec_type_stride;
+  const double* A = p.A[SECOND ? 1 : 0] + t * p.a_type_stride;
+  const double* in = SECOND ? p.out[BWD ? 0 : 1] : p.in;
+  const int64_t col = (int64_t)cb + c0 + r16;
+  const int S0 = KS * wv / 4, S1 = KS * (wv + 1) / 4;
+  d4 a[KW], x[KW];
+#pragma unroll
+  for (int d = 0; d < KW; ++d) {
+    const int S = min(S0 + d, KS - 1);
+    a[d] = *reinterpret_cast<const d4*>(A + (((int64_t)mt * KS + S) * 64 + lane) * 4);
+    x[d] = *reinterpret_cast<const d4*>(in + col * fw + 16 * S + 4 * gq);
+  }
+  // the epilogue's operand: element v = wave of the result, feature m
+  const int m = 16 * mt + 4 * wv + gq;
+  const double prev = BWD ? p.tprev[SECOND ? 1 : 0][col * fw + m] : in[col * fw + m];  // tanh below, or the skip
+  const double add = BWD ? (SECOND ? static_cast<const double*>(p.dh2)[col * fw + m] : vec[3 * fw + m])
+                         : vec[(SECOND ? 2 : 1) * fw + m];
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int d = 0; d < KW; ++d)
+    if (S0 + d < S1) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc = mfma_f64(a[d][v], x[d][v], acc);
+    }
+  red[wv][lane] = acc;
+  if constexpr (BWD && !SECOND) {
+    // E_i of the forward, one work-group per column tile
+    if (mt == 0 && wv == 0 && lane < 16) {
+      double q[16], e = vec[4 * fw] + vec[4 * fw + 1];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) q[k] = p.epart[min(k, KS - 1) * p.ecols + col];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) e += k < KS ? q[k] : 0.0;
+      const int i = p.atom_at[col];
+      if (i >= 0) {
+        p.Ei_col[col] = e;
+        p.Ei_atom[i] = e;
+      }
+    }
+  }
+  __syncthreads();
+  double z = add;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) z += red[w][lane][wv];
+  if constexpr (!BWD) {
+    const double tv = tanh_d(z), h = prev + tv;
+    if constexpr (!SECOND) {
+      p.out[0][col * fw + m] = tv;
+      p.out[1][col * fw + m] = h;
+    } else {
+      if (p.out[2]) p.out[2][col * fw + m] = h;
+      const double wo = vec[3 * fw + m];
+      p.out[3][col * fw + m] = wo * (1.0 - tv * tv);
+      double e = h * wo;
+      e += shfl_xor_d(e, 16);
+      e += shfl_xor_d(e, 32);
+      if (gq == 0) es[wv][r16] = e;
+      __syncthreads();
+      if (threadIdx.x < 16)
+        p.epart[mt * p.ecols + col] = (es[0][r16] + es[1][r16]) + (es[2][r16] + es[3][r16]);
+    }
+  } else {
+    if constexpr (!SECOND) static_cast<double*>(p.dh2)[col * fw + m] = z;
+    p.out[SECOND ? 1 : 0][col * fw + m] = z * (1.0 - prev * prev);
+  }
+}
+
 // One 16-column tile per work-group and four waves of four m-tile slots
 // (32 columns, or eight waves of two slots, measured no faster).  Frames
 // too small to give every CU a work-group (few atoms) take sixteen waves of
@@ -382,6 +524,17 @@ static void launch_pair_f64_t(dp_ctx* c, bool bwd, const PairArgs& p, hipStream_
 
 static void launch_pair_f64(dp_ctx* c, bool bwd, const PairArgs& p, hipStream_t s) {
   const int64_t wgs = (c->natoms_last + 15) / 16 + c->model->desc.ntypes - 1;
+  if (fit_by_layer(c, DP_FP64)) {
+    const dim3 grid((unsigned)((c->natoms_last + 15) / 16), (unsigned)(p.fw / 16), (unsigned)c->model->desc.ntypes);
+    if (bwd) {
+      hipLaunchKernelGGL((k_fit_layer_f64<true, false>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((k_fit_layer_f64<true, true>), grid, dim3(256), 0, s, p);
+    } else {
+      hipLaunchKernelGGL((k_fit_layer_f64<false, false>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((k_fit_layer_f64<false, true>), grid, dim3(256), 0, s, p);
+    }
+    return;
+  }
   if (wgs < c->ncu) launch_pair_f64_t<16>(c, bwd, p, s);
   else launch_pair_f64_t<4>(c, bwd, p, s);
 }
@@ -580,6 +733,9 @@ struct PairArgsLp {
   void* outlp[2];          // forward: dz3; backward: dz2 (element type of P), dz1 (of PO)
   double* Ei_col;
   double* Ei_atom;
+  void* dh2;               // one layer per launch: as in PairArgs
+  double* epart;
+  int64_t ecols;
 };
 
 // PO: element type of dz1, the X operand of the first layer's backward GEMM
@@ -774,6 +930,116 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
   }
 }
 
+// The mixed layers one per launch (as k_fit_layer_f64): wave w of a work-group
+// owns m-tile 4 blockIdx.y + w of a column tile over the whole reduction, in
+// the pair kernel's order of products, so its results are the same bits.
+template <class P, class PO, bool BWD, bool SECOND>
+__global__ __launch_bounds__(256) void k_fit_layer_lp(PairArgsLp p) {
+  constexpr int KM = 8;  // 32-wide k-steps (fw <= 256)
+  typedef typename P::store_t ST;
+  typedef typename P::raw8 R8;
+  typedef typename P::raw4 R4;
+  const int t = blockIdx.z;
+  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int c0 = blockIdx.x * 16;
+  const int lane = threadIdx.x & 63, r16 = lane & 15, gq = lane >> 4;
+  const int fw = p.fw, fwp = p.fwp, KT = fwp / 32;
+  const int mt = blockIdx.y * 4 + (threadIdx.x >> 6);
+  if (c0 >= n_t || mt >= fw / 16) return;
+  const float* vec = p.vec + t * p.vec_type_stride;
+  const ST* A = reinterpret_cast<const ST*>(p.A[SECOND ? 1 : 0]) + t * p.a_type_stride;
+  const int64_t col = (int64_t)cb + c0 + r16;
+  const void* in = SECOND ? (BWD ? (const void*)p.outlp[0] : (const void*)p.out[1]) : p.in;
+  R8 a[KM], x[KM];
+#pragma unroll
+  for (int kt = 0; kt < KM; ++kt) {
+    const int k = min(kt, KT - 1);
+    a[kt] = *reinterpret_cast<const R8*>(A + (((int64_t)mt * KT + k) * 64 + lane) * 8);
+    const bool top = 32 * k + 16 < fw;  // the upper half holds features
+    if constexpr (BWD) {
+      const ST* rowp = static_cast<const ST*>(in) + col * fwp + 32 * k + 4 * gq;
+      const R4 lo = *reinterpret_cast<const R4*>(rowp);
+      R4 hi = *reinterpret_cast<const R4*>(rowp + 16);
+      if (!top) hi = R4{};
+      x[kt] = join8<P>(lo, hi);
+    } else {
+      const float* rowp = static_cast<const float*>(in) + col * fwp + 32 * k + 4 * gq;
+      const f4 lo = *reinterpret_cast<const f4*>(rowp);
+      f4 hi = *reinterpret_cast<const f4*>(rowp + 16);
+      if (!top) hi = f4{0.f, 0.f, 0.f, 0.f};
+      const float v8[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      x[kt] = __builtin_bit_cast(R8, pack8<P>(v8));
+    }
+  }
+  const int m0 = 16 * mt + 4 * gq;
+  // forward: the skip; backward: the tanh below
+  const f4 prev = *reinterpret_cast<const f4*>(
+      BWD ? p.tprev[SECOND ? 1 : 0] + col * fwp + m0 : static_cast<const float*>(in) + col * fwp + m0);
+  f4 acc;
+  if constexpr (BWD && SECOND) {
+    acc = *reinterpret_cast<const f4*>(static_cast<const float*>(p.dh2) + col * fwp + m0);
+  } else {
+    const int off = BWD ? 3 * fw : (SECOND ? 2 : 1) * fw;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = vec[off + m0 + v];
+  }
+  if constexpr (BWD && !SECOND) {
+    if (mt == 0 && lane < 16) {
+      double q[16], e = 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) q[k] = p.epart[min(k, fw / 16 - 1) * p.ecols + col];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) e += k < fw / 16 ? q[k] : 0.0;
+      const int i = p.atom_at[col];
+      if (i >= 0) {
+        const double E = e + (double)vec[4 * fw] + (double)vec[4 * fw + 1];
+        p.Ei_col[col] = E;
+        p.Ei_atom[i] = E;
+      }
+    }
+  }
+#pragma unroll
+  for (int kt = 0; kt < KM; ++kt)
+    if (kt < KT)
+      acc = P::mfma(__builtin_bit_cast(typename P::vec8, a[kt]), __builtin_bit_cast(typename P::vec8, x[kt]), acc);
+  if constexpr (!BWD) {
+    float tv[4], hv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      tv[v] = tanh_f(acc[v]);
+      hv[v] = prev[v] + tv[v];
+    }
+    if constexpr (!SECOND) {
+      *reinterpret_cast<f4*>(p.out[0] + col * fwp + m0) = f4{tv[0], tv[1], tv[2], tv[3]};
+      *reinterpret_cast<f4*>(p.out[1] + col * fwp + m0) = f4{hv[0], hv[1], hv[2], hv[3]};
+    } else {
+      if (p.out[2]) *reinterpret_cast<f4*>(p.out[2] + col * fwp + m0) = f4{hv[0], hv[1], hv[2], hv[3]};
+      float dz[4];
+      double e = 0.0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float wo = vec[3 * fw + m0 + v];
+        dz[v] = wo * (1.f - tv[v] * tv[v]);
+        e += (double)(hv[v] * wo);
+      }
+      store4<P>(reinterpret_cast<ST*>(p.outlp[0]) + col * fwp + m0, dz);
+      e += shfl_xor_d(e, 16);
+      e += shfl_xor_d(e, 32);
+      if (gq == 0) p.epart[mt * p.ecols + col] = e;
+    }
+  } else {
+    float dz[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) dz[v] = acc[v] * (1.f - prev[v] * prev[v]);
+    if constexpr (!SECOND) {
+      *reinterpret_cast<f4*>(static_cast<float*>(p.dh2) + col * fwp + m0) = acc;
+      store4<P>(reinterpret_cast<ST*>(p.outlp[0]) + col * fwp + m0, dz);
+    } else {
+      store4<PO>(reinterpret_cast<typename PO::store_t*>(p.outlp[1]) + col * fwp + m0, dz);
+    }
+  }
+}
+
 // Column tiles per work-group of the half-precision layer pairs (each
 // weight fragment a wave loads serves that many products): one, measured
 // faster than two or four (water12k BF16 forward 57 / 62 / 82 us) — the
@@ -781,7 +1047,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
 constexpr int kPairNCT = 1;
 
 template <class P, class PO>
-static void launch_pair_lp_t(bool bwd, dim3 grid, size_t lds, const PairArgsLp& p, hipStream_t s) {
+static void launch_pair_lp_t(bool bwd, dim3 grid, size_t lds, const PairArgsLp& p, bool by_layer, hipStream_t s) {
+  if (by_layer) {
+    grid.y = (unsigned)((p.fw / 16 + 3) / 4);
+    if (bwd) {
+      hipLaunchKernelGGL((k_fit_layer_lp<P, PO, true, false>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((k_fit_layer_lp<P, PO, true, true>), grid, dim3(256), 0, s, p);
+    } else {
+      hipLaunchKernelGGL((k_fit_layer_lp<P, P, false, false>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((k_fit_layer_lp<P, P, false, true>), grid, dim3(256), 0, s, p);
+    }
+    return;
+  }
   if (bwd) hipLaunchKernelGGL((k_fit_pair_lp<P, PO, true, kPairNCT>), grid, dim3(256), lds, s, p);
   else hipLaunchKernelGGL((k_fit_pair_lp<P, P, false, kPairNCT>), grid, dim3(256), lds, s, p);
 }
@@ -794,10 +1071,10 @@ static void launch_pair_lp(dp_ctx* c, bool bwd, int mode, const PairArgsLp& p, h
   const size_t esz = mk.fit23 == 3 ? 4 : 2;
   const size_t lds = bwd ? (size_t)NC * (p.fwp + 8) * esz : (size_t)NC * (p.fwp + 4) * 4;
   if (grid.x == 0) return;
-  if (mk.fit23 == 1) launch_pair_lp_t<PrecBF16, PrecBF16>(bwd, grid, lds, p, s);
-  else if (mk.fit23 == 2) launch_pair_lp_t<PrecF16, PrecF16>(bwd, grid, lds, p, s);
-  else if (mk.fit1 == 2) launch_pair_lp_t<PrecF32, PrecF16>(bwd, grid, lds, p, s);
-  else launch_pair_lp_t<PrecF32, PrecF32>(bwd, grid, lds, p, s);
+  if (mk.fit23 == 1) launch_pair_lp_t<PrecBF16, PrecBF16>(bwd, grid, lds, p, fit_by_layer(c, mode), s);
+  else if (mk.fit23 == 2) launch_pair_lp_t<PrecF16, PrecF16>(bwd, grid, lds, p, fit_by_layer(c, mode), s);
+  else if (mk.fit1 == 2) launch_pair_lp_t<PrecF32, PrecF16>(bwd, grid, lds, p, fit_by_layer(c, mode), s);
+  else launch_pair_lp_t<PrecF32, PrecF32>(bwd, grid, lds, p, fit_by_layer(c, mode), s);
 }
 
 // ---------------------------------------------------------------- fused first fitting layer
@@ -1223,8 +1500,8 @@ static const void* elem_offset(const void* base, int kind, int64_t off) {
 //   FP64 : 0 t1(=h1) 1 t2 2 h2 4 h3 5 dz3 7 dz2 8 dz1 [cols][fw]
 //   mixed: 0 t1 1 t2 2 h2 4 h3 (f32 [cols][fwp]); 7 dz3 8 dz2 9 dz1 (half
 //          [cols][fwp])
-// The other slots are free; the parameter gradients after a mixed compute
-// use them for FP64 copies.
+// Hidden layers one per launch: 3 the partial sums of E_i (f64 [fw / 16][cols]),
+// 6 dh2 (f64, or f32).  The other slots are free.
 // Tile shapes (m-tiles x n-tiles per wave, 4 waves along the columns).
 // Small-M form (the paper's concern with GEMMs of few rows, here few atoms
 // per type): when the unsplit grid would leave most of the chip idle and the
@@ -1255,6 +1532,22 @@ static void split_finish(dp_ctx* c, const GemmArgs& g, hipStream_t s) {
   if (work > 0) hipLaunchKernelGGL((k_split_finish<T>), grid, dim3(256), 0, s, g);
 }
 
+// FP64: as many splits as leave two work-groups per CU in all (the 16-bit
+// rule's 2,048 columns and fixed counts left half the chip idle at 2,100 to
+// 6,000 atoms), within the workspace (kSplitMax sums of split_cols columns, or
+// fewer sums of more).  Forward product, sums added (us): 192 water atoms
+// 21.5 -> 20.5, 900 52 -> 49, 2,100 92 -> 52, 3,333 169 -> 78, 6,000
+// 173 -> 112, 12,288 (unsplit) 181 -> 179.
+static int split_count_f64(const dp_ctx* c, int64_t wgs_unsplit, int ksteps) {
+  const int64_t cols = c->natoms_last + (int64_t)c->model->desc.ntypes * kColPad;
+  if (wgs_unsplit <= 0) return 1;
+  int64_t ns = 2 * (int64_t)c->ncu / wgs_unsplit;
+  if (ns > kSplitMax) ns = kSplitMax;
+  if (ns > ksteps / 8) ns = ksteps / 8;
+  if (ns > kSplitMax * c->split_cols / cols) ns = kSplitMax * c->split_cols / cols;
+  return ns >= 2 ? (int)ns : 1;
+}
+
 template <int MT, int NT>
 static void gemm_launch_f64(dp_ctx* c, const GemmArgs& g0, hipStream_t s) {
   const int ntypes = c->model->desc.ntypes;
@@ -1264,11 +1557,23 @@ static void gemm_launch_f64(dp_ctx* c, const GemmArgs& g0, hipStream_t s) {
   dim3 grid((unsigned)((c->natoms_last + BN - 1) / BN), (unsigned)mblocks, (unsigned)ntypes);
   if (grid.x == 0) return;
   GemmArgs g = g0;
-  g.nsplit = split_count(c, unsplit_wgs(c, BN, mblocks), g.K / 16);
+  // (the partial sums' workspace is as wide as the fitting layers: the backward
+  // product, which is wider, is never split)
+  g.nsplit = g.T ? split_count_f64(c, unsplit_wgs(c, BN, mblocks), g.K / 16) : 1;
+  if (g.nsplit > 1) grid.y = (unsigned)(mblocks * g.nsplit);
+  // Few column tiles: each XCD's L2 reads its share of the weights (3 MB a
+  // type) instead of all of them, and all columns' inputs.  Both first-layer
+  // products of 900 water atoms 93 -> 81 us, 450 atoms 61 -> 59, 1,500 and
+  // 2,100 unchanged; with more columns their inputs are the larger part.
+  if (c->natoms_last <= 1280) {
+    g.xtiles = (int)grid.x;
+    g.yblocks = (int)grid.y;
+    g.ntypes = ntypes;
+    grid = dim3((unsigned)(((g.yblocks * ntypes + 7) / 8) * 8 * g.xtiles));
+  }
   if (g.nsplit > 1) {
     g.part = c->split_part;
-    g.part_cols = c->split_cols;
-    grid.y = (unsigned)(mblocks * g.nsplit);
+    g.part_cols = c->natoms_last + (int64_t)ntypes * kColPad;
     if (g.T) hipLaunchKernelGGL((k_fit_gemm_f64<MT, NT, true, true>), grid, dim3(256), 0, s, g);
     else hipLaunchKernelGGL((k_fit_gemm_f64<MT, NT, false, true>), grid, dim3(256), 0, s, g);
     split_finish<double>(c, g, s);
@@ -1321,6 +1626,9 @@ static void gemm_launch_lp(dp_ctx* c, const GemmArgs& g0, int kind, hipStream_t 
 // 2x2 per wave (64 x 64 per work-group).
 static void gemm_launch(dp_ctx* c, const GemmArgs& g, int mode, hipStream_t s) {
   if (mode != DP_FP64) gemm_launch_lp<2, 2>(c, g, mix_kinds(mode).fit1, s);
+  // backward product (never split): 16-feature rows while the 48-feature grid
+  // leaves CUs idle, 192 water atoms 17.1 -> 15.0 us, 900 46 -> 40
+  else if (!g.T && unsplit_wgs(c, 128, (g.M / 16 + 2) / 3) < c->ncu) gemm_launch_f64<1, 2>(c, g, s);
   else gemm_launch_f64<3, 2>(c, g, s);
 }
 
@@ -1473,7 +1781,9 @@ void launch_fit_forward(dp_ctx* c, int32_t mode, bool keep_h, hipStream_t s) {
     p.vec = m->fit_vec64;
     p.vec_type_stride = m->fit_vec_per_type;
     p.out[0] = (double*)c->fa[1];
-    p.out[1] = keep_h ? (double*)c->fa[2] : nullptr;
+    p.out[1] = keep_h || fit_by_layer(c, mode) ? (double*)c->fa[2] : nullptr;
+    p.epart = (double*)c->fa[3];
+    p.ecols = c->max_cols;
     p.out[2] = keep_h ? (double*)c->fa[4] : nullptr;
     p.out[3] = (double*)c->fa[5];
     p.Ei_col = c->Ei_col;
@@ -1492,7 +1802,9 @@ void launch_fit_forward(dp_ctx* c, int32_t mode, bool keep_h, hipStream_t s) {
     p.vec = m->fit_vec32;
     p.vec_type_stride = m->fit_vec_per_type;
     p.out[0] = (float*)c->fa[1];
-    p.out[1] = keep_h ? (float*)c->fa[2] : nullptr;
+    p.out[1] = keep_h || fit_by_layer(c, mode) ? (float*)c->fa[2] : nullptr;
+    p.epart = (double*)c->fa[3];
+    p.ecols = c->max_cols;
     p.out[2] = keep_h ? (float*)c->fa[4] : nullptr;
     p.outlp[0] = c->fa[7];
     p.Ei_col = c->Ei_col;
@@ -1527,8 +1839,14 @@ void launch_fit_backward(dp_ctx* c, int32_t mode, bool keep_dz2, hipStream_t s) 
     p.vec_type_stride = m->fit_vec_per_type;
     p.tprev[0] = (const double*)c->fa[1];
     p.tprev[1] = (const double*)c->fa[0];
-    p.out[0] = keep_dz2 ? (double*)c->fa[7] : nullptr;
+    p.out[0] = keep_dz2 || fit_by_layer(c, mode) ? (double*)c->fa[7] : nullptr;
     p.out[1] = (double*)c->fa[8];
+    p.dh2 = c->fa[6];
+    p.epart = (double*)c->fa[3];
+    p.ecols = c->max_cols;
+    p.atom_at = c->atom_at;
+    p.Ei_col = c->Ei_col;
+    p.Ei_atom = c->Ei_atom;
     launch_pair_f64(c, true, p, s);
   } else {
     PairArgsLp p = {};
@@ -1543,8 +1861,14 @@ void launch_fit_backward(dp_ctx* c, int32_t mode, bool keep_dz2, hipStream_t s) 
     p.vec_type_stride = m->fit_vec_per_type;
     p.tprev[0] = (const float*)c->fa[1];
     p.tprev[1] = (const float*)c->fa[0];
-    p.outlp[0] = keep_dz2 ? c->fa[8] : nullptr;
+    p.outlp[0] = keep_dz2 || fit_by_layer(c, mode) ? c->fa[8] : nullptr;
     p.outlp[1] = c->fa[9];
+    p.dh2 = c->fa[6];
+    p.epart = (double*)c->fa[3];
+    p.ecols = c->max_cols;
+    p.atom_at = c->atom_at;
+    p.Ei_col = c->Ei_col;
+    p.Ei_atom = c->Ei_atom;
     launch_pair_lp(c, true, mode, p, s);
   }
   // layer 1: dD = W1 dz1

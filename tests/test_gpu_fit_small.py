@@ -1,0 +1,71 @@
+"""Fitting layers one per launch and the split first layer, on each side of
+the atom counts where the route changes (water: 1,280 atoms FP64, 640 in the
+16-bit forms, 1,792 FP32), at the narrowest and widest fitting nets, and with
+one type empty.  Bars: FP64 as for full frames, mixed forms the relative RMS
+force bars of the other nets."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2410_22867_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+REL_F = {"bf16": 2e-2, "mix_fp32": 2e-5, "mix_fp16": 4e-3}
+
+
+def _compute(fr, desc, p, modes):
+    from paper_2410_22867_amd import dpse
+    dev = torch.device("cuda:0")
+    model = dpse.Model(desc, p)
+    ctx = dpse.Context(model, fr.n)
+    x, t = torch.tensor(fr.coords, device=dev), torch.tensor(fr.types, device=dev)
+    nl, _ = ctx.build_nlist(x, t, fr.box)
+    out = {}
+    for m in modes:
+        print("fitting layers", desc.fit, fr.n, m, flush=True)
+        r = ctx.compute(x, t, fr.box, nl, mode=m, want_atom_energy=True)
+        out[m] = {k: v.cpu().numpy().copy() for k, v in r.items() if k in ("E", "F", "Ei")}
+    ctx.close()
+    return out
+
+
+def _check(o, r, mode):
+    if mode == "fp64":
+        assert abs(r["E"][0] - o["E"]) <= 1e-10 * abs(o["E"])
+        assert np.abs(r["F"] - o["F"]).max() <= 1e-9
+        assert np.abs(r["Ei"] - o["Ei"]).max() <= 1e-10 * np.abs(o["Ei"]).max()
+    else:
+        rel = np.sqrt(((r["F"] - o["F"]) ** 2).mean()) / np.sqrt((o["F"] ** 2).mean())
+        assert rel <= REL_F[mode]
+
+
+# the descriptor's nets and the box's density are the water model's
+@pytest.mark.parametrize("mols,fit,modes", [
+    (64, 16, ["fp64", "bf16", "mix_fp32", "mix_fp16"]),
+    (64, 256, ["fp64", "bf16", "mix_fp32", "mix_fp16"]),
+    (213, 240, ["bf16", "mix_fp16"]), (214, 240, ["bf16", "mix_fp16"]),
+    (426, 240, ["fp64"]), (427, 240, ["fp64"]), (427, 256, ["fp64"]),
+    (597, 240, ["mix_fp32"]), (598, 240, ["fp64", "mix_fp32"]),
+])
+def test_fit_routes_match_oracle(mols, fit, modes):
+    desc = dataclasses.replace(I.WATER, fit=(fit,) * 3)
+    p = I.init_params(desc, 100, I.WATER_OUTPUT_SCALE)
+    sites = int(np.ceil(mols ** (1 / 3)))
+    fr = I.water_box(mols, max(I.water_density_box(mols), 2.95 * sites), 41)
+    o = oracle.compute(fr.coords, fr.types, fr.box, desc, p)
+    for m, r in _compute(fr, desc, p, modes).items():
+        _check(o, r, m)
+
+
+def test_fit_by_layer_with_an_empty_type():
+    fr = I.water_box(216, 18.643, 42)
+    keep = fr.types == 1
+    fr = I.Frame(np.ascontiguousarray(fr.coords[keep]), np.ascontiguousarray(fr.types[keep]), fr.box)
+    p = I.init_params(I.WATER, 100, I.WATER_OUTPUT_SCALE)
+    o = oracle.compute(fr.coords, fr.types, fr.box, I.WATER, p)
+    for m, r in _compute(fr, I.WATER, p, ["fp64", "mix_fp32"]).items():
+        _check(o, r, m)
