@@ -389,6 +389,57 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
+// Exchanges of 64-bit values between the halves (rows of 16) of a wavefront:
+// lanes >= 32 (odd rows) of a trade places with lanes < 32 (even rows) of b.
+__device__ __forceinline__ void swap_rows32(double& a, double& b) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+  b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ void swap_rows16(double& a, double& b) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  a = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+  b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+// Sum over the 64 lanes of four values at once: two half-wave swaps fold the
+// four into one register, value q in lane row q (lanes 16 q ..), which a
+// 16-lane tree then sums; every lane of row q returns the sum of x[q].
+__device__ __forceinline__ double swap_add32(double a, double b) {  // lanes < 32: a of both halves, else b
+  swap_rows32(a, b);
+  return a + b;
+}
+__device__ __forceinline__ double swap_add16(double a, double b) {  // even 16-lane rows: a of the row pair, odd: b
+  swap_rows16(a, b);
+  return a + b;
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum4(double x0, double x1, double x2, double x3) {
+  // the 32-lane swap splits {0, 2} and {1, 3}, the 16-lane swap the members
+  double v = swap_add16(swap_add32(x0, x2), swap_add32(x1, x3));
+  v = dpp_add<0xb1>(v);   // quad_perm [1, 0, 3, 2]
+  v = dpp_add<0x4e>(v);   // quad_perm [2, 3, 0, 1]
+  v = dpp_add<0x141>(v);  // row_half_mirror
+  return dpp_add<0x140>(v);  // row_mirror
+}
+
+// Work-group index for passes over atoms in order: work-group b runs on XCD
+// b % 8, so each XCD is given one contiguous range of the atoms and its L2
+// holds their neighbours' rows.  The grid is n rounded up to a multiple of 8.
+__device__ __forceinline__ int xcd_range(int n) {
+  return (int)(blockIdx.x & 7) * ((n + 7) >> 3) + (int)(blockIdx.x >> 3);
+}
+inline unsigned xcd_grid(int64_t n) { return (unsigned)((n + 7) & ~(int64_t)7); }
+
 // Orders the LDS traffic of one wavefront (lanes exchange data through LDS
 // inside a wave-private region without a work-group barrier).
 __device__ __forceinline__ void wave_lds_sync() {

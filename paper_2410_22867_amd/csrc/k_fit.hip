@@ -69,20 +69,6 @@ struct GemmArgs {
 // v of group g (row 4 v + g) becomes element g of group v, so that a lane
 // holds rows 4 g .. 4 g + 3 and its column's 16 rows are written as one
 // 128-byte line instead of four quarters of it.
-__device__ __forceinline__ void swap_rows32(double& a, double& b) {
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-  a = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
-  b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-}
-__device__ __forceinline__ void swap_rows16(double& a, double& b) {
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
-  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-  a = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
-  b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-}
 __device__ __forceinline__ d4 rows_of_lane(d4 a) {
   double a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3];
   swap_rows32(a0, a2);

@@ -328,40 +328,6 @@ __global__ __launch_bounds__(64 * WPB) void k_embed_fwd_tab(TabArgs A) {
   if (__ballot(clipped) && lane == 0) set_flag(A.flags, DP_FLAG_TABLE_RANGE);
 }
 
-// Sum over the 64 lanes of four values at once: two half-wave swaps fold the
-// four into one register, value q in lane row q (lanes 16 q ..), which a
-// 16-lane tree then sums; every lane of row q returns the sum of x[q].
-__device__ __forceinline__ double swap_add32(double a, double b) {  // lanes < 32: a of both halves, else b
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-  return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
-         __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-}
-__device__ __forceinline__ double swap_add16(double a, double b) {  // even 16-lane rows: a of the row pair, odd: b
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
-  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-  return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
-         __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
-  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
-  return v + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-__device__ __forceinline__ double wave_sum4(const double x[4]) {
-  // rows 0, 1, 2, 3 of the result hold x[0], x[1], x[2], x[3]: the 32-lane
-  // swap splits {0, 2} and {1, 3}, the 16-lane swap the members
-  double v = swap_add16(swap_add32(x[0], x[2]), swap_add32(x[1], x[3]));
-  v = dpp_add<0xb1>(v);   // quad_perm [1, 0, 3, 2]
-  v = dpp_add<0x4e>(v);   // quad_perm [2, 3, 0, 1]
-  v = dpp_add<0x141>(v);  // row_half_mirror
-  return dpp_add<0x140>(v);  // row_mirror
-}
-
 // Backward: per row, dE/dG_a = g_T[a] . R~ / nm, the direct term
 // dE/dR~ = sum_a g_T[a] G_a / nm and dE/dx = sum_a dE/dG_a dG_a/dx.
 // Rows of the window: lanes are rows, the features are taken one after
@@ -467,7 +433,7 @@ __global__ __launch_bounds__(64 * WPB) void k_embed_bwd_tab(TabArgs A) {
           dr[2] = fma(gt[u][2], G, dr[2]);
           dr[3] = fma(gt[u][3], G, dr[3]);
         }
-        const double v = wave_sum4(dr);
+        const double v = wave_sum4(dr[0], dr[1], dr[2], dr[3]);
         if ((lane & 15) == 0) A.netd[(rbase + r0 + r) * 4 + (lane >> 4)] = v * A.inv_nm;
       }
     }
