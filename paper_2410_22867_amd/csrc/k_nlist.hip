@@ -457,57 +457,59 @@ __global__ __launch_bounds__(256) void k_nl_skin_build(SearchArgs A, SkinArgs S,
   }
 }
 
-// Position of each candidate's reverse pair (i, -s) in j's candidate list.
-// One wave per atom i (atoms in a grid-stride loop over a grid of the
-// resident capacity, so that a gated launch with nothing to do is cheap);
-// lane l takes candidates l, l + 64, ... of i's list, four at a time, and
-// runs their binary searches in j's sorted candidate list in lockstep (a
-// fixed ten halvings cover the 512-entry capacity), so that four
-// dependent-load chains are in flight per lane instead of one.
-__global__ __launch_bounds__(256) void k_nl_skin_crev(SkinArgs S, int ntot) {
-  if (S.gate && S.gate[0] == 0) return;
-  const int lane = threadIdx.x & 63;
-  for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < ntot; i += gridDim.x * 4) {
-    const int nc = S.ncand[i];
-    const int32_t* ci = S.cand + (int64_t)i * kCandCap;
-    constexpr int M = kCandCap / 64, U = 4;
-    static_assert(kCandCap <= 1024, "ten halvings cover the list");
-    for (int m0 = 0; m0 < M && 64 * m0 < nc; m0 += U) {
-      int lo[U], hi[U], nj[U], tgt[U];
-      const int32_t* cj[U];
+// Position of each of atom i's candidates' reverse pair (i, -s) in j's
+// candidate list, by one wave: lane l takes candidates l, l + 64, ... of i's
+// list, four at a time, and runs their binary searches in j's sorted candidate
+// list in lockstep (a fixed ten halvings cover the 512-entry capacity), so
+// that four dependent-load chains are in flight per lane instead of one.
+__device__ __forceinline__ void crev_row(const SkinArgs& S, int i, int lane) {
+  const int nc = S.ncand[i];
+  const int32_t* ci = S.cand + (int64_t)i * kCandCap;
+  constexpr int M = kCandCap / 64, U = 4;
+  static_assert(kCandCap <= 1024, "ten halvings cover the list");
+#pragma unroll 1
+  for (int m0 = 0; m0 < M && 64 * m0 < nc; m0 += U) {
+    int lo[U], hi[U], nj[U], tgt[U];
+    const int32_t* cj[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = 64 * (m0 + u) + lane;
-        lo[u] = 0;
-        hi[u] = 0;
-        nj[u] = 0;
-        tgt[u] = 0;
-        cj[u] = ci;
-        if (m0 + u < M && k < nc) {
-          const int e = ci[k];
-          const int j = e / 27;
-          tgt[u] = 27 * i + (26 - (e - 27 * j));
-          cj[u] = S.cand + (int64_t)j * kCandCap;
-          nj[u] = S.ncand[j];
-          hi[u] = nj[u];
-        }
-      }
-#pragma unroll
-      for (int it = 0; it < 10; ++it)
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (lo[u] < hi[u]) {
-            const int mid = (lo[u] + hi[u]) >> 1;
-            if (cj[u][mid] < tgt[u]) lo[u] = mid + 1;
-            else hi[u] = mid;
-          }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = 64 * (m0 + u) + lane;
-        if (m0 + u < M && k < nc) S.crev[(int64_t)i * kCandCap + k] = (lo[u] < nj[u] && cj[u][lo[u]] == tgt[u]) ? lo[u] : -1;
+    for (int u = 0; u < U; ++u) {
+      const int k = 64 * (m0 + u) + lane;
+      lo[u] = 0;
+      hi[u] = 0;
+      nj[u] = 0;
+      tgt[u] = 0;
+      cj[u] = ci;
+      if (m0 + u < M && k < nc) {
+        const int e = ci[k];
+        const int j = e / 27;
+        tgt[u] = 27 * i + (26 - (e - 27 * j));
+        cj[u] = S.cand + (int64_t)j * kCandCap;
+        nj[u] = S.ncand[j];
+        hi[u] = nj[u];
       }
     }
+#pragma unroll 1
+    for (int it = 0; it < 10; ++it)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (lo[u] < hi[u]) {
+          const int mid = (lo[u] + hi[u]) >> 1;
+          if (cj[u][mid] < tgt[u]) lo[u] = mid + 1;
+          else hi[u] = mid;
+        }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = 64 * (m0 + u) + lane;
+      if (m0 + u < M && k < nc) S.crev[(int64_t)i * kCandCap + k] = (lo[u] < nj[u] && cj[u][lo[u]] == tgt[u]) ? lo[u] : -1;
+    }
   }
+}
+
+// The reverse positions after a build the host asked for (a gated build's
+// are found by the next format, one launch less in every update).
+__global__ __launch_bounds__(256) void k_nl_skin_crev(SkinArgs S, int ntot) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i < ntot) crev_row(S, i, threadIdx.x & 63);
 }
 
 // After a build the host asked for: no rebuild pending, no format since.
@@ -519,35 +521,62 @@ __global__ void k_fill_gate(int32_t* gate) {
 // more than skin/2 since the build (the format's exactness condition) or
 // when `every` > 0 updates have passed since it.  gate[0] was cleared by the
 // previous format's second pass.
-__global__ __launch_bounds__(256) void k_nl_skin_check(const double* __restrict__ x, const double* __restrict__ xref,
-                                                       int ntot, double half_skin2, int every, int32_t* gate) {
+__device__ __forceinline__ bool skin_moved(const double* x, const double* xref, int ntot, double half_skin2) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  bool moved = false;
-  if (i < ntot) {
-    const double ex = x[3 * i] - xref[3 * i], ey = x[3 * i + 1] - xref[3 * i + 1], ez = x[3 * i + 2] - xref[3 * i + 2];
-    moved = !((ex * ex + ey * ey) + ez * ez <= half_skin2);
-  }
-  if (__ballot(moved) && (threadIdx.x & 63) == 0) atomicOr(gate, 1);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const int k = gate[1] + 1;
-    gate[1] = k;
-    if (every > 0 && k >= every) atomicOr(gate, 1);
-  }
+  if (i >= ntot) return false;
+  const double ex = x[3 * i] - xref[3 * i], ey = x[3 * i + 1] - xref[3 * i + 1], ez = x[3 * i + 2] - xref[3 * i + 2];
+  return !((ex * ex + ey * ey) + ez * ez <= half_skin2);
+}
+__device__ __forceinline__ bool skin_due(int every, int32_t* gate) {  // one thread of the grid
+  const int k = gate[1] + 1;
+  gate[1] = k;
+  return every > 0 && k >= every;
 }
 
-// Small frames: the cell binning of a gated Verlet build (wrap in place,
-// cell counts, their scan, the scatter) in one work-group, one launch
-// instead of three; a step with no rebuild returns at once.  Counts and
-// fill counters stay in LDS (the global ones, which the multi-work-group
-// binning uses, stay zero).  The skin check stays a kernel of its own: one
-// compute unit alone reads the positions several times slower.
+__global__ __launch_bounds__(256) void k_nl_skin_check(const double* __restrict__ x, const double* __restrict__ xref,
+                                                       int ntot, double half_skin2, int every, int32_t* gate) {
+  const bool moved = skin_moved(x, xref, ntot, half_skin2);
+  if (__ballot(moved) && (threadIdx.x & 63) == 0) atomicOr(gate, 1);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && skin_due(every, gate)) atomicOr(gate, 1);
+}
+
+// Frames of up to 131,072 atoms and 4,096 cells: the check and the cell
+// binning of a gated Verlet build (wrap in place, cell counts, their scan, the
+// scatter) in one launch instead of four.  Every work-group checks 1,024
+// atoms; the one that ends last, when all have read their positions, sees the
+// decision and does the binning alone if there is one (counts and fill
+// counters stay in LDS; the global ones, which the multi-work-group binning
+// uses, stay zero).  A launch that finds nothing to do costs 4.6 us in a
+// stream of kernels, whatever its size (check, empty binning and
+// empty reverse search at 12,288 atoms: 13.9 us before, 4.6 and 0.9 in the
+// format now).
 constexpr int kPrepSmallAtoms = 1 << 17, kPrepSmallCells = 4096;
-__global__ __launch_bounds__(1024) void k_nl_bin_small(double* __restrict__ x, const FrameInfo* __restrict__ fr,
-                                                      int ntot, int ncells, const int32_t* gate,
+__global__ __launch_bounds__(1024) void k_nl_check_bin(double* __restrict__ x, const double* __restrict__ xref,
+                                                      const FrameInfo* __restrict__ fr, int ntot, double half_skin2,
+                                                      int every, int ncells, int32_t* gate, int32_t* done,
                                                       int32_t* __restrict__ cell_of, int32_t* __restrict__ cell_start,
                                                       int32_t* __restrict__ cell_atoms, int32_t* flags,
                                                       int32_t* images) {
-  if (*gate == 0) return;
+  __shared__ int32_t go;
+  const bool due = blockIdx.x == 0 && threadIdx.x == 0 && skin_due(every, gate);
+  const int any = __syncthreads_or(skin_moved(x, xref, ntot, half_skin2) || due);
+  if (threadIdx.x == 0) {
+    // (a decision has reached memory before this work-group counts itself done:
+    // the atomic's result is waited for; nothing else is handed over)
+    if (any) {
+      const int old = atomicOr(gate, 1);
+      asm volatile("" ::"v"(old) : "memory");
+    }
+    go = 0;
+    if (gridDim.x == 1) {
+      go = any;
+    } else if (atomicAdd(done, 1) == (int)gridDim.x - 1) {
+      atomicExch(done, 0);
+      go = atomicOr(gate, 0);
+    }
+  }
+  __syncthreads();
+  if (go == 0) return;
   __shared__ int32_t cnt[kPrepSmallCells];  // counts, then fill counters
   __shared__ int32_t st[kPrepSmallCells];   // cell starts
   __shared__ int32_t part[1024];
@@ -620,6 +649,7 @@ __global__ __launch_bounds__(256) void k_nl_skin_format(SearchArgs A, SkinArgs S
   const int w = threadIdx.x >> 6;
   const int i = blockIdx.x * kSearchWaves + w;
   if (i >= A.ntot) return;
+  const int rebuilt = S.gate[0];
   const double xi = A.x[3 * i], yi = A.x[3 * i + 1], zi = A.x[3 * i + 2];
   if (lane == 0) {
     const double ex = xi - S.xref[3 * i], ey = yi - S.xref[3 * i + 1], ez = zi - S.xref[3 * i + 2];
@@ -677,6 +707,7 @@ __global__ __launch_bounds__(256) void k_nl_skin_format(SearchArgs A, SkinArgs S
   if (capacity) ncand = CAP;
   wave_lds_sync();
   rank_and_write(A, L, w, lane, i, ncand, capacity, S.cof, S.slot_of);
+  if (rebuilt) crev_row(S, i, lane);  // the update's build has just run
 }
 
 // Reverse index from the candidate bookkeeping of the format (same meaning
@@ -861,8 +892,7 @@ static void skin_build_kernels(dp_ctx* c, const double* x, const int32_t* types,
   const int64_t gb = (ntot + kSearchWaves - 1) / kSearchWaves, gbmax = 5LL * c->ncu;
   hipLaunchKernelGGL(k_nl_skin_build, dim3((unsigned)(gb < gbmax ? gb : gbmax)), dim3(64 * kSearchWaves), 0, s, A, S,
                      rl * rl);
-  const int64_t gq = (ntot + 3) / 4, gqmax = 8LL * c->ncu;  // a wave per atom, resident grid
-  hipLaunchKernelGGL(k_nl_skin_crev, dim3((unsigned)(gq < gqmax ? gq : gqmax)), dim3(256), 0, s, S, ntot);
+  if (!gate) hipLaunchKernelGGL(k_nl_skin_crev, dim3((ntot + 3) / 4), dim3(256), 0, s, S, ntot);
 }
 
 void launch_nl_skin_build(dp_ctx* c, double* x, const int32_t* types, int32_t ntot, int32_t ncells, int32_t* images,
@@ -880,12 +910,14 @@ void launch_nl_skin_update(dp_ctx* c, double* x, const int32_t* types, int32_t n
                            int32_t* rebuilds, hipStream_t s) {
   if (ntot <= 0) return;
   int32_t* gate = c->skin_gate;
-  hipLaunchKernelGGL(k_nl_skin_check, dim3((ntot + 255) / 256), dim3(256), 0, s, (const double*)x,
-                     (const double*)c->skin_xref, ntot, 0.25 * c->skin * c->skin, every, gate);
+  const double half_skin2 = 0.25 * c->skin * c->skin;
   if (ntot <= kPrepSmallAtoms && c->skin_ncells <= kPrepSmallCells) {
-    hipLaunchKernelGGL(k_nl_bin_small, dim3(1), dim3(1024), 0, s, x, c->skin_frame, ntot, c->skin_ncells,
-                       (const int32_t*)gate, c->cell_of, c->cell_start, c->cell_atoms, c->flags_dev, images);
+    hipLaunchKernelGGL(k_nl_check_bin, dim3((ntot + 1023) / 1024), dim3(1024), 0, s, x, (const double*)c->skin_xref,
+                       c->skin_frame, ntot, half_skin2, every, c->skin_ncells, gate, c->ovf_ctr + 16, c->cell_of,
+                       c->cell_start, c->cell_atoms, c->flags_dev, images);
   } else {
+    hipLaunchKernelGGL(k_nl_skin_check, dim3((ntot + 255) / 256), dim3(256), 0, s, (const double*)x,
+                       (const double*)c->skin_xref, ntot, half_skin2, every, gate);
     hipLaunchKernelGGL(k_nl_bin, dim3((ntot + 255) / 256), dim3(256), 0, s, (const double*)x, c->skin_frame, 1, ntot,
                        c->cell_of, c->cell_count, c->flags_dev, x, images, (const int32_t*)gate);
     hipLaunchKernelGGL(k_nl_scan, dim3(1), dim3(1024), 0, s, c->cell_count, c->cell_start, c->cell_fill,
@@ -901,6 +933,7 @@ void launch_nl_skin_format(dp_ctx* c, const double* x, const int32_t* types, int
   if (ntot <= 0) return;
   SearchArgs A = search_args(c, x, types, ntot, 1, nlist, c->ovf_ctr);
   SkinArgs S = skin_args(c);
+  S.gate = c->skin_gate;
   const dim3 grid((ntot + kSearchWaves - 1) / kSearchWaves), block(64 * kSearchWaves);
   if (A.nm <= kKeepCapSmall) hipLaunchKernelGGL(k_nl_skin_format<kKeepCapSmall>, grid, block, 0, s, A, S);
   else hipLaunchKernelGGL(k_nl_skin_format<kCandCap>, grid, block, 0, s, A, S);
