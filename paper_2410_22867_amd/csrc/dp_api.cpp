@@ -629,16 +629,20 @@ int set_device(int dev) {
 // count and the frame table are the ones that sort used; building a list
 // (or a Verlet candidate list) always sorts anew, and a list from elsewhere
 // always triggers a sort.
-static void type_sort(dp_ctx* c, const int32_t* types, int64_t n, int32_t nframes, bool may_reuse, hipStream_t s) {
-  if (may_reuse && c->ts_valid && c->ts_types == types && c->ts_n == n && c->ts_nframes == nframes &&
-      c->ts_frames_gen == c->frames_gen)
-    return;
-  launch_type_sort(c, types, (int32_t)n, nframes, s);
+static void type_sorted(dp_ctx* c, const int32_t* types, int64_t n, int32_t nframes) {
   c->ts_valid = true;
   c->ts_types = types;
   c->ts_n = n;
   c->ts_nframes = nframes;
   c->ts_frames_gen = c->frames_gen;
+}
+
+static void type_sort(dp_ctx* c, const int32_t* types, int64_t n, int32_t nframes, bool may_reuse, hipStream_t s) {
+  if (may_reuse && c->ts_valid && c->ts_types == types && c->ts_n == n && c->ts_nframes == nframes &&
+      c->ts_frames_gen == c->frames_gen)
+    return;
+  launch_type_sort(c, types, (int32_t)n, nframes, s);
+  type_sorted(c, types, n, nframes);
 }
 
 int compute_impl(dp_ctx* c, const double* x, const int32_t* types, const double* boxes, const int64_t* off,
@@ -710,12 +714,17 @@ int nlist_impl(dp_ctx* c, const double* x, const int32_t* types, const double* b
   c->last_stream = s;
   const int32_t ntot = (int32_t)n;
   StageScope p(c, DP_STAGE_NLIST, s);
-  launch_fill_i32(overflow, 0, 1, s);
-  launch_nl_bin(c, x, ntot, nframes, s);  // cell counts are zero between builds (cleared by the scan)
-  launch_nl_scan(c, (int32_t)ncells, s);
-  launch_nl_scatter(c, ntot, s);
+  // (the type sort is needed here for frame_of, by the reverse index)
+  if (launch_nl_prep(c, x, types, ntot, nframes, ncells, overflow, s)) {
+    type_sorted(c, types, n, nframes);
+  } else {
+    launch_fill_i32(overflow, 0, 1, s);
+    launch_nl_bin(c, x, ntot, nframes, s);  // cell counts are zero between builds (cleared by the scan)
+    launch_nl_scan(c, (int32_t)ncells, s);
+    launch_nl_scatter(c, ntot, s);
+    type_sort(c, types, n, nframes, false, s);
+  }
   launch_nl_search(c, x, types, ntot, nframes, nlist, overflow, s);
-  type_sort(c, types, n, nframes, false, s);  // frame_of for the reverse index
   launch_nl_reverse(c, x, types, nlist, ntot, s);
   c->rev_list = nlist;
   c->natoms_rev = n;

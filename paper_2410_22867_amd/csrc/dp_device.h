@@ -378,6 +378,65 @@ struct LdsCopy {
   }
 };
 
+__device__ __forceinline__ void set_flag(int32_t* flags, int32_t bit) { atomicOr(flags, bit); }
+
+// ---------------------------------------------------------------------------
+// Frame of atom i in the concatenated frames.
+__device__ __forceinline__ int find_frame(const FrameInfo* fr, int nframes, int i) {
+  int lo = 0, hi = nframes - 1;
+  while (lo < hi) {
+    int mid = (lo + hi + 1) >> 1;
+    if (fr[mid].atom_off <= i) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// The type sort's last part, by threads t < 32 of one wavefront: counts n_t
+// and segment bases from the atoms per type, then one thread per net and kind
+// writes its place in the order of the nets' work (NetShares).
+struct Sections {
+  int sec[kMaxT + 1];
+};
+__device__ __forceinline__ void write_type_meta(const int32_t* tot, int ntypes, const Sections& q, int32_t* meta, int t) {
+  if (t == 0) {
+    int base = 0;
+    for (int u = 0; u < kMaxT; ++u) {
+      meta[2 * u] = tot[u];
+      meta[2 * u + 1] = base;
+      base += ((tot[u] + kColPad - 1) / kColPad) * kColPad;
+    }
+  }
+  const int kind = t >> 4, k = t & 15, nnets = ntypes * ntypes;
+  if (kind >= 2 || k >= nnets) return;
+  auto work = [&](int net) -> int64_t {
+    const int ti = net / ntypes, tj = net - ti * ntypes, n = q.sec[tj + 1] - q.sec[tj];
+    const int unit = kind == 0 ? (n + 15) / 16 : (n * 5 / 8 + 16 * kGroupWaves - 1) / (16 * kGroupWaves);
+    return (int64_t)tot[ti] * unit;
+  };
+  const int64_t own = work(k);
+  int64_t total = 0, before = 0;
+  int rank = 0;
+  for (int o = 0; o < nnets; ++o) {
+    const int64_t w = work(o);
+    total += w;
+    if (w > own || (w == own && o < k)) {
+      ++rank;
+      before += w;
+    }
+  }
+  NetShares* S = reinterpret_cast<NetShares*>(meta + 2 * kMaxT);
+  S->net[kind][rank] = k;
+  S->before[kind][rank] = total > 0 ? (double)before / (double)total : 0.0;
+  if (rank == nnets - 1) S->before[kind][nnets] = total > 0 ? 1.0 : 0.0;
+}
+__device__ __forceinline__ int valid_type(int t, int ntypes, int32_t* flags) {
+  if (t < 0 || t >= ntypes) {
+    set_flag(flags, DP_FLAG_BAD_INPUT);
+    t = t < 0 ? 0 : ntypes - 1;
+  }
+  return t;
+}
+
 // ---------------------------------------------------------------------------
 // Wavefront helpers (wave64).
 __device__ __forceinline__ double shfl_xor_d(double v, int m) { return __shfl_xor(v, m, 64); }
@@ -462,7 +521,5 @@ __device__ __forceinline__ const T* opaque(const T* p) {
   asm volatile("" : "+v"(z));
   return p + z;
 }
-
-__device__ __forceinline__ void set_flag(int32_t* flags, int32_t bit) { atomicOr(flags, bit); }
 
 }  // namespace dpse

@@ -303,6 +303,9 @@ void launch_param_gather(const double* P, const int32_t* idx, int64_t n, int kin
 // writes one frame-table entry and clears a status word (kernel arguments
 // only: no host staging buffer)
 void launch_set_frame(FrameInfo* dst, const FrameInfo& F, int32_t* flags, hipStream_t s);
+// List builds of few atoms: binning and type sort in one launch (false: not taken).
+bool launch_nl_prep(dp_ctx* c, const double* x, const int32_t* types, int32_t ntot, int32_t nframes, int64_t ncells,
+                    int32_t* overflow, hipStream_t s);
 void launch_type_sort(dp_ctx* c, const int32_t* types, int32_t ntot, int32_t nframes, hipStream_t s);
 // compute
 void launch_env(dp_ctx* c, const double* x, const int32_t* types, const int32_t* nlist, int32_t ntot, double* forces,

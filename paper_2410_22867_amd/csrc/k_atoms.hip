@@ -63,15 +63,6 @@ void launch_fill_f64(double* p, double v, int64_t n, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(k_fill_f64, dim3((n + 255) / 256), dim3(256), 0, s, p, v, n);
 }
 
-__device__ __forceinline__ int frame_lookup(const FrameInfo* fr, int nframes, int i) {
-  int lo = 0, hi = nframes - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (fr[mid].atom_off <= i) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 // ---------------------------------------------------------------- type sort
 // Centre atoms are bucketed by type (Computation Optimization section: the
 // environment matrix is pre-classified by atom type) into column segments of
@@ -79,31 +70,19 @@ __device__ __forceinline__ int frame_lookup(const FrameInfo* fr, int nframes, in
 // padded to a multiple of kColPad columns.
 constexpr int kChunk = 1024;
 
-__device__ __forceinline__ int clamp_type(int t, int ntypes, int32_t* flags) {
-  if (t < 0 || t >= ntypes) {
-    set_flag(flags, DP_FLAG_BAD_INPUT);
-    t = t < 0 ? 0 : ntypes - 1;
-  }
-  return t;
-}
-
 __global__ __launch_bounds__(1024) void k_type_count(const int32_t* __restrict__ types, int ntot, int ntypes,
                                                      int32_t* __restrict__ chunk_counts, int32_t* flags) {
   __shared__ int32_t cnt[kMaxT];
   if (threadIdx.x < kMaxT) cnt[threadIdx.x] = 0;
   __syncthreads();
   int i = blockIdx.x * kChunk + threadIdx.x;
-  if (i < ntot) atomicAdd(&cnt[clamp_type(types[i], ntypes, flags)], 1);
+  if (i < ntot) atomicAdd(&cnt[valid_type(types[i], ntypes, flags)], 1);
   __syncthreads();
   if (threadIdx.x < kMaxT) chunk_counts[blockIdx.x * kMaxT + threadIdx.x] = cnt[threadIdx.x];
 }
 
-// One thread per type: turns per-chunk counts into per-chunk offsets and
-// writes n_t and the segment bases; then one thread per net and kind writes
-// its place in the order of the nets' work (NetShares).
-struct Sections {
-  int sec[kMaxT + 1];
-};
+// One thread per type: turns per-chunk counts into per-chunk offsets; then
+// the counts and segment bases and the nets' shares (write_type_meta).
 __global__ void k_type_scan(int32_t* __restrict__ chunk_counts, int nchunks, int ntypes, Sections q,
                             int32_t* __restrict__ meta) {
   __shared__ int32_t tot[kMaxT];
@@ -119,36 +98,7 @@ __global__ void k_type_scan(int32_t* __restrict__ chunk_counts, int nchunks, int
     tot[t] = acc;
   }
   __syncthreads();
-  if (t == 0) {
-    int base = 0;
-    for (int u = 0; u < kMaxT; ++u) {
-      meta[2 * u] = tot[u];
-      meta[2 * u + 1] = base;
-      base += ((tot[u] + kColPad - 1) / kColPad) * kColPad;
-    }
-  }
-  const int kind = t >> 4, k = t & 15, nnets = ntypes * ntypes;
-  if (kind >= 2 || k >= nnets) return;
-  auto work = [&](int net) -> int64_t {
-    const int ti = net / ntypes, tj = net - ti * ntypes, n = q.sec[tj + 1] - q.sec[tj];
-    const int unit = kind == 0 ? (n + 15) / 16 : (n * 5 / 8 + 16 * kGroupWaves - 1) / (16 * kGroupWaves);
-    return (int64_t)tot[ti] * unit;
-  };
-  const int64_t own = work(k);
-  int64_t total = 0, before = 0;
-  int rank = 0;
-  for (int o = 0; o < nnets; ++o) {
-    const int64_t w = work(o);
-    total += w;
-    if (w > own || (w == own && o < k)) {
-      ++rank;
-      before += w;
-    }
-  }
-  NetShares* S = reinterpret_cast<NetShares*>(meta + 2 * kMaxT);
-  S->net[kind][rank] = k;
-  S->before[kind][rank] = total > 0 ? (double)before / (double)total : 0.0;
-  if (rank == nnets - 1) S->before[kind][nnets] = total > 0 ? 1.0 : 0.0;
+  write_type_meta(tot, ntypes, q, meta, t);
 }
 
 __global__ __launch_bounds__(1024) void k_type_assign(const int32_t* __restrict__ types, int ntot, int ntypes,
@@ -175,7 +125,7 @@ __global__ __launch_bounds__(1024) void k_type_assign(const int32_t* __restrict_
     const int col = meta[2 * t + 1] + chunk_off[blockIdx.x * kMaxT + t] + off + before;
     col_of[i] = col;
     atom_at[col] = i;
-    frame_of[i] = frame_lookup(fr, nframes, i);
+    frame_of[i] = find_frame(fr, nframes, i);
   }
 }
 

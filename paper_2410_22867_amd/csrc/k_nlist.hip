@@ -24,15 +24,6 @@ __device__ __forceinline__ double r2_nofma(double dx, double dy, double dz) {
   return (dx * dx + dy * dy) + dz * dz;
 }
 
-__device__ __forceinline__ int find_frame(const FrameInfo* fr, int nframes, int i) {
-  int lo = 0, hi = nframes - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (fr[mid].atom_off <= i) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ int cell_coord(double x, double L, int nc) {
   int k = (int)floor(x / L * (double)nc);
   return k < 0 ? 0 : (k >= nc ? nc - 1 : k);
@@ -151,15 +142,6 @@ struct CandLds {
   CandRec r[kSearchWaves][CAP];
 };
 
-__device__ __forceinline__ int clamp_type(const int32_t* types, int j, int ntypes, int32_t* flags) {
-  int tj = types[j];
-  if (tj < 0 || tj >= ntypes) {
-    set_flag(flags, DP_FLAG_BAD_INPUT);
-    tj = tj < 0 ? 0 : ntypes - 1;
-  }
-  return tj;
-}
-
 // Walks the 27 stencil cells of atom i (one wavefront) and appends every
 // (j, s) with r^2 < rad2 to the LDS buffers of wave w, in a fixed order.
 // Returns the candidate count (capped at CAP; *capacity set beyond).
@@ -235,7 +217,7 @@ __device__ __forceinline__ int gather_cells(const SearchArgs& A, CandLds<CAP>& L
       rec.r2 = r2;
       rec.pk = 27 * j + scode;
       rec.k = 0;
-      rec.t = (int8_t)clamp_type(A.types, j, A.ntypes, A.flags);
+      rec.t = (int8_t)valid_type(A.types[j], A.ntypes, A.flags);
       rec.pad = 0;
       L.r[w][slot] = rec;
     }
@@ -540,6 +522,36 @@ __global__ __launch_bounds__(256) void k_nl_skin_check(const double* __restrict_
   if (blockIdx.x == 0 && threadIdx.x == 0 && skin_due(every, gate)) atomicOr(gate, 1);
 }
 
+// Exclusive scan of a work-group's LDS cell counts (1,024 threads): thread t
+// sums its run of cells, a scan of the 1,024 sums, then the run's starts, to
+// LDS and memory; the counts are cleared for the scatter.
+constexpr int kPrepSmallCells = 4096;
+__device__ __forceinline__ void scan_cells(int32_t* cnt, int32_t* st, int32_t* part, int32_t* __restrict__ start, int ncells) {
+  constexpr int kRun = kPrepSmallCells / 1024;
+  const int tid = threadIdx.x, c0 = tid * kRun;
+  int run = 0;
+#pragma unroll
+  for (int q = 0; q < kRun; ++q) run += c0 + q < ncells ? cnt[c0 + q] : 0;
+  part[tid] = run;
+  __syncthreads();
+  for (int off = 1; off < 1024; off <<= 1) {
+    const int t = tid >= off ? part[tid - off] : 0;
+    __syncthreads();
+    part[tid] += t;
+    __syncthreads();
+  }
+  int acc = part[tid] - run;
+#pragma unroll
+  for (int q = 0; q < kRun; ++q)
+    if (c0 + q < ncells) {
+      st[c0 + q] = acc;
+      start[c0 + q] = acc;
+      acc += cnt[c0 + q];
+      cnt[c0 + q] = 0;
+    }
+  if (tid == 1023) start[ncells] = part[1023];
+}
+
 // Frames of up to 131,072 atoms and 4,096 cells: the check and the cell
 // binning of a gated Verlet build (wrap in place, cell counts, their scan, the
 // scatter) in one launch instead of four.  Every work-group checks 1,024
@@ -550,7 +562,7 @@ __global__ __launch_bounds__(256) void k_nl_skin_check(const double* __restrict_
 // stream of kernels, whatever its size (check, empty binning and
 // empty reverse search at 12,288 atoms: 13.9 us before, 4.6 and 0.9 in the
 // format now).
-constexpr int kPrepSmallAtoms = 1 << 17, kPrepSmallCells = 4096;
+constexpr int kPrepSmallAtoms = 1 << 17;
 __global__ __launch_bounds__(1024) void k_nl_check_bin(double* __restrict__ x, const double* __restrict__ xref,
                                                       const FrameInfo* __restrict__ fr, int ntot, double half_skin2,
                                                       int every, int ncells, int32_t* gate, int32_t* done,
@@ -607,36 +619,132 @@ __global__ __launch_bounds__(1024) void k_nl_check_bin(double* __restrict__ x, c
     atomicAdd(&cnt[cid], 1);
   }
   __syncthreads();
-  // exclusive scan: thread t sums its run of cells, a scan of the 1024 sums,
-  // then the run's starts
-  constexpr int kRun = kPrepSmallCells / 1024;
-  const int c0 = tid * kRun;
-  int run = 0;
-#pragma unroll
-  for (int q = 0; q < kRun; ++q) run += c0 + q < ncells ? cnt[c0 + q] : 0;
-  part[tid] = run;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int t = tid >= off ? part[tid - off] : 0;
-    __syncthreads();
-    part[tid] += t;
-    __syncthreads();
-  }
-  int acc = part[tid] - run;
-#pragma unroll
-  for (int q = 0; q < kRun; ++q)
-    if (c0 + q < ncells) {
-      st[c0 + q] = acc;
-      cell_start[F.cell_off + c0 + q] = acc;
-      acc += cnt[c0 + q];
-      cnt[c0 + q] = 0;
-    }
-  if (tid == 1023) cell_start[F.cell_off + ncells] = part[1023];
+  scan_cells(cnt, st, part, cell_start + F.cell_off, ncells);
   __syncthreads();
   for (int i = tid; i < ntot; i += 1024) {
     const int cid = cell_of[i] - F.cell_off;
     const int p = atomicAdd(&cnt[cid], 1);
     cell_atoms[st[cid] + p] = i;
+  }
+}
+
+// Calls of up to 8,192 atoms and 4,096 cells: everything a list build does
+// before its search, and the type sort, in one launch of two work-groups
+// instead of eight launches (each 4.5 to 17 us in a stream of kernels: 3,333
+// water atoms 39 -> 9 us, 8,190 43 -> 16, 4,000 copper atoms 61 -> 10).  Work-group 0 bins
+// (overflow count cleared, cell counts and fill counters in LDS, the scan, the
+// scatter); work-group 1 sorts the types, as k_type_count, k_type_scan and
+// k_type_assign do.  A thread's eight atoms are loaded before any is used.
+// The launches' time hardly grows with the atoms, this kernel's in proportion:
+// beyond the registers of eight atoms a thread there is little to win, and the
+// multi-work-group kernels are taken.
+constexpr int kPrepAtoms = 8192, kPrepPer = kPrepAtoms / 1024;
+struct PrepArgs {
+  const double* x;
+  const int32_t* types;
+  const FrameInfo* fr;
+  int nframes, ntot, ncells, ntypes, ncols;
+  int32_t *overflow, *flags;
+  int32_t *cell_of, *cell_start, *cell_atoms;
+  int32_t *meta, *col_of, *atom_at, *frame_of;
+  Sections q;
+};
+
+__global__ __launch_bounds__(1024) void k_nl_prep(PrepArgs A) {
+  __shared__ int32_t lds[2 * kPrepSmallCells + 1024];
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0) {
+    int32_t *cnt = lds, *st = lds + kPrepSmallCells, *part = lds + 2 * kPrepSmallCells;
+    if (tid == 0) *A.overflow = 0;
+    for (int c = tid; c < A.ncells; c += 1024) cnt[c] = 0;
+    double x[kPrepPer][3];
+    int cid[kPrepPer];
+#pragma unroll
+    for (int m = 0; m < kPrepPer; ++m)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) x[m][a] = 1024 * m + tid < A.ntot ? A.x[3 * (1024 * m + tid) + a] : 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < kPrepPer; ++m) {
+      const int i = 1024 * m + tid;
+      if (i < A.ntot) {
+        const FrameInfo& F = A.fr[find_frame(A.fr, A.nframes, i)];
+        int c[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          if (!(x[m][a] >= 0.0 && x[m][a] < F.L[a])) set_flag(A.flags, DP_FLAG_NOT_WRAPPED);
+          c[a] = cell_coord(x[m][a], F.L[a], F.ncell[a]);
+        }
+        cid[m] = F.cell_off + c[0] + F.ncell[0] * (c[1] + F.ncell[1] * c[2]);
+        A.cell_of[i] = cid[m];
+        atomicAdd(&cnt[cid[m]], 1);
+      }
+    }
+    __syncthreads();
+    scan_cells(cnt, st, part, A.cell_start, A.ncells);
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < kPrepPer; ++m)
+      if (1024 * m + tid < A.ntot) A.cell_atoms[st[cid[m]] + atomicAdd(&cnt[cid[m]], 1)] = 1024 * m + tid;
+    return;
+  }
+  // [type][chunk of 1,024 atoms][wave]: atoms of the type in the wave, then before it
+  constexpr int kW = kPrepPer * 16;
+  int32_t *wc = lds, *tot = lds + kMaxT * kW;
+  const int lane = tid & 63, w = tid >> 6;
+  int ty[kPrepPer], before[kPrepPer];
+#pragma unroll
+  for (int m = 0; m < kPrepPer; ++m) ty[m] = 1024 * m + tid < A.ntot ? A.types[1024 * m + tid] : -1;
+  for (int c = tid; c < A.ncols; c += 1024) A.atom_at[c] = -1;
+#pragma unroll
+  for (int m = 0; m < kPrepPer; ++m) {
+    if (1024 * m + tid < A.ntot) ty[m] = valid_type(ty[m], A.ntypes, A.flags);
+    before[m] = 0;
+#pragma unroll
+    for (int u = 0; u < kMaxT; ++u) {
+      const uint64_t b = __ballot(ty[m] == u);
+      if (ty[m] == u)
+        before[m] = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0));
+      if (lane == 0) wc[u * kW + m * 16 + w] = __popcll(b);
+    }
+  }
+  __syncthreads();
+  if (w < kMaxT) {  // wave u: exclusive prefix over the kW waves of type u
+    int run = 0;
+#pragma unroll
+    for (int c = 0; c < kW; c += 64) {
+      const int v = wc[w * kW + c + lane];
+      int inc = v;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += y;
+      }
+      wc[w * kW + c + lane] = run + inc - v;
+      run += __shfl(inc, 63, 64);
+    }
+    if (lane == 0) tot[w] = run;
+  }
+  __syncthreads();
+  if (tid < 64) write_type_meta(tot, A.ntypes, A.q, A.meta, tid);
+  int base[kMaxT], acc = 0;
+#pragma unroll
+  for (int u = 0; u < kMaxT; ++u) {
+    base[u] = acc;
+    acc += (tot[u] + kColPad - 1) / kColPad * kColPad;
+  }
+#pragma unroll
+  for (int m = 0; m < kPrepPer; ++m) {
+    const int i = 1024 * m + tid;
+    if (i < A.ntot) {
+      int b = base[0];
+#pragma unroll
+      for (int u = 1; u < kMaxT; ++u) b = ty[m] == u ? base[u] : b;
+      const int col = b + wc[ty[m] * kW + m * 16 + w] + before[m];
+      A.col_of[i] = col;
+      A.atom_at[col] = i;
+      A.frame_of[i] = find_frame(A.fr, A.nframes, i);
+    }
   }
 }
 
@@ -851,6 +959,33 @@ static SearchArgs search_args(dp_ctx* c, const double* x, const int32_t* types, 
   for (int t = 0; t <= kMaxT; ++t) A.sec[t] = t <= m->desc.ntypes ? m->sec[t] : m->nm;
   A.rc2 = m->desc.rcut * m->desc.rcut;
   return A;
+}
+
+bool launch_nl_prep(dp_ctx* c, const double* x, const int32_t* types, int32_t ntot, int32_t nframes, int64_t ncells,
+                    int32_t* overflow, hipStream_t s) {
+  if (ntot <= 0 || ntot > kPrepAtoms || ncells > kPrepSmallCells) return false;
+  const dp_model* m = c->model;
+  PrepArgs A;
+  A.x = x;
+  A.types = types;
+  A.fr = c->frames_dev;
+  A.nframes = nframes;
+  A.ntot = ntot;
+  A.ncells = (int)ncells;
+  A.ntypes = m->desc.ntypes;
+  A.ncols = ntot + A.ntypes * kColPad;  // more than the padded segments
+  A.overflow = overflow;
+  A.flags = c->flags_dev;
+  A.cell_of = c->cell_of;
+  A.cell_start = c->cell_start;
+  A.cell_atoms = c->cell_atoms;
+  A.meta = c->type_meta;
+  A.col_of = c->col_of;
+  A.atom_at = c->atom_at;
+  A.frame_of = c->frame_of;
+  for (int t = 0; t <= kMaxT; ++t) A.q.sec[t] = m->sec[t < A.ntypes ? t : A.ntypes];
+  hipLaunchKernelGGL(k_nl_prep, dim3(2), dim3(1024), 0, s, A);
+  return true;
 }
 
 static SkinArgs skin_args(dp_ctx* c) {

@@ -1,0 +1,80 @@
+"""List builds on each side of the sizes where binning and type sort take one
+launch (8,192 atoms, 4,096 cells): the list against the oracle, one frame and
+several, and the column order through the results computed on it.  The list is
+bit-exact; energies and forces of the two sides of the bound as for full
+frames (energy 1e-10 relative, forces 1e-9 eV/A)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2410_22867_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _frame(n, seed):
+    """n water-density atoms: the first n of a larger box's, so that counts
+    of atoms that are no whole molecules occur too."""
+    mols = (n + 2) // 3
+    sites = int(np.ceil(mols ** (1 / 3)))
+    fr = I.water_box(mols, max(I.water_density_box(mols), 2.95 * sites), seed)
+    return I.Frame(np.ascontiguousarray(fr.coords[:n]), np.ascontiguousarray(fr.types[:n]), fr.box)
+
+
+def _model(n):
+    from paper_2410_22867_amd import dpse
+    p = I.init_params(I.WATER, 100, I.WATER_OUTPUT_SCALE)
+    model = dpse.Model(I.WATER, p)
+    return dpse, p, model, dpse.Context(model, n)
+
+
+@pytest.mark.parametrize("n", [192, 1023, 1025, 8191, 8192, 8193])
+def test_one_frame(n):
+    fr = _frame(n, 51)
+    dpse, p, model, ctx = _model(n + 700)  # a context larger than the frame
+    dev = torch.device("cuda:0")
+    x, t = torch.tensor(fr.coords, device=dev), torch.tensor(fr.types, device=dev)
+    print("list of", n, "atoms", flush=True)
+    o, oov = oracle.nlist(fr.coords, fr.types, fr.box, I.WATER)
+    for _ in range(2):
+        ov = torch.full((1,), 77, dtype=torch.int32, device=dev)
+        nl, ov = ctx.build_nlist(x, t, fr.box, overflow=ov)
+        assert np.array_equal(nl.cpu().numpy(), o) and int(ov) == oov
+    r = ctx.compute(x, t, fr.box, nl, mode="fp64", want_atom_energy=True)
+    rows = np.random.default_rng(1).choice(n, min(n, 200), replace=False)
+    e = oracle.compute(fr.coords, fr.types, fr.box, I.WATER, p, rows=rows, nl=o[rows])["Ei"]
+    got = r["Ei"].cpu().numpy()[rows]
+    assert np.abs(got - e).max() <= 1e-10 * np.abs(e).max()
+    assert np.abs(r["F"].cpu().numpy().sum(0)).max() <= 1e-9
+    assert ctx.status() == 0
+
+
+def test_frames_of_a_batch():
+    sizes = [192, 1, 1500, 64 * 3]
+    frs = [_frame(n, 60 + k) if n > 1 else I.Frame(np.full((1, 3), 1.0), np.zeros(1, np.int32), np.diag([20.0] * 3))
+           for k, n in enumerate(sizes)]
+    dpse, p, model, _ = _model(1)
+    ctx = dpse.Context(model, sum(sizes), max_frames=len(sizes))
+    dev = torch.device("cuda:0")
+    x = torch.tensor(np.concatenate([f.coords for f in frs]), device=dev)
+    t = torch.tensor(np.concatenate([f.types for f in frs]), device=dev)
+    boxes = np.stack([f.box for f in frs])
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    print("list of a batch", sizes, flush=True)
+    nl, ov = ctx.build_nlist_batch(x, t, boxes, off)
+    r = ctx.compute_batch(x, t, boxes, off, nl, mode="fp64")
+    for k, f in enumerate(frs):
+        o, _ = oracle.nlist(f.coords, f.types, f.box, I.WATER)
+        g = nl.cpu().numpy()[off[k]:off[k + 1]].copy()
+        g[g >= 0] -= 27 * off[k]
+        assert np.array_equal(g, o)
+        e = oracle.compute(f.coords, f.types, f.box, I.WATER, p)
+        assert abs(float(r["E"][k]) - e["E"]) <= 1e-10 * max(1.0, abs(e["E"]))
+        assert np.abs(r["F"].cpu().numpy()[off[k]:off[k + 1]] - e["F"]).max() <= 1e-9
+    # a call with an invalid type and a position outside the box is flagged
+    assert ctx.status() == 0
+    t[3], x[700, 1] = 7, -0.5
+    ctx.build_nlist_batch(x, t, boxes, off)
+    flags = ctx.status()
+    assert flags & dpse.FLAG_BAD_INPUT and flags & dpse.FLAG_NOT_WRAPPED
