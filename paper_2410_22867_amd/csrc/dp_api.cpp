@@ -672,7 +672,7 @@ int compute_impl(dp_ctx* c, const double* x, const int32_t* types, const double*
     // list not built by this context: derive its reverse index now (slots
     // whose reverse is not found fall back to atomics in the force pass)
     StageScope p(c, DP_STAGE_NLIST, s);
-    launch_nl_reverse(c, x, types, nlist, ntot, s);
+    launch_nl_reverse(c, types, nlist, ntot, s);
     c->rev_list = nlist;
     c->natoms_rev = n;
   }
@@ -725,7 +725,7 @@ int nlist_impl(dp_ctx* c, const double* x, const int32_t* types, const double* b
     type_sort(c, types, n, nframes, false, s);
   }
   launch_nl_search(c, x, types, ntot, nframes, nlist, overflow, s);
-  launch_nl_reverse(c, x, types, nlist, ntot, s);
+  launch_nl_reverse(c, types, nlist, ntot, s);
   c->rev_list = nlist;
   c->natoms_rev = n;
   HIPCHECK(hipGetLastError());

@@ -281,7 +281,7 @@ void launch_nl_scan(dp_ctx* c, int32_t ncells, hipStream_t s);
 void launch_nl_scatter(dp_ctx* c, int32_t ntot, hipStream_t s);
 void launch_nl_search(dp_ctx* c, const double* x, const int32_t* types, int32_t ntot, int32_t nframes,
                       int32_t* nlist, int32_t* overflow, hipStream_t s);
-void launch_nl_reverse(dp_ctx* c, const double* x, const int32_t* types, const int32_t* nlist, int32_t ntot,
+void launch_nl_reverse(dp_ctx* c, const int32_t* types, const int32_t* nlist, int32_t ntot,
                        hipStream_t s);
 // Verlet build: wraps x in place (image counters when non-NULL), bins on the
 // build's grid and keeps the candidates within r_c + skin.
