@@ -1063,6 +1063,202 @@ static void launch_pair_lp(dp_ctx* c, bool bwd, int mode, const PairArgsLp& p, h
   else launch_pair_lp_t<PrecF32, PrecF32>(bwd, grid, lds, p, fit_by_layer(c, mode), s);
 }
 
+// ------------------------------------------- first fitting layer, few atoms
+// T (sum of the section partials), D and h1 = tanh(D W1 + b1) in one launch: a
+// work-group owns MT m-tiles of one 16-column tile, its waves share the
+// reduction over D, and the partial sums meet in LDS.  T of the 16 columns is
+// staged in LDS once (one round of loads, all in flight), D is formed from it
+// operand by operand.  The work-groups of the first m-tiles also write T (and
+// D in the mixed forms).
+struct FirstArgs {
+  const int32_t* meta;
+  const int32_t* atom_at;
+  const void* Tpart;      // [sections][cols][m1][4]
+  int64_t tstride;
+  int ntypes, m1, M, nsplit;
+  void* T;
+  void* D;
+  const void* Afr;
+  int64_t a_type_stride;
+  const void* vec;        // b1 first
+  int64_t vec_type_stride;
+  void* out;
+  int64_t ld;
+};
+
+constexpr int kFirstT = 16 * 129;  // T rows of a tile, m1 <= 128
+constexpr int kFirstThreads = 1024, kFirstThreadsLp = 512;
+// Section sum of the tile's T rows into LDS ([16][m1 + 1][4]); zeros on
+// padding columns.  A thread's rows of the first two sections are requested
+// before any is used.
+template <typename TT, int NT>
+__device__ __forceinline__ void stage_T(const FirstArgs& p, int64_t col0, TT* Ts, bool write) {
+  typedef TT v4 __attribute__((ext_vector_type(4)));
+  constexpr int K = (16 * 128 + NT - 1) / NT;
+  const int per = 16 * p.m1;
+  const TT* base = static_cast<const TT*>(p.Tpart) + col0 * p.m1 * 4;
+  const int64_t second = p.ntypes > 1 ? p.tstride : 0;
+  v4 a[K], b[K];
+  int col[K], atom[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int e = min((int)threadIdx.x + k * NT, per - 1);
+    col[k] = e / p.m1;
+    a[k] = *reinterpret_cast<const v4*>(base + e * 4);
+    b[k] = *reinterpret_cast<const v4*>(base + e * 4 + second);
+    atom[k] = p.atom_at[col0 + col[k]];
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int e = threadIdx.x + k * NT;
+    if (e >= per) break;
+    v4 sum = v4{(TT)0, (TT)0, (TT)0, (TT)0} + a[k];
+    if (p.ntypes > 1) sum += b[k];
+    for (int t = 2; t < p.ntypes; ++t) sum += *reinterpret_cast<const v4*>(base + e * 4 + t * p.tstride);
+    if (atom[k] < 0) sum = v4{(TT)0, (TT)0, (TT)0, (TT)0};
+    *reinterpret_cast<v4*>(Ts + (e + col[k]) * 4) = sum;
+    if (write) *reinterpret_cast<v4*>(static_cast<TT*>(p.T) + (col0 * p.m1 + e) * 4) = sum;
+  }
+}
+
+template <int MT>
+__global__ __launch_bounds__(kFirstThreads) void k_fit_first_f64(FirstArgs p) {
+  constexpr int NW = 16, R = MT == 1 ? 4 : 2;
+  __shared__ __attribute__((aligned(32))) double lds_first[4 * (MT * NW * 64 > kFirstT ? MT * NW * 64 : kFirstT)];  // T, then the partial sums
+  const int t = blockIdx.z;
+  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int c0 = blockIdx.x * 16;
+  if (c0 >= n_t) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int r16 = lane & 15, gq = lane >> 4;
+  const int KS = p.m1, mtiles = p.M / 16, mt0 = blockIdx.y * MT;
+  const int S0 = KS * wv / NW, S1 = KS * (wv + 1) / NW;
+  const double* A = static_cast<const double*>(p.Afr) + t * p.a_type_stride;
+  d4 ar[R][MT];
+  auto load = [&](int S, d4* a) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      a[mt] = *reinterpret_cast<const d4*>(A + (((int64_t)min(mt0 + mt, mtiles - 1) * KS + min(S, S1 - 1)) * 64 + lane) * 4);
+  };
+  if (S0 < S1) {
+#pragma unroll
+    for (int d = 0; d < R - 1; ++d) load(S0 + d, ar[d]);
+  }
+  stage_T<double, kFirstThreads>(p, (int64_t)cb + c0, lds_first, blockIdx.y == 0);
+  __syncthreads();
+  const double* Tr = lds_first + r16 * (p.m1 + 1) * 4;
+  d4 Tb[4], acc[MT];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Tb[v] = *reinterpret_cast<const d4*>(Tr + (4 * gq + v) * 4);
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) acc[mt] = d4{0.0, 0.0, 0.0, 0.0};
+  auto step = [&](int S, const d4* a) {
+    const d4 Ta = *reinterpret_cast<const d4*>(Tr + S * 4);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double x = Ta[0] * Tb[v][0] + Ta[1] * Tb[v][1] + Ta[2] * Tb[v][2] + Ta[3] * Tb[v][3];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma_f64(a[mt][v], x, acc[mt]);
+    }
+  };
+  int S = S0;
+  for (; S + R <= S1; S += R) {
+#pragma unroll
+    for (int d = 0; d < R; ++d) {
+      load(S + d + R - 1, ar[(d + R - 1) % R]);
+      step(S + d, ar[d]);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < R - 1; ++d)
+    if (S + d < S1) step(S + d, ar[d]);
+  __syncthreads();
+  double* red = lds_first;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) *reinterpret_cast<d4*>(red + ((wv * MT + mt) * 64 + lane) * 4) = rows_of_lane(acc[mt]);
+  __syncthreads();
+  const int mt = threadIdx.x >> 8, e = threadIdx.x & 255;  // element (column e / 16, feature e % 16) of m-tile mt
+  if (mt >= MT || mt0 + mt >= mtiles) return;
+  const int at = (((e & 15) >> 2) * 16 + (e >> 4)) * 4 + (e & 3);
+  double z = 0.0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) z += red[(w * MT + mt) * 256 + at];
+  const int m = (mt0 + mt) * 16 + (e & 15);
+  const double b = (static_cast<const double*>(p.vec) + t * p.vec_type_stride)[m];
+  static_cast<double*>(p.out)[((int64_t)cb + c0 + (e >> 4)) * p.ld + m] = tanh_d(z + b);
+}
+
+// Mixed forms: wave s of nsplit takes the k-steps of split s of the split
+// product above (k_fit_gemm_lp, k_split_finish) in the same order and the
+// splits are added in the same order, so h1 keeps its bits.
+template <class P>
+__global__ __launch_bounds__(kFirstThreadsLp) void k_fit_first_lp(FirstArgs p) {
+  typedef typename P::store_t ST;
+  typedef typename P::raw8 R8;
+  typedef typename P::raw4 R4;
+  __shared__ __attribute__((aligned(16))) float lds_first_lp[4 * kFirstT];  // T, then the partial sums
+  static_assert(kFirstT >= kSplitMax * 64, "the partial sums fit");
+  const int t = blockIdx.z;
+  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int c0 = blockIdx.x * 16;
+  if (c0 >= n_t) return;
+  const int lane = threadIdx.x & 63, sp = threadIdx.x >> 6;
+  const int r16 = lane & 15, gq = lane >> 4;
+  const int KT = p.m1 / 2, mt = blockIdx.y;
+  // (waves past the last split only stage T)
+  const int kt0 = min(KT, (int)((int64_t)KT * sp / p.nsplit)), kt1 = min(KT, (int)((int64_t)KT * (sp + 1) / p.nsplit));
+  const ST* A = static_cast<const ST*>(p.Afr) + t * p.a_type_stride + ((int64_t)mt * KT * 64 + lane) * 8;
+  constexpr int R = 5;
+  R8 ar[R];
+  if (sp < p.nsplit) {
+#pragma unroll
+    for (int d = 0; d < R - 1; ++d) ar[d] = *reinterpret_cast<const R8*>(A + (int64_t)min(kt0 + d, kt1 - 1) * 512);
+  }
+  stage_T<float, kFirstThreadsLp>(p, (int64_t)cb + c0, lds_first_lp, mt == 0);
+  __syncthreads();
+  const float* Tr = lds_first_lp + r16 * (p.m1 + 1) * 4;
+  const int64_t col = (int64_t)cb + c0 + r16;
+  f4 Tb[4], acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Tb[v] = *reinterpret_cast<const f4*>(Tr + (4 * gq + v) * 4);
+  auto step = [&](int kt, const R8& a) {
+    R4 h[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const f4 Ta = *reinterpret_cast<const f4*>(Tr + (2 * kt + u) * 4);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float d = Ta[0] * Tb[v][0] + Ta[1] * Tb[v][1] + Ta[2] * Tb[v][2] + Ta[3] * Tb[v][3];
+        h[u][v] = P::bits(d);
+      }
+      if (mt == 0) *reinterpret_cast<R4*>(static_cast<ST*>(p.D) + (col * p.m1 + 2 * kt + u) * 16 + 4 * gq) = h[u];
+    }
+    acc = P::mfma(__builtin_bit_cast(typename P::vec8, a), __builtin_bit_cast(typename P::vec8, join8<P>(h[0], h[1])), acc);
+  };
+  int kt = kt0;
+  for (; kt + R <= kt1; kt += R) {
+#pragma unroll
+    for (int d = 0; d < R; ++d) {
+      ar[(d + R - 1) % R] = *reinterpret_cast<const R8*>(A + (int64_t)min(kt + d + R - 1, kt1 - 1) * 512);
+      step(kt + d, ar[d]);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < R - 1; ++d)
+    if (kt + d < kt1) step(kt + d, ar[d]);
+  __syncthreads();
+  float* red = lds_first_lp;
+  if (sp < p.nsplit) *reinterpret_cast<f4*>(red + (sp * 64 + lane) * 4) = acc;
+  __syncthreads();
+  if (sp) return;
+  f4 z = {0.f, 0.f, 0.f, 0.f};
+  for (int w = 0; w < p.nsplit; ++w) z += *reinterpret_cast<const f4*>(red + (w * 64 + lane) * 4);
+  const int m0 = 16 * mt + 4 * gq;
+  const float* b = static_cast<const float*>(p.vec) + t * p.vec_type_stride + m0;
+  *reinterpret_cast<f4*>(static_cast<float*>(p.out) + col * p.ld + m0) =
+      f4{tanh_f(z[0] + b[0]), tanh_f(z[1] + b[1]), tanh_f(z[2] + b[2]), tanh_f(z[3] + b[3])};
+}
+
 // ---------------------------------------------------------------- fused first fitting layer
 // Half-precision forms (16-bit operands, FP32 accumulation) of the first
 // fitting layer with the descriptor folded in on both sides:
@@ -1521,9 +1717,8 @@ static void split_finish(dp_ctx* c, const GemmArgs& g, hipStream_t s) {
 // FP64: as many splits as leave two work-groups per CU in all (the 16-bit
 // rule's 2,048 columns and fixed counts left half the chip idle at 2,100 to
 // 6,000 atoms), within the workspace (kSplitMax sums of split_cols columns, or
-// fewer sums of more).  Forward product, sums added (us): 192 water atoms
-// 21.5 -> 20.5, 900 52 -> 49, 2,100 92 -> 52, 3,333 169 -> 78, 6,000
-// 173 -> 112, 12,288 (unsplit) 181 -> 179.
+// fewer sums of more).  Forward product, sums added (us): 2,100 water atoms
+// 92 -> 52, 3,333 169 -> 78, 6,000 173 -> 112, 12,288 (unsplit) 181 -> 179.
 static int split_count_f64(const dp_ctx* c, int64_t wgs_unsplit, int ksteps) {
   const int64_t cols = c->natoms_last + (int64_t)c->model->desc.ntypes * kColPad;
   if (wgs_unsplit <= 0) return 1;
@@ -1548,9 +1743,9 @@ static void gemm_launch_f64(dp_ctx* c, const GemmArgs& g0, hipStream_t s) {
   g.nsplit = g.T ? split_count_f64(c, unsplit_wgs(c, BN, mblocks), g.K / 16) : 1;
   if (g.nsplit > 1) grid.y = (unsigned)(mblocks * g.nsplit);
   // Few column tiles: each XCD's L2 reads its share of the weights (3 MB a
-  // type) instead of all of them, and all columns' inputs.  Both first-layer
-  // products of 900 water atoms 93 -> 81 us, 450 atoms 61 -> 59, 1,500 and
-  // 2,100 unchanged; with more columns their inputs are the larger part.
+  // type) instead of all of them, and all columns' inputs.  The backward
+  // product of 900 water atoms 43.2 -> 39.7 us, 450 atoms 34.8 -> 33.8, 1,500
+  // and 2,100 unchanged; with more columns their inputs are the larger part.
   if (c->natoms_last <= 1280) {
     g.xtiles = (int)grid.x;
     g.yblocks = (int)grid.y;
@@ -1686,8 +1881,71 @@ static void launch_fit1_bwd(dp_ctx* c, int32_t mode, hipStream_t s) {
   else hipLaunchKernelGGL((k_fit1_bwd_lp<PrecF16, NT, NCG, 8, RING>), grid, dim3(256 * NCG), 0, s, f);
 }
 
+// Splits of the mixed first layer's product (1: none), see split_count.
+static int first_splits_lp(const dp_ctx* c) {
+  return split_count(c, unsplit_wgs(c, 64, (c->model->fw / 16 + 3) / 4), c->model->nd / 32);
+}
+
+// Whether T, D and the first layer are one launch (k_fit_first_*).  Descriptor,
+// product and finish against the one launch, water (us):
+//   atoms     192         300         450         900         1,500       2,100
+//   FP64      25 -> 13                36 -> 21    53 -> 39    49 -> 42    60 -> 60
+//   16-bit    13 -> 9     14 -> 11    15 -> 13    17 -> 16    19 -> 36
+//   FP32      20 -> 12    21 -> 13    26 -> 16    30 -> 21    35 -> 50
+// (each work-group forms D anew, which pays while few work-groups share a
+// column tile's and launches are what the rest of the time goes to; the mixed
+// forms' waves are the splits, whose number falls with the atoms).
+static bool fit_first(const dp_ctx* c, int32_t mode) {
+  if (mode == DP_FP64) return c->natoms_last <= 1792;
+  return !fit1_fused(c, mode) && c->natoms_last <= (mix_kinds(mode).fit1 == 3 ? 1280 : 768) && first_splits_lp(c) > 1;
+}
+
+template <int MT>
+static void launch_first_f64(dp_ctx* c, const FirstArgs& p, hipStream_t s) {
+  const dim3 grid((unsigned)((c->natoms_last + 15) / 16), (unsigned)((p.M / 16 + MT - 1) / MT), (unsigned)p.ntypes);
+  hipLaunchKernelGGL((k_fit_first_f64<MT>), grid, dim3(kFirstThreads), 0, s, p);
+}
+
+static void launch_first(dp_ctx* c, int32_t mode, hipStream_t s) {
+  const dp_model* m = c->model;
+  FirstArgs p = {};
+  p.meta = c->type_meta;
+  p.atom_at = c->atom_at;
+  p.Tpart = c->Tpart;
+  p.tstride = c->max_cols * m->m1 * 4;
+  p.ntypes = m->desc.ntypes;
+  p.m1 = m->m1;
+  p.M = m->fw;
+  p.T = c->T;
+  p.D = c->D;
+  p.out = c->fa[0];
+  p.vec_type_stride = m->fit_vec_per_type;
+  if (mode == DP_FP64) {
+    p.Afr = (const double*)m->fit_frag64 + m->ffo.fwd[0];
+    p.a_type_stride = m->ffo.per_type;
+    p.vec = m->fit_vec64;
+    p.ld = m->fw;
+    // one m-tile a work-group while there is a CU for each (192 atoms 13 us,
+    // three 19), else three (450 atoms 21, one 30; 900: 39, 42)
+    const int64_t tiles = (c->natoms_last + 15) / 16 + p.ntypes - 1;
+    if (tiles * (p.M / 16) <= c->ncu) launch_first_f64<1>(c, p, s);
+    else launch_first_f64<3>(c, p, s);
+    return;
+  }
+  const int kind = mix_kinds(mode).fit1;
+  p.Afr = elem_offset(frag_of(m->fit_frag_bf16, m->fit_frag_f16, m->fit_frag_f32, kind), kind, m->ffo_lp.fwd[0]);
+  p.a_type_stride = m->ffo_lp.per_type;
+  p.vec = m->fit_vec32;
+  p.ld = ((m->fw + 31) / 32) * 32;
+  p.nsplit = first_splits_lp(c);
+  const dim3 grid((unsigned)((c->natoms_last + 15) / 16), (unsigned)(p.M / 16), (unsigned)p.ntypes), wg(kFirstThreadsLp);
+  if (kind == 1) hipLaunchKernelGGL((k_fit_first_lp<PrecBF16>), grid, wg, 0, s, p);
+  else if (kind == 2) hipLaunchKernelGGL((k_fit_first_lp<PrecF16>), grid, wg, 0, s, p);
+  else hipLaunchKernelGGL((k_fit_first_lp<PrecF32>), grid, wg, 0, s, p);
+}
+
 void launch_descriptor(dp_ctx* c, int32_t mode, hipStream_t s) {
-  if (fit1_fused(c, mode)) return;  // formed inside the first fitting layer
+  if (fit1_fused(c, mode) || fit_first(c, mode)) return;  // formed inside the first fitting layer
   launch_descriptor_ex(c, mode, mode != DP_FP64, s);
 }
 
@@ -1738,6 +1996,8 @@ void launch_fit_forward(dp_ctx* c, int32_t mode, bool keep_h, hipStream_t s) {
   // layer 1: X = D [cols][nd] (FP64: built from T inside the GEMM)
   if (fit1_fused(c, mode)) {
     launch_fit1_fwd(c, mode, keep_h, s);
+  } else if (fit_first(c, mode)) {
+    launch_first(c, mode, s);
   } else {
   g.a_type_stride = tstride;
   g.Afr = f64 ? (const void*)((const double*)frag1 + off_fwd[0]) : elem_offset(frag1, mk.fit1, off_fwd[0]);

@@ -1,6 +1,7 @@
-"""Fitting layers one per launch and the split first layer, on each side of
-the atom counts where the route changes (water: 1,280 atoms FP64, 640 in the
-16-bit forms, 1,792 FP32), at the narrowest and widest fitting nets, and with
+"""Fitting layers one per launch, the first layer in one launch with the
+descriptor and the split first layer, on each side of the atom counts where
+the route changes (water: hidden layers 1,280 atoms FP64, 640 in the 16-bit
+forms, 1,792 FP32; first layer 272 and 1,792, 768, 1,280), at the narrowest and widest fitting nets, and with
 one type empty.  Bars: FP64 as for full frames, mixed forms the relative RMS
 force bars of the other nets."""
 import dataclasses
@@ -47,9 +48,11 @@ def _check(o, r, mode):
 @pytest.mark.parametrize("mols,fit,modes", [
     (64, 16, ["fp64", "bf16", "mix_fp32", "mix_fp16"]),
     (64, 256, ["fp64", "bf16", "mix_fp32", "mix_fp16"]),
+    (85, 240, ["fp64", "bf16"]), (86, 240, ["fp64"]),
     (213, 240, ["bf16", "mix_fp16"]), (214, 240, ["bf16", "mix_fp16"]),
-    (426, 240, ["fp64"]), (427, 240, ["fp64"]), (427, 256, ["fp64"]),
-    (597, 240, ["mix_fp32"]), (598, 240, ["fp64", "mix_fp32"]),
+    (256, 240, ["bf16", "mix_fp16"]), (257, 240, ["bf16", "mix_fp16"]),
+    (426, 240, ["fp64", "mix_fp32"]), (427, 240, ["fp64", "mix_fp32"]), (427, 256, ["fp64"]),
+    (597, 240, ["fp64", "mix_fp32"]), (598, 240, ["fp64", "mix_fp32"]),
 ])
 def test_fit_routes_match_oracle(mols, fit, modes):
     desc = dataclasses.replace(I.WATER, fit=(fit,) * 3)
