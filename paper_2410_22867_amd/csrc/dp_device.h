@@ -119,6 +119,12 @@ struct PrecF32 {
     for (int j = 0; j < 7; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], c, 0, 0, 0);
     return c;
   }
+  // ... without elements 4 to 7
+  static __device__ __forceinline__ f4 mfma4(vec8 a, vec8 b, f4 c) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], c, 0, 0, 0);
+    return c;
+  }
   static __device__ __forceinline__ float bits(float x) { return x; }
   static __device__ __forceinline__ float tof(float b) { return b; }
 };

@@ -241,7 +241,7 @@ struct PairArgs {
 };
 
 template <bool BWD, int NCT, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : (NW == 8 ? 6 : 4)))) void k_fit_pair_f64(PairArgs p) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 4))) void k_fit_pair_f64(PairArgs p) {
   constexpr int MW = 16 / NW;      // m-tile slots per wave (fw <= 256)
   constexpr int NC = 16 * NCT;    // columns of the work-group
   extern __shared__ double hs[];  // [NC][fw + 2]
@@ -253,9 +253,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int fw = p.fw, KS = fw / 16, mtiles = fw / 16, ldh = fw + 2;
   const double* vec = p.vec + t * p.vec_type_stride;
-  for (int e = threadIdx.x; e < NC * fw; e += 64 * NW) {
-    const int c = e / fw, k = e - c * fw;
-    hs[c * ldh + k] = p.in[(int64_t)(cb + c0 + c) * fw + k];
+  for (int e = threadIdx.x; e < NC * fw / 4; e += 64 * NW) {
+    const int c = e / (fw / 4), k = 4 * (e - c * (fw / 4));
+    *reinterpret_cast<d4*>(hs + c * ldh + k) = *reinterpret_cast<const d4*>(p.in + (int64_t)(cb + c0 + c) * fw + k);
   }
   // m-tile slots past the last tile (wave 3 when fw = 240) repeat the last
   // tile in the products, which keeps the k-loop free of branches; their
@@ -269,7 +269,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
   }
   // element v of m-tile slot j, column tile nt: feature 16 mtj[j] + gq + 4 v
   // of column c0 + 16 nt + r16
+  // (rows_of_lane: feature row4(j) + v)
   auto feat = [&](int j, int v) { return 16 * mtj[j] + gq + 4 * v; };
+  auto row4 = [&](int j) { return 16 * mtj[j] + 4 * gq; };
   auto colof = [&](int nt) { return (int64_t)cb + c0 + 16 * nt + r16; };
   auto hrow = [&](int nt) { return hs + (16 * nt + r16) * ldh; };
   d4 acc[MW][NCT];
@@ -326,22 +328,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
       for (int j = 0; j < MW; ++j) {
         if (!own[j]) continue;
 #pragma unroll
-        for (int nt = 0; nt < NCT; ++nt)
+        for (int nt = 0; nt < NCT; ++nt) {
+          const int m0 = row4(j);
+          const int64_t at = colof(nt) * fw + m0;
+          d4 tv = rows_of_lane(acc[j][nt]);
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int m = feat(j, v);
-            const int64_t col = colof(nt);
-            const double tv = tanh_d(acc[j][nt][v]);
-            const double h = hrow(nt)[m] + tv;
-            hrow(nt)[m] = h;
-            if constexpr (!LAST) {
-              p.out[0][col * fw + m] = tv;
-              if (p.out[1]) p.out[1][col * fw + m] = h;
-            } else {
-              if (p.out[2]) p.out[2][col * fw + m] = h;
-              p.out[3][col * fw + m] = vec[3 * fw + m] * (1.0 - tv * tv);
-            }
+          for (int v = 0; v < 4; ++v) tv[v] = tanh_d(tv[v]);
+          d4* hp = reinterpret_cast<d4*>(hrow(nt) + m0);
+          const d4 h = *hp + tv;
+          *hp = h;
+          if constexpr (!LAST) {
+            *reinterpret_cast<d4*>(p.out[0] + at) = tv;
+            if (p.out[1]) *reinterpret_cast<d4*>(p.out[1] + at) = h;
+          } else {
+            if (p.out[2]) *reinterpret_cast<d4*>(p.out[2] + at) = h;
+            d4 dz;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dz[v] = vec[3 * fw + m0 + v] * (1.0 - tv[v] * tv[v]);
+            *reinterpret_cast<d4*>(p.out[3] + at) = dz;
           }
+        }
       }
     };
     fwd_layer(A0, fw, std::false_type{});
@@ -365,14 +371,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
     }
   } else {
     // tanh of the layers below, requested before the products
-    double tp[MW][NCT][4];
+    d4 tp[MW][NCT];
     auto load_t = [&](const double* src) {
 #pragma unroll
       for (int j = 0; j < MW; ++j)
 #pragma unroll
-        for (int nt = 0; nt < NCT; ++nt)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) tp[j][nt][v] = src[colof(nt) * fw + feat(j, v)];
+        for (int nt = 0; nt < NCT; ++nt) tp[j][nt] = *reinterpret_cast<const d4*>(src + colof(nt) * fw + row4(j));
     };
     load_t(p.tprev[0]);
     init(3 * fw);  // w_o
@@ -383,14 +387,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
     for (int j = 0; j < MW; ++j) {
       if (!own[j]) continue;
 #pragma unroll
-      for (int nt = 0; nt < NCT; ++nt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int m = feat(j, v);
-          const double dz = acc[j][nt][v] * (1.0 - tp[j][nt][v] * tp[j][nt][v]);
-          hrow(nt)[m] = dz;
-          if (p.out[0]) p.out[0][colof(nt) * fw + m] = dz;
-        }
+      for (int nt = 0; nt < NCT; ++nt) {
+        const d4 dh = rows_of_lane(acc[j][nt]);
+        const d4 dz = dh * (1.0 - tp[j][nt] * tp[j][nt]);
+        *reinterpret_cast<d4*>(hrow(nt) + row4(j)) = dz;
+        if (p.out[0]) *reinterpret_cast<d4*>(p.out[0] + colof(nt) * fw + row4(j)) = dz;
+      }
     }
     load_t(p.tprev[1]);
     __syncthreads();
@@ -400,9 +402,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
       if (!own[j]) continue;
 #pragma unroll
       for (int nt = 0; nt < NCT; ++nt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          p.out[1][colof(nt) * fw + feat(j, v)] = acc[j][nt][v] * (1.0 - tp[j][nt][v] * tp[j][nt][v]);
+        *reinterpret_cast<d4*>(p.out[1] + colof(nt) * fw + row4(j)) =
+            rows_of_lane(acc[j][nt]) * (1.0 - tp[j][nt] * tp[j][nt]);
     }
   }
 }
@@ -493,13 +494,16 @@ __global__ __launch_bounds__(256) void k_fit_layer_f64(PairArgs p) {
   }
 }
 
-// One 16-column tile per work-group and four waves of four m-tile slots
-// (32 columns, or eight waves of two slots, measured no faster).  Frames
+// One 16-column tile per work-group and four waves of four m-tile slots; from
+// 32,768 atoms on two tiles and eight waves of two slots, which read the
+// weights half as often but leave the last work-groups longer (forward +
+// backward 98,304 atoms 990 -> 906 us, 12,288 156 both, 6,000 95 -> 148).  With
+// a lane's four rows stored as one vector and the tile copied in vectors,
+// 12,288 atoms 92 + 77 -> 87 + 69 us, 98,304 548 + 560 -> 465 + 441.  Frames
 // too small to give every CU a work-group (few atoms) take sixteen waves of
 // one slot each instead: the same work in a quarter of the serial chain.
-template <int NW>
+template <int NCT, int NW>
 static void launch_pair_f64_t(dp_ctx* c, bool bwd, const PairArgs& p, hipStream_t s) {
-  constexpr int NCT = 1;
   const dp_model* m = c->model;
   dim3 grid((unsigned)((c->natoms_last + 16 * NCT - 1) / (16 * NCT)), 1, (unsigned)m->desc.ntypes);
   const size_t lds = (size_t)16 * NCT * (m->fw + 2) * sizeof(double);
@@ -521,8 +525,9 @@ static void launch_pair_f64(dp_ctx* c, bool bwd, const PairArgs& p, hipStream_t 
     }
     return;
   }
-  if (wgs < c->ncu) launch_pair_f64_t<16>(c, bwd, p, s);
-  else launch_pair_f64_t<4>(c, bwd, p, s);
+  if (wgs < c->ncu) launch_pair_f64_t<1, 16>(c, bwd, p, s);
+  else if (wgs >= 8 * (int64_t)c->ncu) launch_pair_f64_t<2, 8>(c, bwd, p, s);
+  else launch_pair_f64_t<1, 4>(c, bwd, p, s);
 }
 
 // ---------------------------------------------------------------- mixed GEMM
@@ -744,11 +749,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
   const int fw = p.fw, fwp = p.fwp, KT = fwp / 32, mtiles = fw / 16;
   const int ldf = fwp + 4, ldh = fwp + 8;
   const float* vec = p.vec + t * p.vec_type_stride;
-  for (int e = threadIdx.x; e < NC * fwp; e += 64 * NW) {
-    const int c = e / fwp, k = e - c * fwp;
+  for (int e = threadIdx.x; e < NC * fwp / 8; e += 64 * NW) {
+    const int c = e / (fwp / 8), k = 8 * (e - c * (fwp / 8));
     const int64_t src = (int64_t)(cb + c0 + c) * fwp + k;
-    if constexpr (BWD) hsh[c * ldh + k] = k < fw ? reinterpret_cast<const ST*>(p.in)[src] : (ST)0;
-    else hsf[c * ldf + k] = k < fw ? reinterpret_cast<const float*>(p.in)[src] : 0.f;
+    if constexpr (BWD) {
+      R8 x = *reinterpret_cast<const R8*>(reinterpret_cast<const ST*>(p.in) + src);
+      if (k >= fw) x = zero8<P>();
+      *reinterpret_cast<R8*>(hsh + c * ldh + k) = x;
+    } else {
+      f4 lo = *reinterpret_cast<const f4*>(reinterpret_cast<const float*>(p.in) + src);
+      f4 hi = *reinterpret_cast<const f4*>(reinterpret_cast<const float*>(p.in) + src + 4);
+      if (k >= fw) lo = hi = f4{0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<f4*>(hsf + c * ldf + k) = lo;
+      *reinterpret_cast<f4*>(hsf + c * ldf + k + 4) = hi;
+    }
   }
   bool own[MW];
   int mtj[MW];
@@ -762,47 +776,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
   auto feat = [&](int j, int v) { return 16 * mtj[j] + 4 * gq + v; };
   auto colof = [&](int n) { return (int64_t)(cb + c0 + 16 * n + r16); };
   f4 acc[MW][NCT];
-  auto layer = [&](const ST* Afr) {
-    R8 aA[MW], aB[MW];
-    auto load = [&](int kt, R8* a) {
+  // Weights are requested a k-step ahead (three and four measured slower in
+  // all but the 16-bit backward), the next layer's first ones before the
+  // epilogue between the layers (not in the FP32 forward: registers).  With
+  // that and the tile copied in vectors, 12,288 water atoms forward and
+  // backward: BF16 25.8 and 22.3 -> 22.8 and 18.3 us, FP32 51.8 and 46.6 ->
+  // 49.1 and 42.0; leaving the padding's products out of the FP32 forward too
+  // measured 71 against 75 us at 19,652 atoms but 58.7 at 12,288.
+  R8 aA[MW], aB[MW];
+  auto load = [&](const ST* Afr, int kt, R8* a) {
 #pragma unroll
-      for (int j = 0; j < MW; ++j)
-        a[j] = *reinterpret_cast<const R8*>(Afr + (((int64_t)mtj[j] * KT + kt) * 64 + lane) * 8);
-    };
-    auto step = [&](int kt, const R8* a) {
+    for (int j = 0; j < MW; ++j)
+      a[j] = *reinterpret_cast<const R8*>(Afr + (((int64_t)mtj[j] * KT + min(kt, KT - 1)) * 64 + lane) * 8);
+  };
+  auto step = [&](int kt, const R8* a) {
 #pragma unroll
-      for (int n = 0; n < NCT; ++n) {
-        // B operand: features 32 kt + 4 gq + {0..3} and 32 kt + 16 + 4 gq + {0..3}
-        const int rc = 16 * n + r16;
-        typename P::vec8 x;
-        if constexpr (BWD) {
-          const ST* rowp = hsh + rc * ldh + 32 * kt + 4 * gq;
-          const R4 lo = *reinterpret_cast<const R4*>(rowp);
-          const R4 hi = *reinterpret_cast<const R4*>(rowp + 16);
-          x = __builtin_bit_cast(typename P::vec8, join8<P>(lo, hi));
-        } else {
-          const float* rowp = hsf + rc * ldf + 32 * kt + 4 * gq;
-          const f4 lo = *reinterpret_cast<const f4*>(rowp);
-          const f4 hi = *reinterpret_cast<const f4*>(rowp + 16);
-          const float v8[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-          x = pack8<P>(v8);
-        }
-#pragma unroll
-        for (int j = 0; j < MW; ++j) acc[j][n] = P::mfma(__builtin_bit_cast(typename P::vec8, a[j]), x, acc[j][n]);
+    for (int n = 0; n < NCT; ++n) {
+      // B operand: features 32 kt + 4 gq + {0..3} and 32 kt + 16 + 4 gq + {0..3}
+      const int rc = 16 * n + r16;
+      typename P::vec8 x;
+      if constexpr (BWD) {
+        const ST* rowp = hsh + rc * ldh + 32 * kt + 4 * gq;
+        const R4 lo = *reinterpret_cast<const R4*>(rowp);
+        const R4 hi = *reinterpret_cast<const R4*>(rowp + 16);
+        x = __builtin_bit_cast(typename P::vec8, join8<P>(lo, hi));
+      } else {
+        const float* rowp = hsf + rc * ldf + 32 * kt + 4 * gq;
+        const f4 lo = *reinterpret_cast<const f4*>(rowp);
+        const f4 hi = *reinterpret_cast<const f4*>(rowp + 16);
+        const float v8[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        x = pack8<P>(v8);
       }
-    };
-    load(0, aA);
+#pragma unroll
+      for (int j = 0; j < MW; ++j) {
+        const auto w = __builtin_bit_cast(typename P::vec8, a[j]);
+        // (the upper half of the last k-step may be padding: products with zero)
+        if constexpr (P::kind == 3 && BWD) acc[j][n] = 32 * kt + 16 < fw ? P::mfma(w, x, acc[j][n]) : P::mfma4(w, x, acc[j][n]);
+        else acc[j][n] = P::mfma(w, x, acc[j][n]);
+      }
+    }
+  };
+  auto layer = [&](const ST* Afr) {
     int kt = 0;
     for (; kt + 1 < KT; kt += 2) {
-      load(kt + 1, aB);
+      load(Afr, kt + 1, aB);
       step(kt, aA);
-      load(kt + 2 < KT ? kt + 2 : KT - 1, aA);
+      load(Afr, kt + 2, aA);
       step(kt + 1, aB);
     }
     if (kt < KT) step(kt, aA);
   };
   const ST* A0 = reinterpret_cast<const ST*>(p.A[0]) + t * p.a_type_stride;
   const ST* A1 = reinterpret_cast<const ST*>(p.A[1]) + t * p.a_type_stride;
+  load(A0, 0, aA);
   if constexpr (!BWD) {
     auto fwd_layer = [&](const ST* Afr, int bias_off, auto last_tag) {
       constexpr bool LAST = decltype(last_tag)::value;
@@ -813,7 +839,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
 #pragma unroll
           for (int v = 0; v < 4; ++v) acc[j][n][v] = vec[bias_off + feat(j, v)];
       __syncthreads();  // the tile (input or previous layer) is complete
+      if (LAST && P::kind == 3) load(Afr, 0, aA);
       layer(Afr);
+      if constexpr (!LAST && P::kind != 3) load(A1, 0, aA);
       __syncthreads();  // every wave has read the tile
 #pragma unroll
       for (int j = 0; j < MW; ++j)
@@ -886,6 +914,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
         for (int v = 0; v < 4; ++v) acc[j][n][v] = vec[3 * fw + feat(j, v)];  // w_o
     __syncthreads();
     layer(A0);  // acc = dh2
+    load(A1, 0, aA);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < MW; ++j)
