@@ -496,10 +496,7 @@ int build_maps(dp_model* m) {
 
 // Refreshes every device copy from m->params (stream-ordered).
 void gather_all(dp_model* m, hipStream_t s) {
-  for (int k = 0; k < m->n_maps; ++k) {
-    const ParamMap& pm = m->maps[k];
-    launch_param_gather(m->params, pm.idx_use, pm.n, pm.kind, pm.dst, s);
-  }
+  launch_param_gather(m, s);
   if (m->table) launch_tab_build(m, s);
 }
 

@@ -297,9 +297,10 @@ void launch_nl_skin_format(dp_ctx* c, const double* x, const int32_t* types, int
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 void launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
 void launch_copy_i32(const int32_t* a, int32_t* b, int64_t n, hipStream_t s);
-// dst[k] = P[idx[k]] (0 where idx[k] < 0) converted to kind (0 f64, 1 f32,
-// 2 bf16, 3 f16; the half forms round through FP32, to nearest even)
-void launch_param_gather(const double* P, const int32_t* idx, int64_t n, int kind, void* dst, hipStream_t s);
+// every map of the model: dst[k] = P[idx[k]] (0 where idx[k] < 0) converted to
+// kind (0 f64, 1 f32, 2 bf16, 3 f16; the half forms round through FP32, to
+// nearest even)
+void launch_param_gather(const dp_model* m, hipStream_t s);
 // writes one frame-table entry and clears a status word (kernel arguments
 // only: no host staging buffer)
 void launch_set_frame(FrameInfo* dst, const FrameInfo& F, int32_t* flags, hipStream_t s);
