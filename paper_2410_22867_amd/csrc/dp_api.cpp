@@ -1450,10 +1450,11 @@ int dp_ctx_copy_buffer(dp_ctx* c, int32_t which, void* dst, int64_t* nbytes, hip
   else {
     const int32_t md = c->mode_last == DP_FP64_TAB ? DP_FP64 : c->mode_last;
     // buffers the compute did not form: D on the FP64 path (built inside
-    // the GEMM), D and dE/dD with the fused half-precision first layer (which
-    // writes D only on contexts that keep the layer inputs for gradients)
+    // the GEMM), dE/dD where the first layer's backward is fused, D with the
+    // fused half-precision first layer (which writes D only on contexts that
+    // keep the layer inputs for gradients)
     if (which == 2 && (md == DP_FP64 || (fit1_fused(c, md) && !c->h_stored))) launch_descriptor_ex(c, md, true, stream);
-    if (which == 3 && fit1_fused(c, md)) launch_fit1_bwd_gemm(c, md, stream);
+    if (which == 3 && (fit1_fused(c, md) || fit1_bwd_fused64(c, md))) launch_fit1_bwd_gemm(c, md, stream);
     launch_gather_cols(c, which, md, (int32_t)n, (double*)dst, stream);
   }
   HIPCHECK(hipGetLastError());

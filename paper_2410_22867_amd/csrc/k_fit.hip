@@ -1092,6 +1092,110 @@ static void launch_pair_lp(dp_ctx* c, bool bwd, int mode, const PairArgsLp& p, h
   else launch_pair_lp_t<PrecF32, PrecF32>(bwd, grid, lds, p, fit_by_layer(c, mode), s);
 }
 
+// --------------------------- FP64 first layer backward with the descriptor's
+// g_T = d(dD . D)/dT straight from dz1: dD = W1 dz1 stays in registers instead
+// of going through memory (twice 1.3 GB at 98,304 atoms).  A work-group owns
+// 16 NT columns of one type, their dz1 in LDS; wave w takes an eighth of the
+// m1 rows a (m-tile a = dD[a][0..15]), so a weight fragment serves NT
+// products.  Lane (column n, group g) holds dD[a][g + 4 v] in element v: the
+// first term sums the lane's four elements against its T rows and the four
+// lane groups, the second accumulates dD[a][g + 4 v] T[a] over the wave's rows
+// and is added to the rows a < 16 wave by wave in a fixed order.
+struct Fit1Args64 {
+  const int32_t* meta;
+  const double* X;      // dz1 [cols][fw]
+  const double* T;
+  const double* Afr;
+  int64_t a_type_stride;
+  double* gT;
+  int m1;
+};
+
+template <int NT, int KS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fit1_bwd_f64(Fit1Args64 f) {
+  constexpr int NW = 8, NC = 16 * NT, fw = 16 * KS, ld = fw + 2;
+  constexpr int R = KS % 3 == 0 ? 3 : 4;  // weights R - 1 k-steps ahead
+  static_assert(KS % R == 0, "the ring's slots repeat every m-tile");
+  __shared__ __attribute__((aligned(32))) double dz[NC * ld];
+  __shared__ d4 low[NC][16];  // g_T rows a < 16
+  const int t = blockIdx.z;
+  const int n_t = f.meta[2 * t], cb = f.meta[2 * t + 1];
+  const int c0 = blockIdx.x * NC;
+  if (c0 >= n_t) return;
+  const int lane = threadIdx.x & 63, r16 = lane & 15, gq = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m1 = f.m1;
+  const int a_lo = m1 * wv / NW, a_hi = m1 * (wv + 1) / NW, last = (a_hi - a_lo) * KS - 1;
+  const double* A = f.Afr + t * f.a_type_stride + ((int64_t)a_lo * KS * 64 + lane) * 4;
+  d4 ar[R];
+  auto load = [&](int s) { return *reinterpret_cast<const d4*>(A + (int64_t)min(s, last) * 256); };
+  if (last >= 0) {
+#pragma unroll
+    for (int d = 0; d < R - 1; ++d) ar[d] = load(d);
+  }
+  for (int e = threadIdx.x; e < NC * fw / 4; e += 64 * NW) {
+    const int c = e / (fw / 4), k = 4 * (e - c * (fw / 4));
+    *reinterpret_cast<d4*>(dz + c * ld + k) = *reinterpret_cast<const d4*>(f.X + (int64_t)(cb + c0 + c) * fw + k);
+  }
+  const double* Tc[NT];
+  d4 Tlo[NT][4], q[NT][4];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    Tc[n] = f.T + ((int64_t)cb + c0 + 16 * n + r16) * m1 * 4;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      Tlo[n][v] = *reinterpret_cast<const d4*>(Tc[n] + (gq + 4 * v) * 4);
+      q[n][v] = d4{0.0, 0.0, 0.0, 0.0};
+    }
+  }
+  __syncthreads();
+  for (int a = a_lo, s = 0; a < a_hi; ++a, s += KS) {
+    d4 Ta[NT], acc[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      Ta[n] = *reinterpret_cast<const d4*>(Tc[n] + a * 4);
+      acc[n] = d4{0.0, 0.0, 0.0, 0.0};
+    }
+#pragma unroll
+    for (int S = 0; S < KS; ++S) {
+      ar[(S + R - 1) % R] = load(s + S + R - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      d4 x[NT];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) x[n] = *reinterpret_cast<const d4*>(dz + (16 * n + r16) * ld + 16 * S + 4 * gq);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[n] = mfma_f64(ar[S % R][v], x[n][v], acc[n]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      double p[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        p[k] = acc[n][0] * Tlo[n][0][k] + acc[n][1] * Tlo[n][1][k] + acc[n][2] * Tlo[n][2][k] + acc[n][3] * Tlo[n][3][k];
+      const double mine = swap_add16(swap_add32(p[0], p[2]), swap_add32(p[1], p[3]));  // component g
+      if (a < 16) reinterpret_cast<double*>(&low[16 * n + r16][a])[gq] = mine;
+      else f.gT[(((int64_t)cb + c0 + 16 * n + r16) * m1 + a) * 4 + gq] = mine;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) q[n][v] += acc[n][v] * Ta[n];
+    }
+  }
+  for (int h = 0; h < NW; ++h) {
+    __syncthreads();
+    if (wv == h) {
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) low[16 * n + r16][gq + 4 * v] += q[n][v];
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < NC * 16; e += 64 * NW)
+    *reinterpret_cast<d4*>(f.gT + (((int64_t)cb + c0 + (e >> 4)) * m1 + (e & 15)) * 4) = low[e >> 4][e & 15];
+}
+
 // ------------------------------------------- first fitting layer, few atoms
 // T (sum of the section partials), D and h1 = tanh(D W1 + b1) in one launch: a
 // work-group owns MT m-tiles of one 16-column tile, its waves share the
@@ -1996,8 +2100,36 @@ void launch_descriptor_ex(dp_ctx* c, int32_t mode, bool write_d, hipStream_t s) 
                        mix_kinds(mode).fit1 == 2 ? 1 : 0);
 }
 
+// One work-group fits a CU, so the last round of them counts in full: taken
+// when the rounds are at least 85 percent filled.  Product and descriptor
+// backward against the one launch (us): 98,304 atoms (12 rounds) 1,716 ->
+// 1,466, 24,576 (3) 422 -> 358, a batch of 23,700 432 -> 357, but 12,288 (1.5)
+// 232 -> 238.
+bool fit1_bwd_fused64(const dp_ctx* c, int32_t mode) {
+  const dp_model* m = c->model;
+  if (mode != DP_FP64 && mode != DP_FP64_TAB) return false;
+  if (m->m1 < 16 || (m->fw != 240 && m->fw != 256)) return false;
+  const int64_t wgs = (c->natoms_last + 31) / 32, rounds = (wgs + c->ncu - 1) / c->ncu;
+  return wgs > c->ncu && 20 * wgs >= 17 * rounds * c->ncu;
+}
+
+static void launch_fit1_bwd64(dp_ctx* c, hipStream_t s) {
+  const dp_model* m = c->model;
+  Fit1Args64 f;
+  f.meta = c->type_meta;
+  f.X = (const double*)c->fa[8];
+  f.T = (const double*)c->T;
+  f.Afr = (const double*)m->fit_frag64 + m->ffo.bwd[0];
+  f.a_type_stride = m->ffo.per_type;
+  f.gT = (double*)c->gT;
+  f.m1 = m->m1;
+  const dim3 grid((unsigned)((c->natoms_last + 31) / 32), 1, (unsigned)m->desc.ntypes);
+  if (m->fw == 240) hipLaunchKernelGGL((k_fit1_bwd_f64<2, 15>), grid, dim3(512), 0, s, f);
+  else hipLaunchKernelGGL((k_fit1_bwd_f64<2, 16>), grid, dim3(512), 0, s, f);
+}
+
 void launch_desc_bwd(dp_ctx* c, int32_t mode, hipStream_t s) {
-  if (fit1_fused(c, mode)) return;  // folded into the first layer's backward product
+  if (fit1_fused(c, mode) || fit1_bwd_fused64(c, mode)) return;  // folded into the first layer's backward product
   const dp_model* m = c->model;
   const int ncols = (int)(c->natoms_last + m->desc.ntypes * kColPad);
   if (c->natoms_last <= 0) return;
@@ -2148,6 +2280,7 @@ void launch_fit_backward(dp_ctx* c, int32_t mode, bool keep_dz2, hipStream_t s) 
   }
   // layer 1: dD = W1 dz1
   if (fit1_fused(c, mode)) launch_fit1_bwd(c, mode, s);
+  else if (fit1_bwd_fused64(c, mode)) launch_fit1_bwd64(c, s);
   else launch_fit1_bwd_gemm(c, mode, s);
 }
 

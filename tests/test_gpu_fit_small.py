@@ -72,3 +72,30 @@ def test_fit_by_layer_with_an_empty_type():
     o = oracle.compute(fr.coords, fr.types, fr.box, I.WATER, p)
     for m, r in _compute(fr, I.WATER, p, ["fp64", "mix_fp32"]).items():
         _check(o, r, m)
+
+
+@pytest.mark.parametrize("fit", [240, 256])
+def test_first_layer_backward_with_descriptor(fit):
+    """14,100 atoms: the first layer's backward product and the descriptor's in
+    one launch.  Energies and forces against the oracle on sampled atoms and
+    the sums, g_T against its definition from the dE/dD formed on request
+    (1e-11 of its largest entry, as for full frames)."""
+    from paper_2410_22867_amd import dpse
+    desc = dataclasses.replace(I.WATER, fit=(fit,) * 3)
+    p = I.init_params(desc, 100, I.WATER_OUTPUT_SCALE)
+    fr = I.water_box(4700, max(I.water_density_box(4700), 2.95 * 17), 43)
+    dev = torch.device("cuda:0")
+    ctx = dpse.Context(dpse.Model(desc, p), fr.n)
+    x, t = torch.tensor(fr.coords, device=dev), torch.tensor(fr.types, device=dev)
+    nl, _ = ctx.build_nlist(x, t, fr.box)
+    print("fused first layer backward", fit, fr.n, flush=True)
+    r = ctx.compute(x, t, fr.box, nl, mode="fp64")
+    o = oracle.compute(fr.coords, fr.types, fr.box, desc, p)
+    assert abs(float(r["E"][0]) - o["E"]) <= 1e-10 * abs(o["E"])
+    assert np.abs(r["F"].cpu().numpy() - o["F"]).max() <= 1e-9
+    T = ctx.copy_buffer(dpse.BUF_T).cpu().numpy().reshape(fr.n, desc.m1, 4)
+    gT = ctx.copy_buffer(dpse.BUF_GT).cpu().numpy().reshape(fr.n, desc.m1, 4)
+    gD = ctx.copy_buffer(dpse.BUF_GD).cpu().numpy().reshape(fr.n, desc.m1, 16)
+    ref = gD @ T[:, :16]
+    ref[:, :16] += gD.transpose(0, 2, 1) @ T
+    assert np.abs(gT - ref).max() <= 1e-11 * np.abs(ref).max()
