@@ -58,10 +58,6 @@ struct GemmArgs {
   void* part;
   int nsplit;
   int64_t part_cols;
-  // FP64, frames of few atoms: a one-dimensional grid over (weight slice,
-  // column tile) that keeps a slice's column tiles on one XCD (work-group b
-  // runs on XCD b % 8); xtiles: column tiles, yblocks: work-group rows per type
-  int xtiles, yblocks, ntypes;
 };
 
 // ---------------------------------------------------------------- FP64 GEMM
@@ -80,22 +76,15 @@ __device__ __forceinline__ d4 rows_of_lane(d4 a) {
 
 template <int MT, int NT, bool XT, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_fit_gemm_f64(GemmArgs g) {
-  int bx = blockIdx.x, by = blockIdx.y, t = blockIdx.z;
-  if (g.xtiles) {
-    const int j = blockIdx.x >> 3, w = (j / g.xtiles) * 8 + (blockIdx.x & 7);
-    bx = j % g.xtiles;
-    t = w / g.yblocks;
-    by = w - t * g.yblocks;
-    if (t >= g.ntypes) return;
-  }
+  const int t = blockIdx.z;
   const int n_t = g.meta[2 * t], cb = g.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
-  const int c0 = (bx * 4 + wv) * NT * 16;
+  const int c0 = (blockIdx.x * 4 + wv) * NT * 16;
   if (c0 >= n_t) return;
   const int mtiles = g.M / 16;
-  const int mb = SPLIT ? by / g.nsplit : by;
-  const int sp = SPLIT ? by - mb * g.nsplit : 0;
+  const int mb = SPLIT ? (int)blockIdx.y / g.nsplit : (int)blockIdx.y;
+  const int sp = SPLIT ? (int)blockIdx.y - mb * g.nsplit : 0;
   const int mt0 = mb * MT;
   const int KS = g.K / 16;
   // k-steps of this work-group: all of them, or one split's range
@@ -1092,6 +1081,56 @@ static void launch_pair_lp(dp_ctx* c, bool bwd, int mode, const PairArgsLp& p, h
   else launch_pair_lp_t<PrecF32, PrecF32>(bwd, grid, lds, p, fit_by_layer(c, mode), s);
 }
 
+// ------------------------- FP64 first layer backward, frames of few atoms
+// dD = W1 dz1 with the reduction (15 or 16 k-steps) shared by a work-group's
+// four waves, which own 2 x 2 tiles of 16 x 16 together: every operand of a
+// wave is requested before its first product, the partial sums meet in LDS,
+// and wave w writes tile w.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_fit_dd_f64(GemmArgs g) {
+  constexpr int KW = 4;  // k-steps per wave (fw <= 256)
+  __shared__ d4 red[4][4][64];
+  const int t = blockIdx.z;
+  const int n_t = g.meta[2 * t], cb = g.meta[2 * t + 1];
+  const int c0 = blockIdx.x * 32;
+  if (c0 >= n_t) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int r16 = lane & 15, gq = lane >> 4;
+  const int KS = g.K / 16, mtiles = g.M / 16, mt0 = 2 * blockIdx.y;
+  const double* A = reinterpret_cast<const double*>(g.Afr) + t * g.a_type_stride;
+  const double* X = reinterpret_cast<const double*>(g.X) + ((int64_t)cb + c0 + r16) * g.ldx + 4 * gq;
+  const int S0 = KS * wv / 4, S1 = KS * (wv + 1) / 4;
+  d4 a[KW][2], x[KW][2];
+#pragma unroll
+  for (int d = 0; d < KW; ++d) {
+    const int S = min(S0 + d, KS - 1);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      a[d][u] = *reinterpret_cast<const d4*>(A + (((int64_t)min(mt0 + u, mtiles - 1) * KS + S) * 64 + lane) * 4);
+      x[d][u] = *reinterpret_cast<const d4*>(X + (int64_t)16 * u * g.ldx + 16 * S);
+    }
+  }
+  d4 acc[2][2] = {};
+#pragma unroll
+  for (int d = 0; d < KW; ++d)
+    if (S0 + d < S1) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int n = 0; n < 2; ++n) acc[u][n] = mfma_f64(a[d][u][v], x[d][n][v], acc[u][n]);
+    }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) red[wv][2 * u + n][lane] = acc[u][n];
+  __syncthreads();
+  const int mt = mt0 + (wv >> 1), nt = wv & 1;
+  if (mt >= mtiles) return;
+  const d4 z = rows_of_lane((red[0][wv][lane] + red[1][wv][lane]) + (red[2][wv][lane] + red[3][wv][lane]));
+  *reinterpret_cast<d4*>(reinterpret_cast<double*>(g.out0) + ((int64_t)cb + c0 + 16 * nt + r16) * g.ld0 + 16 * mt + 4 * gq) = z;
+}
+
 // --------------------------- FP64 first layer backward with the descriptor's
 // g_T = d(dD . D)/dT straight from dz1: dD = W1 dz1 stays in registers instead
 // of going through memory (twice 1.3 GB at 98,304 atoms).  A work-group owns
@@ -1874,22 +1913,11 @@ static void gemm_launch_f64(dp_ctx* c, const GemmArgs& g0, hipStream_t s) {
   // (the partial sums' workspace is as wide as the fitting layers: the backward
   // product, which is wider, is never split)
   g.nsplit = g.T ? split_count_f64(c, unsplit_wgs(c, BN, mblocks), g.K / 16) : 1;
-  if (g.nsplit > 1) grid.y = (unsigned)(mblocks * g.nsplit);
-  // Few column tiles: each XCD's L2 reads its share of the weights (3 MB a
-  // type) instead of all of them, and all columns' inputs.  The backward
-  // product of 900 water atoms 43.2 -> 39.7 us, 450 atoms 34.8 -> 33.8, 1,500
-  // and 2,100 unchanged; with more columns their inputs are the larger part.
-  if (c->natoms_last <= 1280) {
-    g.xtiles = (int)grid.x;
-    g.yblocks = (int)grid.y;
-    g.ntypes = ntypes;
-    grid = dim3((unsigned)(((g.yblocks * ntypes + 7) / 8) * 8 * g.xtiles));
-  }
   if (g.nsplit > 1) {
+    grid.y = (unsigned)(mblocks * g.nsplit);
     g.part = c->split_part;
     g.part_cols = c->natoms_last + (int64_t)ntypes * kColPad;
-    if (g.T) hipLaunchKernelGGL((k_fit_gemm_f64<MT, NT, true, true>), grid, dim3(256), 0, s, g);
-    else hipLaunchKernelGGL((k_fit_gemm_f64<MT, NT, false, true>), grid, dim3(256), 0, s, g);
+    hipLaunchKernelGGL((k_fit_gemm_f64<MT, NT, true, true>), grid, dim3(256), 0, s, g);
     split_finish<double>(c, g, s);
     return;
   }
@@ -1940,9 +1968,13 @@ static void gemm_launch_lp(dp_ctx* c, const GemmArgs& g0, int kind, hipStream_t 
 // 2x2 per wave (64 x 64 per work-group).
 static void gemm_launch(dp_ctx* c, const GemmArgs& g, int mode, hipStream_t s) {
   if (mode != DP_FP64) gemm_launch_lp<2, 2>(c, g, mix_kinds(mode).fit1, s);
-  // backward product (never split): 16-feature rows while the 48-feature grid
-  // leaves CUs idle, 192 water atoms 17.1 -> 15.0 us, 900 46 -> 40
-  else if (!g.T && unsplit_wgs(c, 128, (g.M / 16 + 2) / 3) < c->ncu) gemm_launch_f64<1, 2>(c, g, s);
+  // backward product (us): 192 water atoms 14.9 -> 11.2, 450 34 -> 17, 900
+  // 39 -> 27, 864 copper atoms 29 -> 27, but 2,100 water atoms 44 -> 55 (the
+  // operands of every tile come from memory again)
+  else if (!g.T && c->natoms_last <= 1280) {
+    const dim3 grid((unsigned)((c->natoms_last + 31) / 32), (unsigned)((g.M / 16 + 1) / 2), (unsigned)c->model->desc.ntypes);
+    hipLaunchKernelGGL(k_fit_dd_f64, grid, dim3(256), 0, s, g);
+  }
   else gemm_launch_f64<3, 2>(c, g, s);
 }
 
