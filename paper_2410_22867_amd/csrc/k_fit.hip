@@ -7,7 +7,7 @@
 // Fitting activations are stored atom-major, [column][feature], one column
 // per centre atom, columns bucketed by centre type into segments padded to
 // kColPad.  A GEMM computes out[col][m] = epi(sum_k X[col][k] W[k][m]) for
-// all columns of every type (blockIdx.z), with the weight operand stored in
+// all columns of every type (column_tile), with the weight operand stored in
 // per-lane fragment order (A operand, features along M) and X as the B
 // operand: FP64 reads it straight from memory (lane n + 16g reads 4
 // consecutive features of its column); the half-precision GEMM stages it
@@ -21,11 +21,49 @@ namespace dpse {
 
 enum { EPI_TANH = 0, EPI_PLAIN = 1 };
 
+// The type t and first column c0 (within its segment) of this work-group's
+// column tile: the types' tiles one after another on a grid without a z
+// dimension, else tile blockIdx.x of type blockIdx.z; false past the last.
+__device__ __forceinline__ bool column_tile(const int32_t* meta, int width, int* t, int* c0) {
+  int b = blockIdx.x;
+  if (gridDim.z > 1) {
+    *t = blockIdx.z;
+    *c0 = b * width;
+    return *c0 < meta[2 * blockIdx.z];
+  }
+#pragma unroll
+  for (int u = 0; u < kMaxT; ++u) {
+    const int tiles = (meta[2 * u] + width - 1) / width;
+    if (b < tiles) {
+      *t = u;
+      *c0 = b * width;
+      return true;
+    }
+    b -= tiles;
+  }
+  return false;
+}
+// The grid for them.  With a row per type, each as long as all atoms' tiles,
+// half the work-groups of a two-type frame end at once, and the dispatcher then
+// puts two of the others on one CU beside idle ones: where there are few, one
+// row without gaps is taken (3,333 water atoms: FP64 hidden layers 43 + 38 ->
+// 29 + 25 us, BF16 first layer 18 + 14 -> 16 + 14; 12,288 FP64 hidden forward 86
+// -> 74).  Where the chip is full many times over the gaps cost nothing and the
+// types' tiles side by side are the better order (12,288 BF16 first layer 40 +
+// 32 us against 44 + 36).
+static dim3 type_grid(const dp_ctx* c, int width, int rows) {
+  return dim3((unsigned)((c->natoms_last + width - 1) / width), (unsigned)rows, (unsigned)c->model->desc.ntypes);
+}
+static dim3 column_grid(const dp_ctx* c, int width, int rows, bool gapless = false) {
+  const int64_t tiles = (c->natoms_last + width - 1) / width + c->model->desc.ntypes - 1;
+  return gapless || tiles * rows <= c->ncu ? dim3((unsigned)tiles, (unsigned)rows) : type_grid(c, width, rows);
+}
+
 // Whether the hidden layers 2 and 3 run one per launch (k_fit_layer_*)
 // instead of as pairs (k_fit_pair_*).  Both pair launches against all four
 // layer launches, water, fw = 240 (us):
 //   atoms            192          900          1,500        2,100
-//   FP64             49 -> 23     50 -> 44     51 -> 50     55 -> 65
+//   FP64             49 -> 23     50 -> 44     51 -> 50     49 -> 65
 //   16-bit           26 -> 22     29 -> 29     29 -> 30     30 -> 49
 //   FP32             46 -> 28     46 -> 38     46 -> 39     47 -> 49
 // (the pairs' time hardly depends on the atoms until every CU has a
@@ -234,10 +272,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
   constexpr int MW = 16 / NW;      // m-tile slots per wave (fw <= 256)
   constexpr int NC = 16 * NCT;    // columns of the work-group
   extern __shared__ double hs[];  // [NC][fw + 2]
-  const int t = blockIdx.z;
+  int t, c0;
+  if (!column_tile(p.meta, NC, &t, &c0)) return;
   const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
-  const int c0 = blockIdx.x * NC;
-  if (c0 >= n_t) return;
   const int lane = threadIdx.x & 63, r16 = lane & 15, gq = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int fw = p.fw, KS = fw / 16, mtiles = fw / 16, ldh = fw + 2;
@@ -409,10 +446,9 @@ __global__ __launch_bounds__(256) void k_fit_layer_f64(PairArgs p) {
   constexpr int KW = 4;  // k-steps of 16 per wave (fw <= 256)
   __shared__ d4 red[4][64];
   __shared__ double es[4][16];
-  const int t = blockIdx.z;
+  int t, c0;
+  if (!column_tile(p.meta, 16, &t, &c0)) return;
   const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
-  const int c0 = blockIdx.x * 16;
-  if (c0 >= n_t) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
   const int fw = p.fw, KS = fw / 16, mt = blockIdx.y;
@@ -494,7 +530,7 @@ __global__ __launch_bounds__(256) void k_fit_layer_f64(PairArgs p) {
 template <int NCT, int NW>
 static void launch_pair_f64_t(dp_ctx* c, bool bwd, const PairArgs& p, hipStream_t s) {
   const dp_model* m = c->model;
-  dim3 grid((unsigned)((c->natoms_last + 16 * NCT - 1) / (16 * NCT)), 1, (unsigned)m->desc.ntypes);
+  const dim3 grid = column_grid(c, 16 * NCT, 1, NCT == 1);
   const size_t lds = (size_t)16 * NCT * (m->fw + 2) * sizeof(double);
   if (grid.x == 0) return;
   if (bwd) hipLaunchKernelGGL((k_fit_pair_f64<true, NCT, NW>), grid, dim3(64 * NW), lds, s, p);
@@ -504,7 +540,7 @@ static void launch_pair_f64_t(dp_ctx* c, bool bwd, const PairArgs& p, hipStream_
 static void launch_pair_f64(dp_ctx* c, bool bwd, const PairArgs& p, hipStream_t s) {
   const int64_t wgs = (c->natoms_last + 15) / 16 + c->model->desc.ntypes - 1;
   if (fit_by_layer(c, DP_FP64)) {
-    const dim3 grid((unsigned)((c->natoms_last + 15) / 16), (unsigned)(p.fw / 16), (unsigned)c->model->desc.ntypes);
+    const dim3 grid = column_grid(c, 16, p.fw / 16);
     if (bwd) {
       hipLaunchKernelGGL((k_fit_layer_f64<true, false>), grid, dim3(256), 0, s, p);
       hipLaunchKernelGGL((k_fit_layer_f64<true, true>), grid, dim3(256), 0, s, p);
@@ -551,10 +587,9 @@ __global__ __launch_bounds__(256) void k_fit_gemm_lp(GemmArgs g) {
   typedef typename P::raw4 R4;
   __shared__ __attribute__((aligned(16))) ST as[2][MB * 512];
   __shared__ __attribute__((aligned(16))) ST xs[2][NB * 512];
-  const int t = blockIdx.z;
+  int t, c0;
+  if (!column_tile(g.meta, BN, &t, &c0)) return;
   const int n_t = g.meta[2 * t], cb = g.meta[2 * t + 1];
-  const int c0 = blockIdx.x * BN;
-  if (c0 >= n_t) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wv = tid >> 6;
   const int wm = wv >> 1, wn = wv & 1;
@@ -729,10 +764,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
   // forward: FP32 tile [NC][fwp + 4]; backward: tile of ST [NC][fwp + 8]
   extern __shared__ __attribute__((aligned(16))) float hsf[];
   ST* const hsh = reinterpret_cast<ST*>(hsf);
-  const int t = blockIdx.z;
+  int t, c0;
+  if (!column_tile(p.meta, NC, &t, &c0)) return;
   const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
-  const int c0 = blockIdx.x * NC;
-  if (c0 >= n_t) return;
   const int lane = threadIdx.x & 63, r16 = lane & 15, gq = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fw = p.fw, fwp = p.fwp, KT = fwp / 32, mtiles = fw / 16;
@@ -943,13 +977,13 @@ __global__ __launch_bounds__(256) void k_fit_layer_lp(PairArgsLp p) {
   typedef typename P::store_t ST;
   typedef typename P::raw8 R8;
   typedef typename P::raw4 R4;
-  const int t = blockIdx.z;
-  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
-  const int c0 = blockIdx.x * 16;
+  int t, c0;
+  if (!column_tile(p.meta, 16, &t, &c0)) return;
+  const int cb = p.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, r16 = lane & 15, gq = lane >> 4;
   const int fw = p.fw, fwp = p.fwp, KT = fwp / 32;
   const int mt = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (c0 >= n_t || mt >= fw / 16) return;
+  if (mt >= fw / 16) return;
   const float* vec = p.vec + t * p.vec_type_stride;
   const ST* A = reinterpret_cast<const ST*>(p.A[SECOND ? 1 : 0]) + t * p.a_type_stride;
   const int64_t col = (int64_t)cb + c0 + r16;
@@ -1071,7 +1105,7 @@ static void launch_pair_lp(dp_ctx* c, bool bwd, int mode, const PairArgsLp& p, h
   const dp_model* m = c->model;
   const MixKinds mk = mix_kinds(mode);
   constexpr int NC = 16 * kPairNCT;
-  dim3 grid((unsigned)((c->natoms_last + NC - 1) / NC), 1, (unsigned)m->desc.ntypes);
+  const dim3 grid = column_grid(c, NC, 1);
   const size_t esz = mk.fit23 == 3 ? 4 : 2;
   const size_t lds = bwd ? (size_t)NC * (p.fwp + 8) * esz : (size_t)NC * (p.fwp + 4) * 4;
   if (grid.x == 0) return;
@@ -1089,10 +1123,9 @@ static void launch_pair_lp(dp_ctx* c, bool bwd, int mode, const PairArgsLp& p, h
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_fit_dd_f64(GemmArgs g) {
   constexpr int KW = 4;  // k-steps per wave (fw <= 256)
   __shared__ d4 red[4][4][64];
-  const int t = blockIdx.z;
+  int t, c0;
+  if (!column_tile(g.meta, 32, &t, &c0)) return;
   const int n_t = g.meta[2 * t], cb = g.meta[2 * t + 1];
-  const int c0 = blockIdx.x * 32;
-  if (c0 >= n_t) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
   const int KS = g.K / 16, mtiles = g.M / 16, mt0 = 2 * blockIdx.y;
@@ -1297,10 +1330,9 @@ template <int MT>
 __global__ __launch_bounds__(kFirstThreads) void k_fit_first_f64(FirstArgs p) {
   constexpr int NW = 16, R = MT == 1 ? 4 : 2;
   __shared__ __attribute__((aligned(32))) double lds_first[4 * (MT * NW * 64 > kFirstT ? MT * NW * 64 : kFirstT)];  // T, then the partial sums
-  const int t = blockIdx.z;
+  int t, c0;
+  if (!column_tile(p.meta, 16, &t, &c0)) return;
   const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
-  const int c0 = blockIdx.x * 16;
-  if (c0 >= n_t) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
   const int KS = p.m1, mtiles = p.M / 16, mt0 = blockIdx.y * MT;
@@ -1370,10 +1402,9 @@ __global__ __launch_bounds__(kFirstThreadsLp) void k_fit_first_lp(FirstArgs p) {
   typedef typename P::raw4 R4;
   __shared__ __attribute__((aligned(16))) float lds_first_lp[4 * kFirstT];  // T, then the partial sums
   static_assert(kFirstT >= kSplitMax * 64, "the partial sums fit");
-  const int t = blockIdx.z;
+  int t, c0;
+  if (!column_tile(p.meta, 16, &t, &c0)) return;
   const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
-  const int c0 = blockIdx.x * 16;
-  if (c0 >= n_t) return;
   const int lane = threadIdx.x & 63, sp = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
   const int KT = p.m1 / 2, mt = blockIdx.y;
@@ -1907,7 +1938,7 @@ static void gemm_launch_f64(dp_ctx* c, const GemmArgs& g0, hipStream_t s) {
   const int BN = 4 * NT * 16;
   const int mtiles = g0.M / 16;
   const int mblocks = (mtiles + MT - 1) / MT;
-  dim3 grid((unsigned)((c->natoms_last + BN - 1) / BN), (unsigned)mblocks, (unsigned)ntypes);
+  dim3 grid = type_grid(c, BN, mblocks);
   if (grid.x == 0) return;
   GemmArgs g = g0;
   // (the partial sums' workspace is as wide as the fitting layers: the backward
@@ -1944,7 +1975,7 @@ static void gemm_launch_lp(dp_ctx* c, const GemmArgs& g0, int kind, hipStream_t 
   const int BN = 32 * NTW;
   const int mtiles = g0.M / 16;
   const int mblocks = (mtiles + 2 * MTW - 1) / (2 * MTW);
-  dim3 grid((unsigned)((c->natoms_last + BN - 1) / BN), (unsigned)mblocks, (unsigned)ntypes);
+  dim3 grid = column_grid(c, BN, mblocks);
   if (grid.x == 0) return;
   GemmArgs g = g0;
   g.nsplit = split_count(c, unsplit_wgs(c, BN, mblocks), g.K / 32);
@@ -1972,7 +2003,7 @@ static void gemm_launch(dp_ctx* c, const GemmArgs& g, int mode, hipStream_t s) {
   // 39 -> 27, 864 copper atoms 29 -> 27, but 2,100 water atoms 44 -> 55 (the
   // operands of every tile come from memory again)
   else if (!g.T && c->natoms_last <= 1280) {
-    const dim3 grid((unsigned)((c->natoms_last + 31) / 32), (unsigned)((g.M / 16 + 1) / 2), (unsigned)c->model->desc.ntypes);
+    const dim3 grid = column_grid(c, 32, (g.M / 16 + 1) / 2);
     hipLaunchKernelGGL(k_fit_dd_f64, grid, dim3(256), 0, s, g);
   }
   else gemm_launch_f64<3, 2>(c, g, s);
@@ -2030,7 +2061,7 @@ static void launch_fit1_fwd(dp_ctx* c, int32_t mode, bool write_d, hipStream_t s
   f.D = write_d ? c->D : nullptr;
   f.X = c->fa[0];
   constexpr int NB = 2, NW = 4;
-  dim3 grid((unsigned)((c->natoms_last + 16 * NB - 1) / (16 * NB)), 1, (unsigned)c->model->desc.ntypes);
+  const dim3 grid = type_grid(c, 16 * NB, 1);
   if (mix_kinds(mode).fit1 == 1) hipLaunchKernelGGL((k_fit1_fwd_lp<PrecBF16, NB, NW, 4>), grid, dim3(64 * NW), 0, s, f);
   else hipLaunchKernelGGL((k_fit1_fwd_lp<PrecF16, NB, NW, 4>), grid, dim3(64 * NW), 0, s, f);
 }
@@ -2041,7 +2072,7 @@ static void launch_fit1_bwd(dp_ctx* c, int32_t mode, hipStream_t s) {
   constexpr int NT = 2, NCG = 1, RING = 2, CW = 16 * NT * NCG;
   Fit1Args f = fit1_base(c, mode, true);
   f.X = c->fa[9];
-  dim3 grid((unsigned)((c->natoms_last + CW - 1) / CW), 1, (unsigned)c->model->desc.ntypes);
+  const dim3 grid = type_grid(c, CW, 1);
   if (mix_kinds(mode).fit1 == 1) hipLaunchKernelGGL((k_fit1_bwd_lp<PrecBF16, NT, NCG, 8, RING>), grid, dim3(256 * NCG), 0, s, f);
   else hipLaunchKernelGGL((k_fit1_bwd_lp<PrecF16, NT, NCG, 8, RING>), grid, dim3(256 * NCG), 0, s, f);
 }
@@ -2067,7 +2098,7 @@ static bool fit_first(const dp_ctx* c, int32_t mode) {
 
 template <int MT>
 static void launch_first_f64(dp_ctx* c, const FirstArgs& p, hipStream_t s) {
-  const dim3 grid((unsigned)((c->natoms_last + 15) / 16), (unsigned)((p.M / 16 + MT - 1) / MT), (unsigned)p.ntypes);
+  const dim3 grid = column_grid(c, 16, (p.M / 16 + MT - 1) / MT);
   hipLaunchKernelGGL((k_fit_first_f64<MT>), grid, dim3(kFirstThreads), 0, s, p);
 }
 
@@ -2103,7 +2134,7 @@ static void launch_first(dp_ctx* c, int32_t mode, hipStream_t s) {
   p.vec = m->fit_vec32;
   p.ld = ((m->fw + 31) / 32) * 32;
   p.nsplit = first_splits_lp(c);
-  const dim3 grid((unsigned)((c->natoms_last + 15) / 16), (unsigned)(p.M / 16), (unsigned)p.ntypes), wg(kFirstThreadsLp);
+  const dim3 grid = column_grid(c, 16, p.M / 16), wg(kFirstThreadsLp);
   if (kind == 1) hipLaunchKernelGGL((k_fit_first_lp<PrecBF16>), grid, wg, 0, s, p);
   else if (kind == 2) hipLaunchKernelGGL((k_fit_first_lp<PrecF16>), grid, wg, 0, s, p);
   else hipLaunchKernelGGL((k_fit_first_lp<PrecF32>), grid, wg, 0, s, p);
@@ -2155,7 +2186,7 @@ static void launch_fit1_bwd64(dp_ctx* c, hipStream_t s) {
   f.a_type_stride = m->ffo.per_type;
   f.gT = (double*)c->gT;
   f.m1 = m->m1;
-  const dim3 grid((unsigned)((c->natoms_last + 31) / 32), 1, (unsigned)m->desc.ntypes);
+  const dim3 grid = type_grid(c, 32, 1);
   if (m->fw == 240) hipLaunchKernelGGL((k_fit1_bwd_f64<2, 15>), grid, dim3(512), 0, s, f);
   else hipLaunchKernelGGL((k_fit1_bwd_f64<2, 16>), grid, dim3(512), 0, s, f);
 }
