@@ -62,15 +62,16 @@ static dim3 column_grid(const dp_ctx* c, int width, int rows, bool gapless = fal
 // Whether the hidden layers 2 and 3 run one per launch (k_fit_layer_*)
 // instead of as pairs (k_fit_pair_*).  Both pair launches against all four
 // layer launches, water, fw = 240 (us):
-//   atoms            192          900          1,500        2,100
-//   FP64             49 -> 23     50 -> 44     51 -> 50     49 -> 65
-//   16-bit           26 -> 22     29 -> 29     29 -> 30     30 -> 49
-//   FP32             46 -> 28     46 -> 38     46 -> 39     47 -> 49
+//   atoms            192          450          900          1,200 - 1,260  1,500
+//   FP64             49 -> 23                  45 -> 43     45.6 -> 45.8   46 -> 50
+//   16-bit                        21.6 -> 20   22.8 -> 22.6
+//   FP32                                       34 -> 30     34 -> 37       34 -> 38
+// and the step of 192 atoms 101.8 -> 100.9 (BF16), 125.8 -> 120.3 (MIX-fp32)
 // (the pairs' time hardly depends on the atoms until every CU has a
 // work-group, the layers' is their products and a launch each).
 static bool fit_by_layer(const dp_ctx* c, int32_t mode) {
   const int kind = mode == DP_FP64 ? 0 : mix_kinds(mode).fit23;
-  return c->natoms_last <= (kind == 0 ? 1280 : kind == 3 ? 1792 : 640);
+  return c->natoms_last <= (kind == 0 ? 1280 : kind == 3 ? 1024 : 640);
 }
 
 struct GemmArgs {

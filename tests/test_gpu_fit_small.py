@@ -1,7 +1,7 @@
 """Fitting layers one per launch, the first layer in one launch with the
 descriptor and the split first layer, on each side of the atom counts where
 the route changes (water: hidden layers 1,280 atoms FP64, 640 in the 16-bit
-forms, 1,792 FP32; first layer 272 and 1,792, 768, 1,280), at the narrowest and widest fitting nets, and with
+forms, 1,024 FP32; first layer 272 and 1,792, 768, 1,280), at the narrowest and widest fitting nets, and with
 one type empty.  Bars: FP64 as for full frames, mixed forms the relative RMS
 force bars of the other nets."""
 import dataclasses
@@ -50,6 +50,7 @@ def _check(o, r, mode):
     (64, 256, ["fp64", "bf16", "mix_fp32", "mix_fp16"]),
     (85, 240, ["fp64", "bf16"]), (86, 240, ["fp64"]),
     (213, 240, ["bf16", "mix_fp16"]), (214, 240, ["bf16", "mix_fp16"]),
+    (341, 240, ["mix_fp32"]), (342, 240, ["mix_fp32"]),
     (256, 240, ["bf16", "mix_fp16"]), (257, 240, ["bf16", "mix_fp16"]),
     (426, 240, ["fp64", "mix_fp32"]), (427, 240, ["fp64", "mix_fp32"]), (427, 256, ["fp64"]),
     (597, 240, ["fp64", "mix_fp32"]), (598, 240, ["fp64", "mix_fp32"]),
