@@ -1148,7 +1148,7 @@ int dp_ctx_create(const dp_model* m, int64_t max_atoms, int32_t max_frames, int6
   ALLOC(c->col_of, N);
   ALLOC(c->atom_at, C);
   ALLOC(c->frame_of, N);
-  ALLOC(c->emb_ctr, (int64_t)kMaxT * kMaxT * 3 * c->ncu * 32);
+  ALLOC(c->emb_ctr, (int64_t)m->desc.ntypes * m->desc.ntypes * kEmbPerCu * c->ncu * 32);
   ALLOC(c->R, N * nm * 4);
   ALLOC(c->nnei, N * kMaxT);
   ALLOC(c->netd, N * nm * 4);

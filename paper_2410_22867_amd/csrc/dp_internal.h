@@ -18,6 +18,10 @@ constexpr int kCandCap = 512;    // neighbour candidates inside r_c per atom (LD
 constexpr int kMaxNm = 1024;     // sum(sel)
 constexpr int kTanhLutEntries = 2496;  // tanh(k / 128) for |x| up to 19.5
 constexpr int kRedChunk = 256;  // atoms per partial sum of the per-frame reductions
+// Work-groups per CU of the embedding kernels (and of their tabulated and
+// gradient forms) at most, in each grid row; a grid has at most one row per
+// net, and each of its work-groups a column counter (dp_ctx::emb_ctr)
+constexpr int kEmbPerCu = 4;
 
 // Slot layout of the embedding activations (see k_embed.hip): widths
 // (w, 2w, 4w) with w <= 32 occupy 32, 64 and 128 slots.
@@ -208,7 +212,7 @@ struct dp_ctx {
   int32_t* atom_at;        // [max_cols]
   int32_t* frame_of;       // [max_atoms]
   int32_t ncu;             // compute units of the device
-  int32_t* emb_ctr;        // [nets][3 ncu][32] next-column counter of each embedding work-group (one per 128-byte line)
+  int32_t* emb_ctr;        // [nets][kEmbPerCu ncu][32] next-column counter of each embedding work-group (one per 128-byte line)
   // compute buffers
   double* R;               // [N, nm, 4] f64
   int32_t* nnei;           // [N, kMaxT]

@@ -1097,7 +1097,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(4))) v
 
 // ============================================================== launchers
 // FP64 kernels run 2 waves per SIMD: 8-wave work-groups share one LDS copy
-// of the net's fragments.  The mixed kernels fit 3 work-groups of 4 waves.
+// of the net's fragments.  The mixed kernels: see launch_embed.
 constexpr int kWPB64 = 8, kWPBlp = 4;
 
 static EmbArgs emb_args(dp_ctx* c, int32_t mode) {
@@ -1190,7 +1190,7 @@ static void launch_embed(dp_ctx* c, int32_t mode, bool bwd, hipStream_t s) {
   const int kind = mode == DP_FP64 ? 0 : mix_kinds(mode).emb;
   const int wpb = mode == DP_FP64 ? kWPB64 : (bwd ? (kind == 3 ? 16 : 8) : (kind == 3 ? 8 : kWPBlp));
   EmbArgs A = emb_args(c, mode);
-  const int per_cu = mode == DP_FP64 ? 1 : (kind == 3 ? (bwd ? 1 : 2) : (bwd ? 2 : 4));
+  const int per_cu = mode == DP_FP64 ? 1 : (kind == 3 ? (bwd ? 1 : 2) : (bwd ? 2 : kEmbPerCu));
   const int nnets = A.ntypes * A.ntypes;
   // one-row grid for the FP64 kernels and the FP32 form's backward (water12k:
   // FP64 forward 547 -> 516 us, backward with stored activations 589 -> 561

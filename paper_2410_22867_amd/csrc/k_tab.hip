@@ -481,6 +481,7 @@ void launch_embed_tab(dp_ctx* c, bool bwd, hipStream_t s) {
   const int64_t columns = c->natoms_last * A.ntypes;
   const int wpb = columns >= (int64_t)c->ncu * 10 ? 16 : 4;
   const int64_t need = (columns + wpb - 1) / wpb, res = (int64_t)c->ncu * (wpb == 16 ? 1 : 3);
+  static_assert(kEmbPerCu >= 3, "a column counter per work-group");
   const int64_t groups = need < res ? need : res;
   dim3 grid((unsigned)(groups > nnets ? groups : nnets), 1);
   if (m->m1 == 100) launch_tab<100>(bwd, wpb, grid, A, s);
