@@ -470,6 +470,7 @@ int build_maps(dp_model* m) {
   int nup = 0;
   m->n_maps = 0;
   for (const Target& t : tg) {
+    if (w == 25 && (t.map == &ev || t.map == &e64)) continue;  // read by the 32-wide gradient only
     int32_t* idx = nullptr;
     for (int k = 0; k < nup; ++k)
       if (uploaded[k] == t.map) idx = uploaded_dev[k];

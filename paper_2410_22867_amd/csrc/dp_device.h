@@ -296,7 +296,8 @@ __device__ __forceinline__ double tanh_d_tab(double x, const double* tab) {
 // |y| <= 2^-8 and (1 - y)(1 + y^2)(1 + y^4) for 2^-7 (remainders y^6, y^8,
 // times (1 - T^2) u below 1e-17).  No division, no exponential: 16 (18) FP64
 // instructions where tanh_d_tab needs 19 and a reciprocal that costs four.
-// Absolute error below 1.3e-16, relative accuracy kept for small |x|.
+// Absolute error below 1.3e-16, relative accuracy kept for small |x|.  A NaN
+// argument takes the clamp's value and gives +-1 (callers as for tanh_d).
 template <int LOG>
 __device__ __forceinline__ double tanh_lut(double x, const double* tab) {
   constexpr double magic = 1.5 * (double)(1ull << (52 - LOG));

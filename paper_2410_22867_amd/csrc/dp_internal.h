@@ -129,12 +129,12 @@ struct dp_model {
   float* emb_vec32;
   int64_t emb_vec_per_net;   // = 32+32+64+128+128
   double* emb_frag64;
-  // the FP64 force kernels' copies in the denser width-2w layout (w = 25;
-  // the same as the plain ones otherwise); the gradient kernels and the
-  // mixed kernels use the plain layout
+  // the FP64 kernels' copies in the denser width-2w layout (w = 25) and
+  // compact blocks; emb_vec64 and emb_frag64 are the plain layout in FP64,
+  // which the 32-wide gradient kernel reads (NULL for w = 25)
   double* emb_vec64d;
   double* emb_frag64d;
-  double* tanh_lut;          // tanh(k / 128), k < kTanhLut (the FP64 force kernels' table)
+  double* tanh_lut;          // tanh(k / 128), k < kTanhLutEntries (the FP64 kernels' table)
   uint16_t* emb_frag_bf16;
   uint16_t* emb_frag_f16;
   float* emb_frag_f32;

@@ -275,7 +275,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
   extern __shared__ double hs[];  // [NC][fw + 2]
   int t, c0;
   if (!column_tile(p.meta, NC, &t, &c0)) return;
-  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int cb = p.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, r16 = lane & 15, gq = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int fw = p.fw, KS = fw / 16, mtiles = fw / 16, ldh = fw + 2;
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(256) void k_fit_layer_f64(PairArgs p) {
   __shared__ double es[4][16];
   int t, c0;
   if (!column_tile(p.meta, 16, &t, &c0)) return;
-  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int cb = p.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
   const int fw = p.fw, KS = fw / 16, mt = blockIdx.y;
@@ -767,7 +767,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
   ST* const hsh = reinterpret_cast<ST*>(hsf);
   int t, c0;
   if (!column_tile(p.meta, NC, &t, &c0)) return;
-  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int cb = p.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, r16 = lane & 15, gq = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fw = p.fw, fwp = p.fwp, KT = fwp / 32, mtiles = fw / 16;
@@ -971,7 +971,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCT > 1 ? 2
 
 // The mixed layers one per launch (as k_fit_layer_f64): wave w of a work-group
 // owns m-tile 4 blockIdx.y + w of a column tile over the whole reduction, in
-// the pair kernel's order of products, so its results are the same bits.
+// the pair kernel's order of products, so activations and deltas are the same
+// bits.  E_i is summed in another order (m-tiles one after another instead of
+// 16 strided sums in a tree; FP64 in both).
 template <class P, class PO, bool BWD, bool SECOND>
 __global__ __launch_bounds__(256) void k_fit_layer_lp(PairArgsLp p) {
   constexpr int KM = 8;  // 32-wide k-steps (fw <= 256)
@@ -1126,7 +1128,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ d4 red[4][4][64];
   int t, c0;
   if (!column_tile(g.meta, 32, &t, &c0)) return;
-  const int n_t = g.meta[2 * t], cb = g.meta[2 * t + 1];
+  const int cb = g.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
   const int KS = g.K / 16, mtiles = g.M / 16, mt0 = 2 * blockIdx.y;
@@ -1292,7 +1294,8 @@ struct FirstArgs {
   int64_t ld;
 };
 
-constexpr int kFirstT = 16 * 129;  // T rows of a tile, m1 <= 128
+constexpr int kFit1MaxM1 = 128;               // LDS copies of T hold rows of this width at most
+constexpr int kFirstT = 16 * (kFit1MaxM1 + 1);  // T rows of a tile
 constexpr int kFirstThreads = 1024, kFirstThreadsLp = 512;
 // Section sum of the tile's T rows into LDS ([16][m1 + 1][4]); zeros on
 // padding columns.  A thread's rows of the first two sections are requested
@@ -1333,7 +1336,7 @@ __global__ __launch_bounds__(kFirstThreads) void k_fit_first_f64(FirstArgs p) {
   __shared__ __attribute__((aligned(32))) double lds_first[4 * (MT * NW * 64 > kFirstT ? MT * NW * 64 : kFirstT)];  // T, then the partial sums
   int t, c0;
   if (!column_tile(p.meta, 16, &t, &c0)) return;
-  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int cb = p.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
   const int KS = p.m1, mtiles = p.M / 16, mt0 = blockIdx.y * MT;
@@ -1403,9 +1406,11 @@ __global__ __launch_bounds__(kFirstThreadsLp) void k_fit_first_lp(FirstArgs p) {
   typedef typename P::raw4 R4;
   __shared__ __attribute__((aligned(16))) float lds_first_lp[4 * kFirstT];  // T, then the partial sums
   static_assert(kFirstT >= kSplitMax * 64, "the partial sums fit");
+  // (split_count: eight 32-wide k-steps of the m1 x 16 descriptor at least in each)
+  static_assert(kFit1MaxM1 * 16 / 32 / 8 <= kFirstThreadsLp / 64, "a wave for every split");
   int t, c0;
   if (!column_tile(p.meta, 16, &t, &c0)) return;
-  const int n_t = p.meta[2 * t], cb = p.meta[2 * t + 1];
+  const int cb = p.meta[2 * t + 1];
   const int lane = threadIdx.x & 63, sp = threadIdx.x >> 6;
   const int r16 = lane & 15, gq = lane >> 4;
   const int KT = p.m1 / 2, mt = blockIdx.y;
@@ -1475,8 +1480,6 @@ __global__ __launch_bounds__(kFirstThreadsLp) void k_fit_first_lp(FirstArgs p) {
 // k = 32 kt + 16 (j / 4) + 4 g + j % 4), so a lane of a D fragment always
 // holds b = 4 g .. 4 g + 3 and a = 2 kt + j / 4: the four T rows b are kept
 // in registers and one row a is read per step.
-constexpr int kFit1MaxM1 = 128;  // LDS copy of T: 16 B per column and row
-
 struct Fit1Args {
   const int32_t* meta;   // n_t, cbase_t per centre type
   const float* Tpart;    // forward: [sections][cols][m1][4] partial T
