@@ -145,8 +145,10 @@ int dp_model_set_params(dp_model* model, const double* params_host, int64_t n_pa
 /* The same from device FP64 parameters [n_params], asynchronously on
  * `stream` (a copy into the model, then the gathers): no allocation, no host
  * wait, so a training loop can update the model every step.  Values are not
- * checked on the host; non-finite parameters give non-finite energies, which
- * the computes flag with DP_FLAG_NONFINITE. */
+ * checked: a NaN among them makes the mixed forms' energies NaN, which the
+ * computes flag with DP_FLAG_NONFINITE; in the FP64 forms, whose tanh is finite
+ * for every argument, and for infinities in every form, only output weights,
+ * output biases and e_bias are sure to.  dp_model_set_params checks. */
 int dp_model_set_params_device(dp_model* model, const double* params_dev, int64_t n_params, hipStream_t stream);
 int dp_model_destroy(dp_model* model);
 
@@ -285,7 +287,9 @@ int dp_compute_batch(dp_ctx* ctx, const double* coords, const int32_t* types, co
  * g_T of its half-precision passes are used (widened to FP64 for the
  * weight-gradient reductions; the embedding nets are re-evaluated in FP64),
  * so the result is the mixed model's gradient to mixed-precision accuracy.
- * Gradients are accumulated with atomics (summation order not fixed). */
+ * The fitting nets' sums have a fixed order; the embedding nets' depends on
+ * which wavefront took which atoms, so their last bits may differ from call to
+ * call. */
 int dp_backward_params(dp_ctx* ctx, const double* dL_dE, double* grad_params, hipStream_t stream);
 
 /* Velocity-Verlet halves (FP64; Evaluation section time steps).
@@ -321,10 +325,10 @@ int dp_ctx_store_info(dp_ctx* ctx, int64_t* capacity_bytes, int32_t* last_used);
  *        3 = dE/dD [n, m1*m2] f64 (atom order);
  *        4 = net_deriv = dE/dR~ [n, nm, 4] f64 (atom order);
  *        5 = g_T = dE/dT [n, m1, 4] f64 (atom order; FP32 in mixed modes).
- * Where the compute folded D and dE/dD into the first fitting layer (the
- * BF16 / FP16 first layer on frames of many atoms) they are formed on
- * request from the compute's T and dz1 by the plain descriptor and GEMM
- * passes.  Copies into dst (device, caller-owned, at least the stated size)
+ * Where the compute folded D (FP64) or dE/dD (FP64 on frames of many atoms)
+ * or both (the BF16 / FP16 first layer on frames of many atoms) into the first
+ * fitting layer, they are formed on request from the compute's T and dz1 by the
+ * plain descriptor and GEMM passes.  Copies into dst (device, caller-owned, at least the stated size)
  * on stream; *nbytes receives the size. */
 int dp_ctx_copy_buffer(dp_ctx* ctx, int32_t which, void* dst, int64_t* nbytes, hipStream_t stream);
 

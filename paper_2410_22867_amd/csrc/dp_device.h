@@ -228,9 +228,9 @@ __device__ __forceinline__ int part_start(int n, int g, int G) { return (int)((d
 // q + q (r + r^2) leaves r^3 ~ 1e-22 (two Newton steps would cost one more
 // instruction and round twice).  Absolute error below 5e-16 (about 2 ulp
 // of 1); relative accuracy is lost only for |x| below ~1e-3, where the
-// absolute error still is ~1e-16.  A NaN argument gives +-0: every caller's
-// arguments derive from coordinates checked by the wrap test and parameters
-// checked finite when the model is created.
+// absolute error still is ~1e-16.  A NaN argument gives +-0: coordinates are
+// checked by the wrap test and parameters from the host for being finite, those
+// loaded from the device are not.
 __device__ __forceinline__ double tanh_d(double x) {
   const double u = __builtin_fmin(__builtin_fmax(__builtin_fabs(x) * 0.03125, 0.0), 1.0);
   const double n = rint(u * -92.33248261689366);  // -64/ln2

@@ -69,9 +69,24 @@ static dim3 column_grid(const dp_ctx* c, int width, int rows, bool gapless = fal
 // and the step of 192 atoms 101.8 -> 100.9 (BF16), 125.8 -> 120.3 (MIX-fp32)
 // (the pairs' time hardly depends on the atoms until every CU has a
 // work-group, the layers' is their products and a launch each).
+// Narrower layers: the pairs' serial chain shortens with the width, the two
+// launches more do not.  Whole compute with the layers one per launch less that
+// with the pairs (us), water:
+//   width               16     64     96    128    160    192    240    256
+//   FP64     192      +3.9   -0.4   -4.3   -8.5  -12.1  -15.0  -23.2  -23.8
+//            768      +3.0   -1.5   -0.7   -3.5   -7.3   -5.7   -8.6   -9.3
+//            990      +3.3   -0.7   +4.7   +6.1   +6.7   +4.8   -1.8   -4.1
+//            1,260    +4.5   +9.4   +6.2   +8.8   +8.1   +4.9   -0.1   +2.5
+//   16-bit   192      +4.7   +9.1   +7.4   +7.7   +5.4   +3.8   -0.1   -0.8
+//            630      +3.9   +9.6   +6.8   +7.0   +4.3   +3.2   -0.3   -1.1
+//   FP32     192      +4.9   +8.5   +7.1   +3.2   +0.6   -1.8   -6.1   -5.8
+//            990      +5.2   +8.3   +6.6   +2.8   +0.1   -2.0   -4.2   -5.0
+// (copper of 864 atoms, FP64 128-wide -4.8; three types, 240-wide, as two)
 static bool fit_by_layer(const dp_ctx* c, int32_t mode) {
-  const int kind = mode == DP_FP64 ? 0 : mix_kinds(mode).fit23;
-  return c->natoms_last <= (kind == 0 ? 1280 : kind == 3 ? 1024 : 640);
+  const int kind = mode == DP_FP64 ? 0 : mix_kinds(mode).fit23, fw = c->model->fw;
+  if (kind == 0) return c->natoms_last <= (fw > 224 ? 1280 : fw >= 64 ? 896 : 0);
+  if (kind == 3) return fw >= 192 && c->natoms_last <= 1024;
+  return fw > 224 && c->natoms_last <= 640;
 }
 
 struct GemmArgs {
@@ -2005,8 +2020,12 @@ static void gemm_launch(dp_ctx* c, const GemmArgs& g, int mode, hipStream_t s) {
   if (mode != DP_FP64) gemm_launch_lp<2, 2>(c, g, mix_kinds(mode).fit1, s);
   // backward product (us): 192 water atoms 14.9 -> 11.2, 450 34 -> 17, 900
   // 39 -> 27, 864 copper atoms 29 -> 27, but 2,100 water atoms 44 -> 55 (the
-  // operands of every tile come from memory again)
-  else if (!g.T && c->natoms_last <= 1280) {
+  // operands of every tile come from memory again).  A short reduction leaves
+  // little to share: whole compute less that with the plain product, at 192 /
+  // 450 / 990 / 1,260 water atoms, 240-wide -6 / -10 / -8 / -4 us, 192-wide
+  // -4 / -8 / -4 / +1, 160-wide -3 / -6 / -2 / +2 (768: +7), 128-wide -2 / -3 /
+  // +3 / +6, 64-wide 0 / 0 / +8 / +13
+  else if (!g.T && c->model->fw >= 192 && c->natoms_last <= 1280) {
     const dim3 grid = column_grid(c, 32, (g.M / 16 + 1) / 2);
     hipLaunchKernelGGL(k_fit_dd_f64, grid, dim3(256), 0, s, g);
   }
@@ -2094,10 +2113,16 @@ static int first_splits_lp(const dp_ctx* c) {
 //   FP32      20 -> 12    21 -> 13    26 -> 16    30 -> 21    35 -> 50
 // (each work-group forms D anew, which pays while few work-groups share a
 // column tile's and launches are what the rest of the time goes to; the mixed
-// forms' waves are the splits, whose number falls with the atoms).
+// forms' waves are the splits, whose number falls with the atoms).  Narrower
+// layers gain as much (64-wide, whole compute: FP64 -10 to -19 us, 16-bit -5,
+// FP32 -9 to -5).  With more than two types the mixed bounds fall with their
+// number: every section of T is staged again by each work-group (three types,
+// FP32 at 450 / 630 / 990 / 1,260 atoms -1 / +3 / +2 / +11 us, 16-bit at 450 /
+// 630 / 768 -1 / +1 / +2; FP64 -12 to -3 up to 1,770).
 static bool fit_first(const dp_ctx* c, int32_t mode) {
   if (mode == DP_FP64) return c->natoms_last <= 1792;
-  return !fit1_fused(c, mode) && c->natoms_last <= (mix_kinds(mode).fit1 == 3 ? 1280 : 768) && first_splits_lp(c) > 1;
+  const int64_t most = mix_kinds(mode).fit1 == 3 ? 1280 : 768, types = c->model->desc.ntypes;
+  return !fit1_fused(c, mode) && c->natoms_last <= (types > 2 ? 2 * most / types : most) && first_splits_lp(c) > 1;
 }
 
 template <int MT>

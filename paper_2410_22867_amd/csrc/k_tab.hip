@@ -161,14 +161,18 @@ struct TabArgs {
 // made the table's trip from L2 the bound of both kernels.  Most rows lie at
 // small x (s(r) falls to 0 at the cut-off: 9 of 10 water rows at x < 3, 30 of
 // the 1,475 intervals), so a work-group of WPB = 16 waves, one per CU, keeps
-// the first A.nk intervals of its net in LDS, [interval][feature][power] with
+// the first nk intervals of its net in LDS, [interval][feature][power] with
 // the interval stride an odd number of 16-byte units: lanes that read
 // neighbouring intervals, or neighbouring features, fall in different banks.
 // Rows past the window read L2.  Frames of few columns take 4-wave
 // work-groups and no window (launch_embed_tab).  water12k: forward 395 ->
-// 103 us, backward 418 -> 187 us; copper of 23,328 atoms 2,175 -> 346 and
+// 86 us, backward 418 -> 176 us; copper of 23,328 atoms 2,175 -> 346 and
 // 1,746 -> 596 us.  The backward is now bound by LDS reads (4.8 KB per window
-// row of 64 lanes at 128 bytes per cycle: ~100 us), the forward by issue.
+// row of 64 lanes at 128 bytes per cycle: ~100 us), the forward by issue.  The
+// window holds intervals, so a finer table has fewer rows in it; the whole
+// compute with it and with every row from L2 as before, 12,288 water atoms:
+// h = 0.1 835 / 1,440 us, 0.02 973 / 1,443, 0.01 1,051 / 1,451, 0.005 1,138 /
+// 1,465; 4,000 copper atoms: 459 / 1,094, 554 / 1,225, 593 / 1,282, 660 / 1,336.
 template <int M1>
 struct TabWin {
   static constexpr int stride = 6 * M1 + 2;                   // doubles per interval

@@ -11,7 +11,8 @@
 typedef int err_t;
 typedef struct { uint32_t x, y, z; } dim3_t;
 
-enum { MAX_FN = 1024, MAX_ALLOC = 4096, MAX_LAUNCH = 8192, ARG_WORDS = 192, NCU = 263 };
+enum { MAX_FN = 1024, MAX_ALLOC = 4096, MAX_LAUNCH = 8192, ARG_WORDS = 192 };
+static int ncu = 263; /* (a prime: sizes in lines per compute unit are told from the others) */
 
 static struct { const void* host; const char* name; } fn[MAX_FN];
 static int nfn;
@@ -28,7 +29,8 @@ static launch_t launch[MAX_LAUNCH];
 static int nlaunch;
 
 /* ---- reading the record */
-int rec_ncu(void) { return NCU; }
+int rec_ncu(void) { return ncu; }
+void rec_set_ncu(int n) { ncu = n; }
 int rec_launches(void) { return nlaunch; }
 const launch_t* rec_launch(int k) { return &launch[k]; }
 void rec_clear(void) { nlaunch = 0; }
@@ -73,7 +75,7 @@ err_t hipGetSymbolAddress(void** p, const void* s) { (void)s; return hipMalloc(p
 /* ---- device, events, streams */
 err_t hipGetDevice(int* d) { *d = 0; return 0; }
 err_t hipSetDevice(int d) { (void)d; return 0; }
-err_t hipDeviceGetAttribute(int* v, int a, int d) { (void)a; (void)d; *v = NCU; return 0; }
+err_t hipDeviceGetAttribute(int* v, int a, int d) { (void)a; (void)d; *v = ncu; return 0; }
 err_t hipDeviceSynchronize(void) { return 0; }
 err_t hipStreamSynchronize(void* s) { (void)s; return 0; }
 err_t hipGetLastError(void) { return 0; }

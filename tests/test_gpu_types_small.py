@@ -72,6 +72,32 @@ def test_small_frames_of_many_types(ntypes, mols):
     assert ctx.status() == 0
 
 
+@pytest.mark.parametrize("mols,fits", [(64, (48, 64, 176, 192, 224)), (299, (64, 224)), (300, (64, 192)), (427, (192, 176))])
+def test_fitting_routes_of_other_widths(mols, fits):
+    """Both sides of the widths and atom counts at which narrower fitting
+    layers change their kernels, two types: as above without the gradients."""
+    from paper_2410_22867_amd import dpse
+    _, fr, _ = _case(3, mols)
+    fr = I.Frame(fr.coords, np.where(fr.types == 2, 0, fr.types).astype(np.int32), fr.box)
+    dev = torch.device("cuda:0")
+    x, t = torch.tensor(fr.coords, device=dev), torch.tensor(fr.types, device=dev)
+    for fit in fits:
+        desc = dataclasses.replace(I.WATER, fit=(fit,) * 3)
+        p = I.init_params(desc, 132, I.WATER_OUTPUT_SCALE)
+        o = oracle.compute(fr.coords, fr.types, fr.box, desc, p)
+        ctx = dpse.Context(dpse.Model(desc, p), fr.n)
+        nl, _ = ctx.build_nlist(x, t, fr.box)
+        for mode in ("fp64", "bf16", "mix_fp32"):
+            print("width", fit, fr.n, mode, flush=True)
+            r = {k: v.cpu().numpy() for k, v in ctx.compute(x, t, fr.box, nl, mode=mode, want_atom_energy=True).items()}
+            if mode == "fp64":
+                assert np.abs(r["Ei"] - o["Ei"]).max() <= 1e-10 * np.abs(o["Ei"]).max()
+                assert np.abs(r["F"] - o["F"]).max() <= 1e-9
+            else:
+                assert np.abs(r["Ei"] - o["Ei"]).max() <= EI_MAX[mode]
+                assert np.sqrt(((r["F"] - o["F"]) ** 2).mean()) <= REL_F[mode] * np.sqrt((o["F"] ** 2).mean())
+
+
 def test_widest_layer_pairs_on_a_large_frame():
     """256-wide fitting layers from 32,768 atoms on: the two-tile pair kernel
     holds 66 KB of activations in LDS.  Atomic energies and forces against the
